@@ -26,6 +26,9 @@ constexpr int kTileRows = 4;       // by 4 rows
 // edge is 32 >> level voxels.
 enum : uint8_t { kUnknown = 0, kFree = 1, kOccupied = 2, kOutside = 3, kUnknownBrick = 8, kFreeBrick = 9 };
 constexpr uint32_t kLevelShift = 2, kLevelMask = 7;
+// (block edge - 1) of level l in bits 4 l .. 4 l + 3: 0, 15, 7, 3, 1 (a byte's
+// level field, in place at bit 2, is the shift)
+constexpr uint32_t kEdgeOfLevel = 0x137f0u;
 __host__ __device__ inline bool is_unknown(uint32_t s) { return (s & 3u) == 0u; }
 
 // The block levels of one brick's voxels up to the brick (levels 2 to 4; the

@@ -536,6 +536,32 @@ __global__ __launch_bounds__(kBuildThreads) void k_mask_build(MapDev M, SensorDe
 // requested before the step ends, and a mask word is used one step after it
 // was requested, so both loads have a step of work to hide behind. Ends with
 // the tile's bins added to the node's global bins.
+//
+// Mirrored coordinates: on an axis the ray moves down, the coordinate is
+// negated (voxel index x becomes ~x, boundary b becomes -b), so every ray moves
+// up on every axis. The parameter (boundary - q) * (1/d) is the same float
+// either way (negating both factors is exact). A voxel's byte address merges
+// bit fields of its coordinates, so the mirroring is undone by one exclusive or
+// of the merged address.
+//
+// One step leaves the aligned block of `edge` voxels around the voxel (edge 1:
+// the voxel itself), through the face whose boundary parameter T comes first
+// (ties x, y, z), and then every axis has crossed the boundaries that come
+// before that crossing in the DDA's order: those with parameter below T, or
+// equal to T on the exit axis and the axes before it. An axis's position at T
+// is q + T d; the error of that sum is below 0.01 voxel (|q| <= 8192, T at most
+// the grid's diagonal, three roundings of T and one of the sum), so every
+// boundary but the one nearest to it lies at least 0.49 voxel away and its side
+// of T is not in doubt, and the nearest one is decided by its own parameter,
+// computed as the single step computes it. (A boundary the ray starts on or has
+// passed is never crossed again: the coordinate does not fall.) One probe an
+// axis replaces the three or four of a search over the block's boundaries, and
+// a single voxel is the same step with edge 1, so a wave takes one path: this
+// loop is bound by instruction issue, and by the latency of its chain where a
+// level has few nodes. Against the search: 59.8 -> 48.1 ms a batch of 4 trees of
+// 3000 nodes (720 x 120 rays, 512 x 512 x 128 grid), 2.93 -> 2.12 ms the
+// absolute pass of 1000 of these nodes, 1.21 -> 1.01 ms one tree of 500 nodes
+// (360 x 60 rays, 200 x 200 x 60 grid).
 template <bool kMarginal, int kTh>
 __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
                                            int32_t tile, uint32_t* __restrict__ s_bins) {
@@ -567,35 +593,26 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     const float4 p = Tr.q4[node];
     const float4 d = S.d4[rr];
     const float4 iv = S.iv4[rr];
-    const int32_t sx = d.x > 0.f ? 1 : (d.x < 0.f ? -1 : 0);
-    const int32_t sy = d.y > 0.f ? 1 : (d.y < 0.f ? -1 : 0);
-    const int32_t sz = d.z > 0.f ? 1 : (d.z < 0.f ? -1 : 0);
-    int32_t ix = (int32_t)floorf(p.x), iy = (int32_t)floorf(p.y), iz = (int32_t)floorf(p.z);
-    // Face-crossing parameters (b - q) / d with b the next voxel boundary,
-    // kept as floats (integers, exact): b moves by the step sign. An axis the
-    // ray does not move along has b = +inf and a factor 1, so its parameter
-    // stays +inf.
+    // Mirrored coordinates of the ray: 0 or ~0 per axis (the mirroring), the
+    // node, the direction and its inverse (both >= 0), and the voxel. An axis
+    // the ray does not move along has factor +inf: its next boundary lies past
+    // the node, so its parameter is +inf, and its voxel never changes.
     const float inf = __builtin_inff();
-    float bx = sx ? (float)(ix + (sx > 0 ? 1 : 0)) : inf;
-    float by = sy ? (float)(iy + (sy > 0 ? 1 : 0)) : inf;
-    float bz = sz ? (float)(iz + (sz > 0 ? 1 : 0)) : inf;
-    const float fx = sx ? iv.x : 1.f, fy = sy ? iv.y : 1.f, fz = sz ? iv.z : 1.f;
-    const float dbx = (float)sx, dby = (float)sy, dbz = (float)sz;
-    // the node's coordinates, -inf on an axis the ray does not move along: every
-    // boundary parameter of that axis, (b - q) * 1 with b = +inf or a brick
-    // exit, is then +inf
-    const float qx = sx ? p.x : -inf, qy = sy ? p.y : -inf, qz = sz ? p.z : -inf;
-    // a block's exit boundary along an axis: its low face, plus its edge when moving up
-    const int32_t upx = sx > 0 ? -1 : 0, upy = sy > 0 ? -1 : 0, upz = sz > 0 ? -1 : 0;
-    float tx = (bx - qx) * fx;
-    float ty = (by - qy) * fy;
-    float tz = (bz - qz) * fz;
+    const int32_t mx = d.x < 0.f ? -1 : 0, my = d.y < 0.f ? -1 : 0, mz = d.z < 0.f ? -1 : 0;
+    const float qx = mx ? -p.x : p.x, qy = my ? -p.y : p.y, qz = mz ? -p.z : p.z;
+    const float dx = fabsf(d.x), dy = fabsf(d.y), dz = fabsf(d.z);
+    const float fx = dx != 0.f ? fabsf(iv.x) : inf, fy = dy != 0.f ? fabsf(iv.y) : inf, fz = dz != 0.f ? fabsf(iv.z) : inf;
+    int32_t ux = (int32_t)floorf(p.x) ^ mx, uy = (int32_t)floorf(p.y) ^ my, uz = (int32_t)floorf(p.z) ^ mz;
+    int32_t usum = ux + uy + uz;
+    const uint32_t mirror = voxel_addr(mx, my, mz, M);
+    const int32_t rv_before = (int32_t)__float_as_uint(S.rv) - 1;       // the float below the range (> 0)
+    const float rv_most = __uint_as_float((uint32_t)rv_before);
     float t = 0.f, h = S.rv;
     uint32_t n_abs = 0, n_new = 0;
     const gbytes_t grid = as_global(M.bricks);
     // the node lies inside the grid and t = 0 < rv, so its own voxel is
     // visited; a lane without a ray reads a padding byte and is done at once
-    uint32_t addr = has_ray ? voxel_addr(ix, iy, iz, M) : M.outside;   // address of the current voxel
+    uint32_t addr = has_ray ? voxel_addr(ux, uy, uz, M) ^ mirror : M.outside;   // address of the current voxel
     // (this first byte is read through the generic pointer and the loop's through
     // the global one, so the compiler keeps the loop's load at the end of the
     // step instead of merging the two into one load at the top of the loop)
@@ -606,126 +623,94 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     if (ballot(has_ray)) {
         uint64_t alive;
         do {
-            // Straight-line step: the mask word requested in the previous step
-            // and the current voxel's byte are used first, then the next voxel is
-            // found and its byte requested. A lane that has finished (or left the
-            // grid) reads a padding byte, which is neither unknown nor occupied.
+            // The mask word requested in the previous step and the current voxel's
+            // byte are used first, then the next voxel is found and its byte
+            // requested. A lane that has finished (or left the grid) reads a
+            // padding byte, which is neither unknown nor occupied.
             if (kMarginal) {
                 n_new += (pend & !((mw >> mb) & 1u)) ? 1u : 0u;
                 pend = false;
             }
             h = st == kOccupied ? t : h;
-            // An aligned block (a block of 2x2x2 bricks, a brick, a quarter brick
-            // or, for free voxels, a 2x2x2 block) whose voxels are all free, or
-            // all unknown with the parent's mask uniform over it (every bit clear
-            // or every bit set; a wholly unknown block over which the mask is
-            // mixed is crossed a brick or a quarter at a time where it is uniform
-            // over that), is crossed in one step: it is left through the face whose
-            // boundary parameter comes first (ties x, y, z) and every other axis
-            // has crossed the boundaries that come before that crossing in the
-            // same order. The voxels crossed are one per crossing; crossing an
-            // unknown block counts them all as absolute, and as marginal when no
-            // ancestor observes any of them. An unknown block that the range ends
-            // in is finished in one step too: its voxels visited before the range
-            // ends are counted and the ray ends.
-            float tn;                           // entry parameter of the next voxel
-            float kx, ky, kz;                   // boundaries this step crosses along each axis (set by
-                                                // the crossing when it is taken, else by the voxel step)
-            uint32_t level = (st >> kLevelShift) & kLevelMask;   // the voxel's block: edge 32 >> level, or none (0)
-            const bool free_blk = (level != 0u) & ((st & 3u) == kFree);
-            bool cand = free_blk;
-            uint32_t code = kMaskNone;          // (the absolute pass, and the root, see nothing observed)
-            // (a wholly unknown block with a uniform code is always crossed by its
-            // code: the words of its brick need not exist)
-            if ((level != 0u) & ((st & 3u) == kUnknown)) {
-                if (kMarginal && pc != nullptr) {
-                    const uint32_t b = mask_brick(ix, iy, iz, M);
-                    if (b != cb_idx) {
-                        cw = pc[b];
-                        cb_idx = b;
+            // The block crossed in this step (e1: its edge - 1): the marked block
+            // around a free voxel; for an unknown voxel the largest marked block
+            // over which the parent's mask is uniform (every bit clear, or every
+            // bit set), else the voxel itself, whose mask bit is looked up. The
+            // absolute pass and the root see nothing observed.
+            const bool unk = is_unknown(st);
+            uint32_t e1 = __builtin_amdgcn_ubfe(kEdgeOfLevel, st & (kLevelMask << kLevelShift), 4u);
+            bool fresh = unk;           // the voxels crossed are unknown and no ancestor observes them
+            if (kMarginal && pm != nullptr) {
+                fresh = false;
+                if (unk) {
+                    const int32_t x = ux ^ mx, y = uy ^ my, z = uz ^ mz;
+                    const uint32_t b = mask_brick(x, y, z, M);
+                    uint32_t code = kMaskMixed;
+                    // (a wholly unknown block with a uniform code is always crossed by its
+                    // code: the words of its brick need not exist)
+                    if (e1 != 0u) {
+                        if (b != cb_idx) {
+                            cw = *(gwords_t)((gbytes_t)pc + (b << 2));
+                            cb_idx = b;
+                        }
+                        // the code of its block of 2x2x2 bricks (a 16-voxel block), else the
+                        // brick's (a brick at most), else its quarter's (a quarter at most)
+                        const uint32_t qs = 2u + ((((uint32_t)x >> 1) & 2u) | ((uint32_t)y & 4u) | (((uint32_t)z << 1) & 8u));
+                        const uint32_t bc = (cw >> 18) & 3u, kc = cw & 3u, qc = (cw >> qs) & 3u;
+                        const bool block_uniform = (e1 == 15u) & (bc != kMaskMixed);
+                        const bool brick_uniform = kc != kMaskMixed;
+                        code = block_uniform ? bc : (brick_uniform ? kc : qc);
+                        const uint32_t most = block_uniform ? 15u : (brick_uniform ? 7u : 3u);
+                        e1 = code == kMaskMixed ? 0u : (e1 < most ? e1 : most);
                     }
-                    // the code of its block of 2x2x2 bricks (a 16-voxel block), else the
-                    // brick's (a brick at most), else its quarter's (a quarter at most)
-                    const uint32_t qs = 2u + ((((uint32_t)ix >> 1) & 2u) | ((uint32_t)iy & 4u) | (((uint32_t)iz << 1) & 8u));
-                    const uint32_t bc = (cw >> 18) & 3u;
-                    const bool block_uniform = (level == 1u) & (bc != kMaskMixed);
-                    const bool brick_uniform = (cw & 3u) != kMaskMixed;
-                    code = block_uniform ? bc : (brick_uniform ? (cw & 3u) : ((cw >> qs) & 3u));
-                    level = block_uniform ? 1u : (brick_uniform ? (level > 2u ? level : 2u) : 3u);
-                }
-                cand = code != kMaskMixed;
-            }
-            if (cand) {
-                const int32_t edge = 32 >> level;
-                const float Tx = ((float)((ix & -edge) + (edge & upx)) - qx) * fx;
-                const float Ty = ((float)((iy & -edge) + (edge & upy)) - qy) * fy;
-                const float Tz = ((float)((iz & -edge) + (edge & upz)) - qz) * fz;
-                const bool fx_ = (Tx <= Ty) & (Tx <= Tz);
-                const bool fy_ = !fx_ & (Ty <= Tz);
-                const bool fz_ = !fx_ & !fy_;
-                const float T = fx_ ? Tx : (fy_ ? Ty : Tz);
-                // An axis that precedes the exit axis in the tie order also
-                // counts a boundary whose parameter equals T: it compares with
-                // the next float above T (T >= 0; +0 for -0 first). When the
-                // range ends inside an unknown block (cut), the ray's remaining
-                // voxels are the current one and one per boundary whose
-                // parameter is below the range, all inside the block: every
-                // axis counts against the range, and the ray ends (T >= range).
-                const bool cut = !free_blk & !(T < S.rv);
-                const float Tn = __uint_as_float(__float_as_uint(T + 0.f) + 1u);
-                const bool wide = ballot(level == 1u) != 0ull;     // some lane crosses a 16-voxel block
-                kx = crossings_before(bx, dbx, qx, fx, cut ? S.rv : (fx_ ? T : Tn), wide) + (fx_ ? 1.f : 0.f);
-                ky = crossings_before(by, dby, qy, fy, cut ? S.rv : (fz_ ? Tn : T), wide) + (fy_ ? 1.f : 0.f);
-                kz = crossings_before(bz, dbz, qz, fz, cut ? S.rv : T, wide) + (fz_ ? 1.f : 0.f);
-                tn = T;
-                if (!free_blk) {
-                    const uint32_t v = (uint32_t)(kx + ky + kz);
-                    n_abs += v;
-                    if (kMarginal) n_new += code == kMaskNone ? v : 0u;
+                    fresh = code == kMaskNone;
+                    pend = code == kMaskMixed;
+                    if (pend) {
+                        const uint32_t off = ((b << 4) | ((uint32_t)(z & 7) << 1) | ((uint32_t)(y & 4) >> 2)) << 2;  // < 2^29 bytes
+                        mw = *(gwords_t)((gbytes_t)pm + off);
+                        mb = mask_bit(x, y);
+                    }
                 }
             }
-            if (!cand) {
-                const bool unk = is_unknown(st);
-                n_abs += unk ? 1u : 0u;
-                if (kMarginal && pm != nullptr) {
-                    // every lane loads (a lane off unknown voxels reads word 0), so the
-                    // word lands in the register the next step reads
-                    const uint32_t off = (unk ? mask_word(ix, iy, iz, M) : 0u) << 2;   // < 2^29 bytes
-                    mw = *(gwords_t)((gbytes_t)pm + off);
-                    mb = mask_bit(ix, iy);
-                    pend = unk;
-                }
-                const bool mx = (tx <= ty) & (tx <= tz);
-                const bool my = !mx & (ty <= tz);
-                const bool mz = !mx & !my;
-                tn = mx ? tx : (my ? ty : tz);
-                kx = mx ? 1.f : 0.f;
-                ky = my ? 1.f : 0.f;
-                kz = mz ? 1.f : 0.f;
-            }
-            // one update for both kinds of step (counts are small integers: exact)
-            ix += __mul24((int32_t)kx, sx);
-            iy += __mul24((int32_t)ky, sy);
-            iz += __mul24((int32_t)kz, sz);
-            bx = __builtin_fmaf(kx, dbx, bx);
-            by = __builtin_fmaf(ky, dby, by);
-            bz = __builtin_fmaf(kz, dbz, bz);
+            // the block's exit boundary and its parameter on each axis; the first one
+            const float Tx = ((float)((ux | (int32_t)e1) + 1) - qx) * fx;
+            const float Ty = ((float)((uy | (int32_t)e1) + 1) - qy) * fy;
+            const float Tz = ((float)((uz | (int32_t)e1) + 1) - qz) * fz;
+            const float Txy = fminf(Tx, Ty), T = fminf(Txy, Tz);
+            // Boundaries crossed: parameter at most T on the exit axis and the axes
+            // before it, at most the float below T on those after it (T >= +0; below
+            // 0 there is none: a NaN, which no parameter is at most). Where the range
+            // ends inside the block, the ray visits the current voxel and one per
+            // boundary whose parameter is below the range, and ends.
+            const bool in_range = T < S.rv;
+            const float at_most = fminf(T, rv_most);
+            const int32_t tb = (int32_t)__float_as_uint(T) - 1;
+            const float below = __uint_as_float((uint32_t)(tb < rv_before ? tb : rv_before));
+            const float cy_at = Tx == T ? below : at_most, cz_at = Txy == T ? below : at_most;
+            const float ex = __builtin_rintf(__builtin_fmaf(at_most, dx, qx));
+            const float ey = __builtin_rintf(__builtin_fmaf(at_most, dy, qy));
+            const float ez = __builtin_rintf(__builtin_fmaf(at_most, dz, qz));
+            ux = max(ux, (int32_t)ex - ((ex - qx) * fx <= at_most ? 0 : 1));
+            uy = max(uy, (int32_t)ey - ((ey - qy) * fy <= cy_at ? 0 : 1));
+            uz = max(uz, (int32_t)ez - ((ez - qz) * fz <= cz_at ? 0 : 1));
+            // voxels of the block visited: one per boundary crossed, and the last one of a ray that ends
+            const int32_t unew = ux + uy + uz;
+            const uint32_t count = (uint32_t)(unew - usum) + (in_range ? 0u : 1u);
+            usum = unew;
+            n_abs += unk ? count : 0u;
+            if (kMarginal) n_new += fresh ? count : 0u;
             // a lane that stops here (occupied, finished or outside) compares +inf
             // with the range: one comparison gives the mask the ballot takes
-            const float tn_go = (st & 2u) == 0u ? tn : inf;
+            const float tn_go = (st & 2u) == 0u ? T : inf;
             const bool next_ok = tn_go < S.rv;
             alive = ballot(next_ok);
-            addr = next_ok ? voxel_addr(ix, iy, iz, M) : M.outside;
+            addr = next_ok ? voxel_addr(ux, uy, uz, M) ^ mirror : M.outside;
             st = grid[addr];
-            tx = (bx - qx) * fx;
-            ty = (by - qy) * fy;
-            tz = (bz - qz) * fz;
-            t = tn;
+            t = T;
         } while (alive);
     }
     if (kMarginal) {
         n_new += (pend & !((mw >> mb) & 1u)) ? 1u : 0u;
-        if (pm == nullptr) n_new = n_abs;                   // the root: nothing is observed yet
         if (has_ray) Tr.dpan[(size_t)node * S.R + r] = h;
         if (n_new) atomicAdd(&s_bins[S.B + bin], n_new);
     }

@@ -1,0 +1,61 @@
+"""GPU parity at the edges of the block step of the ray walk: coordinates and parameters near the
+largest a grid allows (where the rounding of a position along the ray is largest), rays that start
+on voxel faces, edges and corners, and directions along the axes and their diagonals, on maps of
+nested uniform blocks, bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2609_40297_amd import workloads as W
+from tests.gpu_util import assert_same, gpu_eval_tree, log, threads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mg():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_40297_amd import mg as mgmod
+    mgmod.lib()
+    return mgmod
+
+
+def _blocks(rng, dims):
+    """States of nested uniform blocks: 16-voxel blocks of one state, some split down to 8, 4, 2 and 1."""
+    nx, ny, nz = dims
+    st = np.zeros((nz, ny, nx), np.uint8)
+    for edge, keep in ((16, 1.0), (8, 0.4), (4, 0.3), (2, 0.3), (1, 0.2)):
+        n = [-(-d // edge) for d in (nz, ny, nx)]
+        s = rng.choice(np.array([W.UNK, W.FREE, W.OCC], np.uint8), n, p=[0.45, 0.548, 0.002])
+        take = rng.uniform(size=n) < keep
+        for a in (0, 1, 2):
+            s, take = np.repeat(s, edge, a), np.repeat(take, edge, a)
+        s, take = s[:nz, :ny, :nx], take[:nz, :ny, :nx]
+        st = np.where(take, s, st)
+    return st
+
+
+@pytest.mark.parametrize("dims, range_vox", [((8192, 17, 16), 9000.0), ((16, 4099, 23), 5000.0), ((9, 16, 2047), 2050.5),
+                                             ((63, 65, 33), 70.0)])
+def test_block_step_at_the_largest_coordinates(mg, dims, range_vox):
+    from oracle import mgref
+    rng = np.random.Generator(np.random.PCG64(sum(dims)))
+    m = W.Map(states=_blocks(rng, dims), voxel_m=1.0, origin_m=np.zeros(3, np.float32))
+    ext = np.array(dims, np.float32)
+    n = 12
+    pos = (rng.uniform(0.0, 1.0, (n, 3)) * (ext - 0.01)).astype(np.float32)
+    pos[1] = np.floor(pos[1])                               # a voxel corner
+    pos[2, 0] = np.floor(pos[2, 0])                         # a face
+    pos[3, 1:] = np.floor(pos[3, 1:])                       # an edge
+    pos[4] = np.floor(pos[4]) + np.float32(0.5)             # a centre
+    pos[5] = np.nextafter(ext, np.float32(0))               # the far corner
+    pos[6] = 0.0                                            # the near corner
+    par = np.array([-1] + [int(rng.integers(0, i)) for i in range(1, n)], np.int32)
+    tree = W.Tree(pos_m=pos, parent=par)
+    sensor = W.Sensor(n_az=72, n_el=21, fov_h_deg=90.0, fov_v_deg=63.0, range_m=float(range_vox), yaw_bins=8,
+                      az_offset_deg=-2.5)                   # column centres on the axes and diagonals, row 10 level
+    log(f"[steps] {dims}: {np.bincount(m.states.reshape(-1), minlength=3).tolist()}")
+    ref = mgref.eval_tree(m, tree, sensor, n_threads=threads())
+    got = gpu_eval_tree(mg, m, tree, sensor, mode="both")
+    assert_same(got, ref, keys=("g_db", "k_db", "D", "g_abs", "k_abs"))
