@@ -607,7 +607,10 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     const uint32_t mirror = voxel_addr(mx, my, mz, M);
     const int32_t rv_before = (int32_t)__float_as_uint(S.rv) - 1;       // the float below the range (> 0)
     const float rv_most = __uint_as_float((uint32_t)rv_before);
-    float t = 0.f, h = S.rv;
+    // h is kept negated (and t starts at -0): a hit at parameter 0 is +0 in the
+    // node's own voxel and -0 in a voxel entered at once, since only an axis the
+    // ray moves down has a boundary at the node, with parameter 0 * (1/d), d < 0
+    float t = -0.f, h = -S.rv;
     uint32_t n_abs = 0, n_new = 0;
     const gbytes_t grid = as_global(M.bricks);
     // the node lies inside the grid and t = 0 < rv, so its own voxel is
@@ -631,7 +634,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
                 n_new += (pend & !((mw >> mb) & 1u)) ? 1u : 0u;
                 pend = false;
             }
-            h = st == kOccupied ? t : h;
+            h = st == kOccupied ? -t : h;
             // The block crossed in this step (e1: its edge - 1): the marked block
             // around a free voxel; for an unknown voxel the largest marked block
             // over which the parent's mask is uniform (every bit clear, or every
@@ -711,7 +714,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     }
     if (kMarginal) {
         n_new += (pend & !((mw >> mb) & 1u)) ? 1u : 0u;
-        if (has_ray) Tr.dpan[(size_t)node * S.R + r] = h;
+        if (has_ray) Tr.dpan[(size_t)node * S.R + r] = h == 0.f ? h : -h;
         if (n_new) atomicAdd(&s_bins[S.B + bin], n_new);
     }
     if (n_abs) atomicAdd(&s_bins[bin], n_abs);

@@ -59,3 +59,24 @@ def test_block_step_at_the_largest_coordinates(mg, dims, range_vox):
     ref = mgref.eval_tree(m, tree, sensor, n_threads=threads())
     got = gpu_eval_tree(mg, m, tree, sensor, mode="both")
     assert_same(got, ref, keys=("g_db", "k_db", "D", "g_abs", "k_abs"))
+
+
+@pytest.mark.parametrize("seed", [3, 4])
+def test_hits_at_parameter_zero(mg, seed):
+    """Nodes on voxel faces, edges and corners beside occupied voxels, and inside them: the first hit at
+    parameter 0 keeps the sign of its zero (depth buffers are compared by their bits)."""
+    from oracle import mgref
+    rng = np.random.Generator(np.random.PCG64(seed))
+    dims = (19, 17, 14)
+    st = rng.choice(np.array([W.UNK, W.FREE, W.OCC], np.uint8), dims[::-1], p=[0.3, 0.3, 0.4])
+    m = W.Map(states=st, voxel_m=1.0, origin_m=np.zeros(3, np.float32))
+    pos = (rng.uniform(0.0, 1.0, (40, 3)) * np.array(dims)).astype(np.float32)
+    pos = np.where(rng.uniform(size=pos.shape) < 0.7, np.floor(pos), pos).astype(np.float32)
+    tree = W.Tree(pos_m=pos, parent=np.array([-1] + [int(rng.integers(0, i)) for i in range(1, 40)], np.int32))
+    sensor = W.Sensor(n_az=72, n_el=21, fov_h_deg=90.0, fov_v_deg=63.0, range_m=9.0, yaw_bins=8, az_offset_deg=-2.5)
+    ref = mgref.eval_tree(m, tree, sensor, n_threads=threads())
+    zeros = ref["D"] == 0.0
+    log(f"[zero hits] {int(zeros.sum())} of {zeros.size}, {int(np.signbit(ref['D'][zeros]).sum())} negative")
+    assert 0 < int(np.signbit(ref["D"][zeros]).sum()) < int(zeros.sum())
+    assert_same(gpu_eval_tree(mg, m, tree, sensor), ref)
+    assert_same(gpu_eval_tree(mg, m, tree, sensor, mode="batch"), ref)
