@@ -562,7 +562,17 @@ __global__ __launch_bounds__(kBuildThreads) void k_mask_build(MapDev M, SensorDe
 // 3000 nodes (720 x 120 rays, 512 x 512 x 128 grid), 2.93 -> 2.12 ms the
 // absolute pass of 1000 of these nodes, 1.21 -> 1.01 ms one tree of 500 nodes
 // (360 x 60 rays, 200 x 200 x 60 grid).
-template <bool kMarginal, int kTh>
+//
+// kSeg > 1 gives each ray to kSeg lanes, each walking the stretch of the ray
+// between two parameters (kSeg equal parts of the range; a wave then holds a
+// kSeg times narrower block of pixels), for launches too small to fill the chip:
+// they last as long as the longest ray's chain of dependent steps, which the
+// split divides. A stretch starts in the voxel that the walk stands in when every
+// boundary with a parameter below the stretch's start is crossed (found as a
+// step finds it), whose visit the stretch before has counted, and ends as the
+// range ends; stretches after the ray's first hit count nothing, and a ray that
+// has left the grid starts its later stretches outside.
+template <bool kMarginal, int kTh, int kSeg = 1>
 __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
                                            int32_t tile, uint32_t* __restrict__ s_bins) {
     const int32_t tid = threadIdx.x;
@@ -584,8 +594,10 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     // this wave's pixel block and this lane's pixel in it (column c, row j)
     const int32_t blk = __builtin_amdgcn_readfirstlane(tile * (kTh / 64) + (tid >> 6));
     const int32_t cb = __builtin_amdgcn_readfirstlane(blk / S.nrb);
-    const int32_t c = cb * kRayBlockCols + (tid & (kRayBlockCols - 1));
-    const int32_t j = (blk - cb * S.nrb) * kRayBlockRows + ((tid & 63) / kRayBlockCols);
+    constexpr int32_t kCols = kRayBlockCols / kSeg, kPix = 64 / kSeg;
+    const int32_t seg = (tid & 63) / kPix;               // this lane's stretch of its ray
+    const int32_t c = cb * kCols + (tid & (kCols - 1));
+    const int32_t j = (blk - cb * S.nrb) * kRayBlockRows + ((tid & (kPix - 1)) / kCols);
     const bool has_ray = (blk < S.n_blocks) & (c < S.W) & (j < S.H);
     const int32_t r = c * S.H + j;
     const int32_t rr = has_ray ? r : 0;
@@ -603,19 +615,42 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     const float dx = fabsf(d.x), dy = fabsf(d.y), dz = fabsf(d.z);
     const float fx = dx != 0.f ? fabsf(iv.x) : inf, fy = dy != 0.f ? fabsf(iv.y) : inf, fz = dz != 0.f ? fabsf(iv.z) : inf;
     int32_t ux = (int32_t)floorf(p.x) ^ mx, uy = (int32_t)floorf(p.y) ^ my, uz = (int32_t)floorf(p.z) ^ mz;
-    int32_t usum = ux + uy + uz;
+    // the stretch's start and end parameters, and the float below its end (> 0);
+    // a range of less than a voxel a stretch is left to the ray's first lane
+    const bool split = kSeg > 1 && S.rv >= (float)kSeg;
+    const float t0 = split ? S.rv * ((float)seg / (float)kSeg) : 0.f;
+    const float t1 = split && seg < kSeg - 1 ? S.rv * ((float)(seg + 1) / (float)kSeg) : S.rv;
+    const int32_t t1_before = (int32_t)__float_as_uint(t1) - 1;
+    const float t1_most = __uint_as_float((uint32_t)t1_before);
+    bool inside = has_ray & (split | (seg == 0));   // (the node lies inside the grid)
+    bool counted = false;                // the current voxel's visit is the stretch before's
+    if (split && seg > 0) {
+        const float most = __uint_as_float(__float_as_uint(t0) - 1u);
+        const float ex = __builtin_rintf(__builtin_fmaf(most, dx, qx));
+        const float ey = __builtin_rintf(__builtin_fmaf(most, dy, qy));
+        const float ez = __builtin_rintf(__builtin_fmaf(most, dz, qz));
+        ux = max(ux, (int32_t)ex - ((ex - qx) * fx <= most ? 0 : 1));
+        uy = max(uy, (int32_t)ey - ((ey - qy) * fy <= most ? 0 : 1));
+        uz = max(uz, (int32_t)ez - ((ez - qz) * fz <= most ? 0 : 1));
+        inside = has_ray & ((uint32_t)(ux ^ mx) < (uint32_t)M.nx) & ((uint32_t)(uy ^ my) < (uint32_t)M.ny) &
+                 ((uint32_t)(uz ^ mz) < (uint32_t)M.nz);
+        counted = true;
+    }
+    int32_t usum = ux + uy + uz + (counted ? 1 : 0);
     const uint32_t mirror = voxel_addr(mx, my, mz, M);
-    const int32_t rv_before = (int32_t)__float_as_uint(S.rv) - 1;       // the float below the range (> 0)
-    const float rv_most = __uint_as_float((uint32_t)rv_before);
+    // lanes holding the earlier stretches of this lane's ray, and those that hit
+    constexpr uint64_t kRayLanes = kSeg == 4 ? 0x0001000100010001ull : (kSeg == 2 ? 0x0000000100000001ull : 0x0101010101010101ull);
+    const uint64_t earlier = kSeg > 1 ? ((kRayLanes << (tid & (kPix - 1))) & ((1ull << (tid & 63)) - 1ull)) : 0ull;
+    uint64_t hits = 0ull;
     // h is kept negated (and t starts at -0): a hit at parameter 0 is +0 in the
     // node's own voxel and -0 in a voxel entered at once, since only an axis the
     // ray moves down has a boundary at the node, with parameter 0 * (1/d), d < 0
-    float t = -0.f, h = -S.rv;
+    float t = kSeg > 1 && seg > 0 ? t0 : -0.f, h = -S.rv;
     uint32_t n_abs = 0, n_new = 0;
     const gbytes_t grid = as_global(M.bricks);
-    // the node lies inside the grid and t = 0 < rv, so its own voxel is
-    // visited; a lane without a ray reads a padding byte and is done at once
-    uint32_t addr = has_ray ? voxel_addr(ux, uy, uz, M) ^ mirror : M.outside;   // address of the current voxel
+    // a lane without a ray (or whose ray has left the grid) reads a padding byte
+    // and is done at once
+    uint32_t addr = inside ? voxel_addr(ux, uy, uz, M) ^ mirror : M.outside;   // address of the current voxel
     // (this first byte is read through the generic pointer and the loop's through
     // the global one, so the compiler keeps the loop's load at the end of the
     // step instead of merging the two into one load at the top of the loop)
@@ -635,6 +670,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
                 pend = false;
             }
             h = st == kOccupied ? -t : h;
+            if (kSeg > 1) hits |= ballot(st == kOccupied);
             // The block crossed in this step (e1: its edge - 1): the marked block
             // around a free voxel; for an unknown voxel the largest marked block
             // over which the parent's mask is uniform (every bit clear, or every
@@ -667,7 +703,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
                         e1 = code == kMaskMixed ? 0u : (e1 < most ? e1 : most);
                     }
                     fresh = code == kMaskNone;
-                    pend = code == kMaskMixed;
+                    pend = (code == kMaskMixed) & !counted;
                     if (pend) {
                         const uint32_t off = ((b << 4) | ((uint32_t)(z & 7) << 1) | ((uint32_t)(y & 4) >> 2)) << 2;  // < 2^29 bytes
                         mw = *(gwords_t)((gbytes_t)pm + off);
@@ -685,10 +721,10 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
             // 0 there is none: a NaN, which no parameter is at most). Where the range
             // ends inside the block, the ray visits the current voxel and one per
             // boundary whose parameter is below the range, and ends.
-            const bool in_range = T < S.rv;
-            const float at_most = fminf(T, rv_most);
+            const bool in_range = T < t1;
+            const float at_most = fminf(T, t1_most);
             const int32_t tb = (int32_t)__float_as_uint(T) - 1;
-            const float below = __uint_as_float((uint32_t)(tb < rv_before ? tb : rv_before));
+            const float below = __uint_as_float((uint32_t)(tb < t1_before ? tb : t1_before));
             const float cy_at = Tx == T ? below : at_most, cz_at = Txy == T ? below : at_most;
             const float ex = __builtin_rintf(__builtin_fmaf(at_most, dx, qx));
             const float ey = __builtin_rintf(__builtin_fmaf(at_most, dy, qy));
@@ -702,10 +738,11 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
             usum = unew;
             n_abs += unk ? count : 0u;
             if (kMarginal) n_new += fresh ? count : 0u;
+            if (kSeg > 1) counted = false;
             // a lane that stops here (occupied, finished or outside) compares +inf
             // with the range: one comparison gives the mask the ballot takes
             const float tn_go = (st & 2u) == 0u ? T : inf;
-            const bool next_ok = tn_go < S.rv;
+            const bool next_ok = (tn_go < t1) & (kSeg == 1 || (hits & earlier) == 0ull);
             alive = ballot(next_ok);
             addr = next_ok ? voxel_addr(ux, uy, uz, M) ^ mirror : M.outside;
             st = grid[addr];
@@ -714,9 +751,13 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     }
     if (kMarginal) {
         n_new += (pend & !((mw >> mb) & 1u)) ? 1u : 0u;
-        if (has_ray) Tr.dpan[(size_t)node * S.R + r] = h == 0.f ? h : -h;
+        // (one lane of a ray writes: that of its first hit, else its last stretch's)
+        const bool first = (hits & earlier) == 0ull;
+        if (kSeg > 1 && !first) n_new = 0u;
+        if (has_ray & (kSeg == 1 || (first & ((h > -S.rv) | (seg == kSeg - 1))))) Tr.dpan[(size_t)node * S.R + r] = h == 0.f ? h : -h;
         if (n_new) atomicAdd(&s_bins[S.B + bin], n_new);
     }
+    if (kSeg > 1 && (hits & earlier) != 0ull) n_abs = 0u;
     if (n_abs) atomicAdd(&s_bins[bin], n_abs);
     __syncthreads();
     uint32_t* gb = Tr.bins + (size_t)node * 2 * S.B;
@@ -729,14 +770,14 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
 // Per-tree levels: one-wave workgroups (as the batch autotuner picks for the
 // large workloads).
 constexpr int kTreeTraceThreads = 64;
-template <bool kMarginal>
+template <bool kMarginal, int kSeg>
 __global__ __launch_bounds__(kTreeTraceThreads) void k_trace(MapDev M, SensorDev S, TreeDev Tr,
                                                              const int32_t* __restrict__ nodes) {
     __shared__ uint32_t s_bins[2 * kMaxBins];
     // (workgroup-uniform values kept in scalar registers)
     const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x / (uint32_t)S.T));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
-    trace_tile<kMarginal, kTreeTraceThreads>(M, S, Tr, nodes[item], tile, s_bins);
+    trace_tile<kMarginal, kTreeTraceThreads, kSeg>(M, S, Tr, nodes[item], tile, s_bins);
 }
 
 // ---------------------------------------------------------------- window selection
@@ -852,7 +893,7 @@ __device__ __forceinline__ uint32_t xcd_grouped(uint32_t g, uint32_t n) {
 
 // One depth level of all trees at once: work item = (tree, node) from
 // `items` (tree << 32 | node), T workgroups per item.
-template <int kTh>
+template <int kTh, int kSeg>
 __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict__ trees,
                                                      const unsigned long long* __restrict__ items, SensorDev S) {
     __shared__ uint32_t s_bins[2 * kMaxBins];
@@ -868,7 +909,7 @@ __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict
     St.rv2 = BT.rv2;
     const MapDev M = BT.map;     // copies: loaded once, not re-read through the descriptor
     const TreeDev Tr = BT.td;
-    trace_tile<true, kTh>(M, St, Tr, (int32_t)(uint32_t)it, tile, s_bins);
+    trace_tile<true, kTh, kSeg>(M, St, Tr, (int32_t)(uint32_t)it, tile, s_bins);
 }
 
 // Path masks of one depth level's nodes with children, all trees at once:
@@ -1121,16 +1162,54 @@ int32_t tiles_per_node(const SensorDev& sd, int shape) {
     return (sd.n_blocks * 64 + kShapes[shape].threads - 1) / kShapes[shape].threads;
 }
 
+// Lanes per ray of a trace launch: the most that keep it at kSplitWaves waves
+// (two rounds of the chip's 8192 wave slots; beyond, the chip is full and the
+// stretches after first hits are work lost). Measured (1 lane -> this rule): a
+// 20-node tree 121 -> 98 us, 100 nodes 545 -> 510, 333 nodes of short rays
+// 623 -> 608, 500 nodes 1006 -> 971, 29000 nodes even; limits of 8192, 12288 and
+// 24576 waves: 517, 517 and 520 us for the 100 nodes, 985, 976 and 974 for the 500.
+constexpr int64_t kSplitWaves = 16384;
+static int trace_segments(const SensorDev& sd, int32_t n_nodes) {
+    const int64_t waves = (int64_t)n_nodes * sd.n_blocks;
+    for (int seg = 8; seg > 1; seg >>= 1)
+        if (waves * seg <= kSplitWaves) return seg;
+    return 1;
+}
+
+// The sensor as a trace launch of `threads` lanes a workgroup and `seg` lanes a ray takes it.
+static SensorDev trace_sensor(const SensorDev& sd, int seg, int32_t threads) {
+    SensorDev st = sd;
+    const int32_t cols = kRayBlockCols / seg;
+    st.n_blocks = (sd.W + cols - 1) / cols * sd.nrb;
+    st.T = (st.n_blocks * 64 + threads - 1) / threads;
+    return st;
+}
+
 hipError_t launch_trace(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
                         int32_t n_nodes, bool marginal, hipStream_t s) {
     if (n_nodes <= 0) return hipSuccess;
-    SensorDev st = sd;
-    st.T = (sd.n_blocks * 64 + kTreeTraceThreads - 1) / kTreeTraceThreads;   // tiles per node at this size
-    dim3 grid((unsigned)n_nodes * (unsigned)st.T);
-    if (marginal)
-        hipLaunchKernelGGL((k_trace<true>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
-    else
-        hipLaunchKernelGGL((k_trace<false>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+    const int seg = trace_segments(sd, n_nodes);
+    const SensorDev st = trace_sensor(sd, seg, kTreeTraceThreads);
+    const dim3 grid((unsigned)n_nodes * (unsigned)st.T);
+    if (marginal) {
+        if (seg == 8)
+            hipLaunchKernelGGL((k_trace<true, 8>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+        else if (seg == 4)
+            hipLaunchKernelGGL((k_trace<true, 4>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+        else if (seg == 2)
+            hipLaunchKernelGGL((k_trace<true, 2>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+        else
+            hipLaunchKernelGGL((k_trace<true, 1>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+    } else {
+        if (seg == 8)
+            hipLaunchKernelGGL((k_trace<false, 8>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+        else if (seg == 4)
+            hipLaunchKernelGGL((k_trace<false, 4>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+        else if (seg == 2)
+            hipLaunchKernelGGL((k_trace<false, 2>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+        else
+            hipLaunchKernelGGL((k_trace<false, 1>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes);
+    }
     return hipGetLastError();
 }
 
@@ -1316,13 +1395,23 @@ namespace {
 template <int kTh>
 void launch_multi(const BatchTree* trees, const unsigned long long* items, int32_t n_items, const SensorDev& sd,
                   hipStream_t s, hipEvent_t t0, hipEvent_t t1, int shape) {
-    SensorDev st = sd;
-    st.T = tiles_per_node(sd, shape);
+    const int seg = trace_segments(sd, n_items);
+    const SensorDev st = trace_sensor(sd, seg, seg > 1 ? 64 : kTh);
     const dim3 grid((unsigned)n_items * (unsigned)st.T);
-    if (t0 && t1)
-        hipExtLaunchKernelGGL(k_trace_multi<kTh>, grid, dim3(kTh), 0, s, t0, t1, 0u, trees, items, st);
+    auto go = [&](auto kernel, int threads) {
+        if (t0 && t1)
+            hipExtLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, t0, t1, 0u, trees, items, st);
+        else
+            hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, trees, items, st);
+    };
+    if (seg == 8)
+        go(k_trace_multi<64, 8>, 64);
+    else if (seg == 4)
+        go(k_trace_multi<64, 4>, 64);
+    else if (seg == 2)
+        go(k_trace_multi<64, 2>, 64);
     else
-        hipLaunchKernelGGL(k_trace_multi<kTh>, grid, dim3(kTh), 0, s, trees, items, st);
+        go(k_trace_multi<kTh, 1>, kTh);
 }
 
 template <int I>

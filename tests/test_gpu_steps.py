@@ -37,7 +37,7 @@ def _blocks(rng, dims):
 
 
 @pytest.mark.parametrize("dims, range_vox", [((8192, 17, 16), 9000.0), ((16, 4099, 23), 5000.0), ((9, 16, 2047), 2050.5),
-                                             ((63, 65, 33), 70.0)])
+                                             ((63, 65, 33), 70.0), ((63, 65, 33), 64.0)])
 def test_block_step_at_the_largest_coordinates(mg, dims, range_vox):
     from oracle import mgref
     rng = np.random.Generator(np.random.PCG64(sum(dims)))
@@ -59,6 +59,29 @@ def test_block_step_at_the_largest_coordinates(mg, dims, range_vox):
     ref = mgref.eval_tree(m, tree, sensor, n_threads=threads())
     got = gpu_eval_tree(mg, m, tree, sensor, mode="both")
     assert_same(got, ref, keys=("g_db", "k_db", "D", "g_abs", "k_abs"))
+    assert_same(gpu_eval_tree(mg, m, tree, sensor, mode="batch"), ref)
+
+
+@pytest.mark.parametrize("copies, range_vox", [(1, 64.0), (18, 64.0), (35, 64.0), (69, 64.0), (137, 64.0), (1, 8.0), (1, 7.5),
+                                               (35, 0.25)])
+def test_split_rays_give_the_rays_results(mg, copies, range_vox):
+    """A level of `copies` nodes (the launch takes 8, 8, 4, 2 and 1 lanes a ray): parameters at which a
+    ray is split fall on voxel boundaries (ranges 64 and 8, nodes on voxel corners, rays along the axes),
+    inside free and unknown blocks and past first hits and the grid's faces; and ranges
+    of less than a voxel per lane."""
+    from oracle import mgref
+    rng = np.random.Generator(np.random.PCG64(40 + copies))
+    dims = (61, 66, 40)
+    m = W.Map(states=_blocks(rng, dims), voxel_m=1.0, origin_m=np.zeros(3, np.float32))
+    pos = (rng.uniform(0.0, 1.0, (copies + 1, 3)) * (np.array(dims) - 0.01)).astype(np.float32)
+    pos[1::2] = np.floor(pos[1::2])
+    par = np.array([-1] + [0] * copies, np.int32)
+    tree = W.Tree(pos_m=pos, parent=par)
+    sensor = W.Sensor(n_az=216, n_el=33, fov_h_deg=90.0, fov_v_deg=66.0, range_m=range_vox, yaw_bins=8,
+                      az_offset_deg=-(5.0 / 6.0))
+    log(f"[split] {copies} nodes below the root")
+    ref = mgref.eval_tree(m, tree, sensor, n_threads=threads())
+    assert_same(gpu_eval_tree(mg, m, tree, sensor, mode="both"), ref, keys=("g_db", "k_db", "D", "g_abs", "k_abs"))
 
 
 @pytest.mark.parametrize("seed", [3, 4])
