@@ -669,7 +669,7 @@ int prepare_tree(mg_map map, const float* pos_m, const int32_t* parent, int32_t 
     H->o_c0 = take(sizeof(int32_t) * n);
     H->o_g = take(sizeof(uint32_t) * n);
     H->o_y = take(sizeof(int32_t) * n);
-    H->o_bins = take(sizeof(uint32_t) * 2 * sensor->yaw_bins * (size_t)n);
+    H->o_bins = take(sizeof(uint32_t) * sensor->yaw_bins * (size_t)n);
     H->o_dpan = take(sizeof(float) * R * (size_t)n);
     H->o_ms = take(sizeof(int32_t) * n);
     H->o_mn = take(sizeof(int32_t) * std::max<size_t>(H->mask_nodes.size(), 1));
@@ -820,11 +820,11 @@ int eval_levels(mg_tree t, hipStream_t s, uint32_t* gain, int32_t* yaw, float* d
                 int32_t* host_yaw, int32_t anc_cap = kMaxAnc) {
     TreeDev td = t->dev;
     td.anc_cap = anc_cap;
-    HIP_TRY(launch_zero_u32(td.bins, (size_t)2 * t->sd.B * t->n, s));
+    HIP_TRY(launch_zero_u32(td.bins, (size_t)t->sd.B * t->n, s));
     for (int32_t d = 0; d < t->levels; ++d) {
         const int32_t b = t->level_ptr[d], cnt = t->level_ptr[d + 1] - b;
         const int32_t* nodes = td.level_nodes + b;
-        HIP_TRY(launch_trace(t->map->dev, t->sd, td, nodes, cnt, true, s));
+        HIP_TRY(launch_trace(t->map->dev, t->sd, td, nodes, cnt, true, depth != nullptr, s));
         HIP_TRY(launch_finish(t->sd, td, nodes, cnt, true, gain, yaw, s));
         const int32_t mb = t->mask_level_ptr[d], mcnt = t->mask_level_ptr[d + 1] - mb;
         HIP_TRY(launch_mask_build(t->map->dev, t->sd, td, td.mask_nodes + mb, mcnt, s));
@@ -874,8 +874,8 @@ extern "C" int mg_eval_absolute(mg_tree t, void* hip_stream, uint32_t* gain, int
     int rc = check_device(t);
     if (rc != MG_OK) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
-    HIP_TRY(launch_zero_u32(t->dev.bins, (size_t)2 * t->sd.B * t->n, s));
-    HIP_TRY(launch_trace(t->map->dev, t->sd, t->dev, t->dev.level_nodes, t->n, false, s));
+    HIP_TRY(launch_zero_u32(t->dev.bins, (size_t)t->sd.B * t->n, s));
+    HIP_TRY(launch_trace(t->map->dev, t->sd, t->dev, t->dev.level_nodes, t->n, false, false, s));
     HIP_TRY(launch_finish(t->sd, t->dev, t->dev.level_nodes, t->n, false, gain, yaw_bin, s));
     return MG_OK;
 }

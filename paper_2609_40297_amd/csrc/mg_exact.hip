@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kXThreads) void k_exact_bins(MapDev M, SensorDev S,
         if (f.n) atomicAdd(&s_bins[S.bin_of_col[r / S.H]], f.n);
     }
     __syncthreads();
-    uint32_t* gb = Tr.bins + (size_t)node * 2 * S.B + S.B;
+    uint32_t* gb = Tr.bins + (size_t)node * S.B;
     for (int32_t i = threadIdx.x; i < S.B; i += kXThreads)
         if (s_bins[i]) atomicAdd(&gb[i], s_bins[i]);
 }
@@ -377,8 +377,8 @@ extern "C" int mg_eval_exact_marginal(mg_tree t, void* hip_stream, uint32_t* gai
     std::lock_guard<std::mutex> lk(g_mu);
     State& st = g_state[t];
     // 1. bound |I(n)| by the absolute gain (the largest window's unknown incidences)
-    e = launch_zero_u32(Tr.bins, (size_t)2 * S.B * n, s);
-    if (e == hipSuccess) e = launch_trace(*v.map, S, Tr, Tr.level_nodes, n, false, s);
+    e = launch_zero_u32(Tr.bins, (size_t)S.B * n, s);
+    if (e == hipSuccess) e = launch_trace(*v.map, S, Tr, Tr.level_nodes, n, false, false, s);
     if (e == hipSuccess) e = launch_finish(S, Tr, Tr.level_nodes, n, false, v.scratch_gain, v.scratch_yaw, s);
     std::vector<uint32_t> bound(n);
     if (e == hipSuccess) e = hipMemcpyAsync(bound.data(), v.scratch_gain, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s);
@@ -388,7 +388,7 @@ extern "C" int mg_eval_exact_marginal(mg_tree t, void* hip_stream, uint32_t* gai
     rc = setup_tables(st, n, bound.data(), s, &T);
     if (rc != MG_OK) return rc;
     // 2. level by level: new incidences per bin, window, then the node's set at that window
-    e = launch_zero_u32(Tr.bins, (size_t)2 * S.B * n, s);
+    e = launch_zero_u32(Tr.bins, (size_t)S.B * n, s);
     const int32_t tiles_all = (S.R + kXThreads - 1) / kXThreads;
     const int32_t tiles_win = (S.WB * S.H + kXThreads - 1) / kXThreads;
     for (int32_t d = 0; d < v.levels && e == hipSuccess; ++d) {

@@ -258,7 +258,7 @@ struct TreeDev {
     const int32_t* level_nodes;// [n] nodes sorted by depth
     const int32_t* child_ptr;  // [n+1]
     const int32_t* child_ids;
-    uint32_t* bins;            // [n][2][B]: absolute, then marginal
+    uint32_t* bins;            // [n][B]: the evaluation's counts (absolute, or marginal)
     float* dpan;               // [n][R]
     int32_t* c0;               // [n]
     uint32_t* masks;           // [nodes with children][mask_words]
@@ -305,7 +305,7 @@ hipError_t launch_brick_flags(const MapDev& m, hipStream_t s);
 // The 16x16x16 blocks alone (after a conversion that took the bricks' summaries itself).
 hipError_t launch_blocks16(const MapDev& m, hipStream_t s);
 hipError_t launch_trace(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
-                        int32_t n_nodes, bool marginal, hipStream_t s);
+                        int32_t n_nodes, bool marginal, bool depth, hipStream_t s);   // depth: keep every node's first hits
 // Path masks of the listed nodes (all with children), after their windows are chosen.
 hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
                              int32_t n_nodes, hipStream_t s);

@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kIvlThreads) void k_ivl_trace(MapDev M, SensorDev S
                                                            const int32_t* __restrict__ yaw, int32_t tiles,
                                                            int32_t cap) {
     __shared__ Anc s_anc[kMaxAnc];
-    __shared__ uint32_t s_bins[2 * kMaxBins];
+    __shared__ uint32_t s_bins[kMaxBins];
     const int32_t tid = threadIdx.x;
     const int32_t node = nodes[blockIdx.x / tiles];
     const int32_t tile = blockIdx.x % tiles;
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kIvlThreads) void k_ivl_trace(MapDev M, SensorDev S
         A.pad[0] = A.pad[1] = 0u;
         s_anc[k] = A;
     }
-    for (int32_t i = tid; i < 2 * S.B; i += kIvlThreads) s_bins[i] = 0u;
+    for (int32_t i = tid; i < S.B; i += kIvlThreads) s_bins[i] = 0u;
     __syncthreads();
 
     const int32_t r = tile * kIvlThreads + tid;
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kIvlThreads) void k_ivl_trace(MapDev M, SensorDev S
         int32_t ix = ix0, iy = iy0, iz = iz0, bx = bx0, by = by0, bz = bz0;
         float tx = tx0, ty = ty0, tz = tz0;
         float t = 0.0f;
-        uint32_t n_abs = 0, n_marg = 0;
+        uint32_t n_marg = 0;
         int32_t ptr = 0;
         for (;;) {
             if (ix < 0 || ix >= M.nx || iy < 0 || iy >= M.ny || iz < 0 || iz >= M.nz) break;
@@ -335,7 +335,6 @@ __global__ __launch_bounds__(kIvlThreads) void k_ivl_trace(MapDev M, SensorDev S
             const int ax = (tx <= ty && tx <= tz) ? 0 : (ty <= tz ? 1 : 2);
             const float tn = ax == 0 ? tx : (ax == 1 ? ty : tz);
             if (is_unknown(st)) {
-                ++n_abs;
                 const float tex = tn < S.rv ? tn : S.rv;
                 const float tm = 0.5f * (t + tex);
                 while (tm >= U.tcut) {               // move the window past the cut
@@ -365,12 +364,11 @@ __global__ __launch_bounds__(kIvlThreads) void k_ivl_trace(MapDev M, SensorDev S
             }
         }
         const int32_t bin = S.bin_of_col[r / S.H];
-        if (n_abs) atomicAdd(&s_bins[bin], n_abs);
-        if (n_marg) atomicAdd(&s_bins[S.B + bin], n_marg);
+        if (n_marg) atomicAdd(&s_bins[bin], n_marg);
     }
     __syncthreads();
-    uint32_t* gb = Tr.bins + (size_t)node * 2 * S.B;
-    for (int32_t i = tid; i < 2 * S.B; i += kIvlThreads) {
+    uint32_t* gb = Tr.bins + (size_t)node * S.B;
+    for (int32_t i = tid; i < S.B; i += kIvlThreads) {
         const uint32_t v = s_bins[i];
         if (v) atomicAdd(&gb[i], v);
     }
@@ -623,7 +621,7 @@ extern "C" int mg_eval_interval(mg_tree t, void* hip_stream, int32_t wd, int32_t
     }
     const SensorDev& S = *v.sd;
     const TreeDev& Tr = *v.td;
-    e = launch_zero_u32(Tr.bins, (size_t)2 * S.B * v.n, s);
+    e = launch_zero_u32(Tr.bins, (size_t)S.B * v.n, s);
     if (e != hipSuccess) return fail_hip(e, "interval bins");
     const int32_t tiles = (S.R + kIvlThreads - 1) / kIvlThreads;
     const int32_t rtiles = (int32_t)((npx + kIvlThreads - 1) / kIvlThreads);

@@ -336,7 +336,7 @@ int mg_server_s::step() {
         r->level = 0;
         r->levels = v.levels;
         r->state = 1;
-        hipError_t e = launch_zero_u32(v.td->bins, (size_t)2 * v.sd->B * v.n, compute);
+        hipError_t e = launch_zero_u32(v.td->bins, (size_t)v.sd->B * v.n, compute);
         if (e == hipSuccess) e = launch_zero_u32((uint32_t*)(d_status + r->slot), 1, compute);
         if (e != hipSuccess) return hip_fail(e, "server bins");
         if (r->inject != 0) {            // failed (mg_server_fail_request) while queued
