@@ -302,16 +302,17 @@ int mg_interval_config(int32_t cap);
 int mg_interval_tables(const mg_sensor* sensor, float voxel_m, int32_t wd, int32_t hd, int32_t* wh, float* intr,
                        float* pdir, float* cs);
 
-/* Exact marginal gain with voxel hash sets (eq. 2; the exact comparison of
+/* Exact marginal gain with voxel sets (eq. 2; the exact comparison of
  * Sec. V-A, there computed with hash maps on the CPU) at given windows:
  * yaw_bin DEVICE int32[n] (e.g. from mg_eval_marginal). I(n) is the set of
  * unknown voxels met by the rays of node n's window; outputs DEVICE
  * uint32[n]: x_ray = unknown incidences of those rays whose voxel is in no
  * ancestor's I (the per-incidence counterpart of the depth-buffer gain),
  * x_set = |I(n) minus the ancestors' I| (may be NULL), a_set = |I(n)| (may be
- * NULL). Synchronises hip_stream twice (windows checked on the host, tables
- * sized from a first pass) and may grow the tree's table pool (about 8 bytes
- * per unknown incidence of the windows). MG_E_INVALID for a window outside
+ * NULL). Synchronises hip_stream twice (windows checked on the host; the call
+ * returns after the work). The first call on a tree allocates its sets (a bit
+ * per map voxel for each node of its widest level, at most 1 GiB or one node's).
+ * It overwrites the tree's path masks. MG_E_INVALID for a window outside
  * [0, yaw_bins). */
 int mg_eval_exact(mg_tree tree, void* hip_stream, const int32_t* yaw_bin, uint32_t* x_ray, uint32_t* x_set,
                   uint32_t* a_set);
@@ -322,10 +323,9 @@ int mg_eval_exact(mg_tree tree, void* hip_stream, const int32_t* yaw_bin, uint32
  * incidences of its panorama rays whose voxel lies in no ancestor's set I(a)
  * (each I(a) at a's own chosen window); the best window is chosen as for the
  * other evaluations and I(n) is then built at it. gain DEVICE uint32[n],
- * yaw_bin DEVICE int32[n]. Tables are sized from an absolute pass (one host
- * synchronisation; the pool may grow, about 8 bytes per unknown incidence of
- * each node's best absolute window); the call returns after the work. It
- * overwrites the tree's bins and window starts. */
+ * yaw_bin DEVICE int32[n]. Allocates as mg_eval_exact on the first call; the
+ * call returns after the work. It overwrites the tree's bins, window starts and
+ * path masks. */
 int mg_eval_exact_marginal(mg_tree tree, void* hip_stream, uint32_t* gain, int32_t* yaw_bin);
 
 /* Absolute gain of every node (eq. 1 maximised over the yaw windows), no

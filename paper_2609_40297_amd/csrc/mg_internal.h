@@ -210,6 +210,82 @@ __device__ __forceinline__ float cross_block(int32_t edge, float4 p, float4 inv,
     return T;
 }
 
+// A ray walked by the Amanatides-Woo 3D DDA (face-crossing parameters recomputed
+// as (boundary - q) * (1/d); ties step x, then y, then z), an aligned block at a
+// time.
+//
+// Mirrored coordinates: on an axis the ray moves down, the coordinate is
+// negated (voxel index x becomes ~x, boundary b becomes -b), so every ray moves
+// up on every axis. The parameter (boundary - q) * (1/d) is the same float
+// either way (negating both factors is exact), but for the sign of a zero. A
+// voxel's byte address merges bit fields of its coordinates, so the mirroring is
+// undone by one exclusive or of the merged address.
+//
+// One step leaves the aligned block of `edge` voxels around the voxel (edge 1:
+// the voxel itself), through the face whose boundary parameter T comes first
+// (ties x, y, z), and then every axis has crossed the boundaries that come
+// before that crossing in the DDA's order: those with parameter below T, or
+// equal to T on the exit axis and the axes before it. An axis's position at T
+// is q + T d; the error of that sum is below 0.01 voxel (|q| <= 8192, T at most
+// the grid's diagonal, three roundings of T and one of the sum), so every
+// boundary but the one nearest to it lies at least 0.49 voxel away and its side
+// of T is not in doubt, and the nearest one is decided by its own parameter,
+// computed as the single step computes it. (A boundary the ray starts on or has
+// passed is never crossed again: the coordinate does not fall.) A single voxel is
+// the same step with edge 1.
+struct RayWalk {
+    int32_t mx, my, mz;      // 0, or ~0 on an axis the ray moves down
+    float qx, qy, qz;        // the node, mirrored
+    float dx, dy, dz;        // the direction's magnitudes
+    float fx, fy, fz;        // their inverses; +inf on an axis the ray does not move along: its
+                             // next boundary lies past the node, so its parameter is +inf
+    int32_t ux, uy, uz;      // the voxel, mirrored
+    uint32_t mirror;         // the address bits of the mirrored axes
+    __device__ __forceinline__ void start(float4 p, float4 d, float4 iv, const MapDev& M) {
+        const float inf = __builtin_inff();
+        mx = d.x < 0.f ? -1 : 0; my = d.y < 0.f ? -1 : 0; mz = d.z < 0.f ? -1 : 0;
+        qx = mx ? -p.x : p.x; qy = my ? -p.y : p.y; qz = mz ? -p.z : p.z;
+        dx = fabsf(d.x); dy = fabsf(d.y); dz = fabsf(d.z);
+        fx = dx != 0.f ? fabsf(iv.x) : inf; fy = dy != 0.f ? fabsf(iv.y) : inf; fz = dz != 0.f ? fabsf(iv.z) : inf;
+        ux = (int32_t)floorf(p.x) ^ mx; uy = (int32_t)floorf(p.y) ^ my; uz = (int32_t)floorf(p.z) ^ mz;
+        mirror = voxel_addr(mx, my, mz, M);
+    }
+    __device__ __forceinline__ int32_t x() const { return ux ^ mx; }
+    __device__ __forceinline__ int32_t y() const { return uy ^ my; }
+    __device__ __forceinline__ int32_t z() const { return uz ^ mz; }
+    __device__ __forceinline__ uint32_t addr(const MapDev& M) const { return voxel_addr(ux, uy, uz, M) ^ mirror; }
+    __device__ __forceinline__ bool in_grid(const MapDev& M) const {
+        return (uint32_t)x() < (uint32_t)M.nx && (uint32_t)y() < (uint32_t)M.ny && (uint32_t)z() < (uint32_t)M.nz;
+    }
+    // Crosses, from the ray's start or from where it stands, every boundary whose
+    // parameter is at most ax, ay, az on its axis, those near the parameter `at`.
+    __device__ __forceinline__ void pass(float at, float ax, float ay, float az) {
+        const float ex = __builtin_rintf(__builtin_fmaf(at, dx, qx));
+        const float ey = __builtin_rintf(__builtin_fmaf(at, dy, qy));
+        const float ez = __builtin_rintf(__builtin_fmaf(at, dz, qz));
+        ux = max(ux, (int32_t)ex - ((ex - qx) * fx <= ax ? 0 : 1));
+        uy = max(uy, (int32_t)ey - ((ey - qy) * fy <= ay ? 0 : 1));
+        uz = max(uz, (int32_t)ez - ((ez - qz) * fz <= az ? 0 : 1));
+    }
+    // Leaves the aligned block of e1 + 1 voxels a side and returns the parameter T
+    // at which it is left. Where the walk's end lies inside the block (T is not
+    // below it), only boundaries with a parameter below the end are crossed. before
+    // and most: the float below the end (> 0), as bits and as a float.
+    __device__ __forceinline__ float cross(uint32_t e1, int32_t before, float most) {
+        // the block's exit boundary and its parameter on each axis; the first one
+        const float Tx = ((float)((ux | (int32_t)e1) + 1) - qx) * fx;
+        const float Ty = ((float)((uy | (int32_t)e1) + 1) - qy) * fy;
+        const float Tz = ((float)((uz | (int32_t)e1) + 1) - qz) * fz;
+        const float Txy = fminf(Tx, Ty), T = fminf(Txy, Tz);
+        // (T >= +0; below 0 there is no parameter: a NaN, which none is at most)
+        const float at = fminf(T, most);
+        const int32_t tb = (int32_t)__float_as_uint(T) - 1;
+        const float below = __uint_as_float((uint32_t)(tb < before ? tb : before));
+        pass(at, at, Tx == T ? below : at, Txy == T ? below : at);
+        return T;
+    }
+};
+
 // Panorama ray tables and yaw-window geometry (built on the host, see mg_api).
 struct SensorDev {
     const float4* d4;          // [R] unit direction (w unused)
@@ -306,6 +382,10 @@ hipError_t launch_brick_flags(const MapDev& m, hipStream_t s);
 hipError_t launch_blocks16(const MapDev& m, hipStream_t s);
 hipError_t launch_trace(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
                         int32_t n_nodes, bool marginal, bool depth, hipStream_t s);   // depth: keep every node's first hits
+// Unknown voxels met by the rays of each listed node's window yaw[node] and not
+// in its parent's path mask, added to total[node].
+hipError_t launch_trace_window(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
+                               int32_t n_nodes, const int32_t* yaw, uint32_t* total, hipStream_t s);
 // Path masks of the listed nodes (all with children), after their windows are chosen.
 hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
                              int32_t n_nodes, hipStream_t s);

@@ -557,7 +557,7 @@ __device__ __forceinline__ void add_to_bins(uint32_t n, uint32_t bin, uint32_t* 
 #define MG_SCAN(off)                                                                               \
     if (off < kCols) {                                                                             \
         const uint32_t o = dpp<kRowShr + off>(n, 0u), b = dpp<kRowShr + off>(bin, ~0u);            \
-        n += (b == bin) & (col >= off) ? o : 0u;                                                   \
+        n += (b == bin && col >= off) ? o : 0u;                                                   \
     }
     MG_SCAN(1)
     MG_SCAN(2)
@@ -584,26 +584,9 @@ __device__ __forceinline__ void add_to_bins(uint32_t n, uint32_t bin, uint32_t* 
 // was requested, so both loads have a step of work to hide behind. Ends with
 // each wave's counts added to the node's bins.
 //
-// Mirrored coordinates: on an axis the ray moves down, the coordinate is
-// negated (voxel index x becomes ~x, boundary b becomes -b), so every ray moves
-// up on every axis. The parameter (boundary - q) * (1/d) is the same float
-// either way (negating both factors is exact). A voxel's byte address merges
-// bit fields of its coordinates, so the mirroring is undone by one exclusive or
-// of the merged address.
-//
-// One step leaves the aligned block of `edge` voxels around the voxel (edge 1:
-// the voxel itself), through the face whose boundary parameter T comes first
-// (ties x, y, z), and then every axis has crossed the boundaries that come
-// before that crossing in the DDA's order: those with parameter below T, or
-// equal to T on the exit axis and the axes before it. An axis's position at T
-// is q + T d; the error of that sum is below 0.01 voxel (|q| <= 8192, T at most
-// the grid's diagonal, three roundings of T and one of the sum), so every
-// boundary but the one nearest to it lies at least 0.49 voxel away and its side
-// of T is not in doubt, and the nearest one is decided by its own parameter,
-// computed as the single step computes it. (A boundary the ray starts on or has
-// passed is never crossed again: the coordinate does not fall.) One probe an
-// axis replaces the three or four of a search over the block's boundaries, and
-// a single voxel is the same step with edge 1, so a wave takes one path: this
+// Steps are RayWalk's: one exact probe an axis decides which boundaries a block
+// crossing passes, in place of the three or four of a search over the block's
+// boundaries, and a single voxel takes the same path, so a wave does too: this
 // loop is bound by instruction issue, and by the latency of its chain where a
 // level has few nodes. Against the search: 59.8 -> 48.1 ms a batch of 4 trees of
 // 3000 nodes (720 x 120 rays, 512 x 512 x 128 grid), 2.93 -> 2.12 ms the
@@ -619,9 +602,12 @@ __device__ __forceinline__ void add_to_bins(uint32_t n, uint32_t bin, uint32_t* 
 // step finds it), whose visit the stretch before has counted, and ends as the
 // range ends; stretches after the ray's first hit count nothing, and a ray that
 // has left the grid starts its later stretches outside.
-template <bool kMarginal, int kTh, int kSeg = 1>
+//
+// kWindow walks the rays of one yaw window only (WB columns from column c0) and
+// adds their counts to *total.
+template <bool kMarginal, int kTh, int kSeg = 1, bool kWindow = false>
 __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
-                                           int32_t tile, bool keep_hits) {
+                                           int32_t tile, bool keep_hits, int32_t c0 = 0, uint32_t* total = nullptr) {
     const int32_t tid = threadIdx.x;
     const uint32_t* pmask = nullptr;     // the parent's path mask
     const uint32_t* pcode = nullptr;     // and its bricks' code words
@@ -640,25 +626,18 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     const int32_t cb = __builtin_amdgcn_readfirstlane(blk / S.nrb);
     constexpr int32_t kCols = kRayBlockCols / kSeg, kPix = 64 / kSeg;
     const int32_t seg = (tid & 63) / kPix;               // this lane's stretch of its ray
-    const int32_t c = cb * kCols + (tid & (kCols - 1));
+    const int32_t i = cb * kCols + (tid & (kCols - 1));
+    const int32_t c = kWindow ? wrap(c0 + i, S.W) : i;
     const int32_t j = (blk - cb * S.nrb) * kRayBlockRows + ((tid & (kPix - 1)) / kCols);
-    const bool has_ray = (blk < S.n_blocks) & (c < S.W) & (j < S.H);
+    const bool has_ray = (blk < S.n_blocks) & (i < (kWindow ? S.WB : S.W)) & (j < S.H);
     const int32_t r = c * S.H + j;
     const int32_t rr = has_ray ? r : 0;
-    const uint32_t bin = (uint32_t)S.bin_of_col[has_ray ? c : 0];
+    const uint32_t bin = kWindow ? 0u : (uint32_t)S.bin_of_col[has_ray ? c : 0];
     const float4 p = Tr.q4[node];
     const float4 d = S.d4[rr];
     const float4 iv = S.iv4[rr];
-    // Mirrored coordinates of the ray: 0 or ~0 per axis (the mirroring), the
-    // node, the direction and its inverse (both >= 0), and the voxel. An axis
-    // the ray does not move along has factor +inf: its next boundary lies past
-    // the node, so its parameter is +inf, and its voxel never changes.
-    const float inf = __builtin_inff();
-    const int32_t mx = d.x < 0.f ? -1 : 0, my = d.y < 0.f ? -1 : 0, mz = d.z < 0.f ? -1 : 0;
-    const float qx = mx ? -p.x : p.x, qy = my ? -p.y : p.y, qz = mz ? -p.z : p.z;
-    const float dx = fabsf(d.x), dy = fabsf(d.y), dz = fabsf(d.z);
-    const float fx = dx != 0.f ? fabsf(iv.x) : inf, fy = dy != 0.f ? fabsf(iv.y) : inf, fz = dz != 0.f ? fabsf(iv.z) : inf;
-    int32_t ux = (int32_t)floorf(p.x) ^ mx, uy = (int32_t)floorf(p.y) ^ my, uz = (int32_t)floorf(p.z) ^ mz;
+    RayWalk w;
+    w.start(p, d, iv, M);
     // the stretch's start and end parameters, and the float below its end (> 0);
     // a range of less than a voxel a stretch is left to the ray's first lane
     const bool split = kSeg > 1 && S.rv >= (float)kSeg;
@@ -670,18 +649,11 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     bool counted = false;                // the current voxel's visit is the stretch before's
     if (split && seg > 0) {
         const float most = __uint_as_float(__float_as_uint(t0) - 1u);
-        const float ex = __builtin_rintf(__builtin_fmaf(most, dx, qx));
-        const float ey = __builtin_rintf(__builtin_fmaf(most, dy, qy));
-        const float ez = __builtin_rintf(__builtin_fmaf(most, dz, qz));
-        ux = max(ux, (int32_t)ex - ((ex - qx) * fx <= most ? 0 : 1));
-        uy = max(uy, (int32_t)ey - ((ey - qy) * fy <= most ? 0 : 1));
-        uz = max(uz, (int32_t)ez - ((ez - qz) * fz <= most ? 0 : 1));
-        inside = has_ray & ((uint32_t)(ux ^ mx) < (uint32_t)M.nx) & ((uint32_t)(uy ^ my) < (uint32_t)M.ny) &
-                 ((uint32_t)(uz ^ mz) < (uint32_t)M.nz);
+        w.pass(most, most, most, most);
+        inside = has_ray & w.in_grid(M);
         counted = true;
     }
-    int32_t usum = ux + uy + uz + (counted ? 1 : 0);
-    const uint32_t mirror = voxel_addr(mx, my, mz, M);
+    int32_t usum = w.ux + w.uy + w.uz + (counted ? 1 : 0);
     // lanes holding the earlier stretches of this lane's ray, and those that hit
     constexpr uint64_t kRayLanes = kSeg == 4 ? 0x0001000100010001ull : (kSeg == 2 ? 0x0000000100000001ull : 0x0101010101010101ull);
     const uint64_t earlier = kSeg > 1 ? ((kRayLanes << (tid & (kPix - 1))) & ((1ull << (tid & 63)) - 1ull)) : 0ull;
@@ -694,7 +666,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     const gbytes_t grid = as_global(M.bricks);
     // a lane without a ray (or whose ray has left the grid) reads a padding byte
     // and is done at once
-    uint32_t addr = inside ? voxel_addr(ux, uy, uz, M) ^ mirror : M.outside;   // address of the current voxel
+    uint32_t addr = inside ? w.addr(M) : M.outside;   // address of the current voxel
     // (this first byte is read through the generic pointer and the loop's through
     // the global one, so the compiler keeps the loop's load at the end of the
     // step instead of merging the two into one load at the top of the loop)
@@ -726,7 +698,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
             if (kMarginal && pm != nullptr) {
                 fresh = false;
                 if (unk) {
-                    const int32_t x = ux ^ mx, y = uy ^ my, z = uz ^ mz;
+                    const int32_t x = w.x(), y = w.y(), z = w.z();
                     const uint32_t b = mask_brick(x, y, z, M);
                     uint32_t code = kMaskMixed;
                     // (a wholly unknown block with a uniform code is always crossed by its
@@ -755,39 +727,19 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
                     }
                 }
             }
-            // the block's exit boundary and its parameter on each axis; the first one
-            const float Tx = ((float)((ux | (int32_t)e1) + 1) - qx) * fx;
-            const float Ty = ((float)((uy | (int32_t)e1) + 1) - qy) * fy;
-            const float Tz = ((float)((uz | (int32_t)e1) + 1) - qz) * fz;
-            const float Txy = fminf(Tx, Ty), T = fminf(Txy, Tz);
-            // Boundaries crossed: parameter at most T on the exit axis and the axes
-            // before it, at most the float below T on those after it (T >= +0; below
-            // 0 there is none: a NaN, which no parameter is at most). Where the range
-            // ends inside the block, the ray visits the current voxel and one per
-            // boundary whose parameter is below the range, and ends.
-            const bool in_range = T < t1;
-            const float at_most = fminf(T, t1_most);
-            const int32_t tb = (int32_t)__float_as_uint(T) - 1;
-            const float below = __uint_as_float((uint32_t)(tb < t1_before ? tb : t1_before));
-            const float cy_at = Tx == T ? below : at_most, cz_at = Txy == T ? below : at_most;
-            const float ex = __builtin_rintf(__builtin_fmaf(at_most, dx, qx));
-            const float ey = __builtin_rintf(__builtin_fmaf(at_most, dy, qy));
-            const float ez = __builtin_rintf(__builtin_fmaf(at_most, dz, qz));
-            ux = max(ux, (int32_t)ex - ((ex - qx) * fx <= at_most ? 0 : 1));
-            uy = max(uy, (int32_t)ey - ((ey - qy) * fy <= cy_at ? 0 : 1));
-            uz = max(uz, (int32_t)ez - ((ez - qz) * fz <= cz_at ? 0 : 1));
+            const float T = w.cross(e1, t1_before, t1_most);
             // voxels of the block visited: one per boundary crossed, and the last one of a ray that ends
-            const int32_t unew = ux + uy + uz;
-            const uint32_t count = (uint32_t)(unew - usum) + (in_range ? 0u : 1u);
+            const int32_t unew = w.ux + w.uy + w.uz;
+            const uint32_t count = (uint32_t)(unew - usum) + (T < t1 ? 0u : 1u);
             usum = unew;
             n += fresh ? count : 0u;
             if (kSeg > 1) counted = false;
             // a lane that stops here (occupied, finished or outside) compares +inf
             // with the range: one comparison gives the mask the ballot takes
-            const float tn_go = (st & 2u) == 0u ? T : inf;
+            const float tn_go = (st & 2u) == 0u ? T : __builtin_inff();
             const bool next_ok = (tn_go < t1) & (kSeg == 1 || (hits & earlier) == 0ull);
             alive = ballot(next_ok);
-            addr = next_ok ? voxel_addr(ux, uy, uz, M) ^ mirror : M.outside;
+            addr = next_ok ? w.addr(M) : M.outside;
             st = grid[addr];
             t = T;
         } while (alive);
@@ -800,7 +752,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
         if (keep_hits & has_ray & first & (kSeg == 1 || (h > -S.rv) | (seg == kSeg - 1)))
             Tr.dpan[(size_t)node * S.R + r] = h == 0.f ? h : -h;
     }
-    add_to_bins<kCols>(first ? n : 0u, bin, Tr.bins + (size_t)node * S.B);
+    add_to_bins<kCols>(first ? n : 0u, bin, kWindow ? total : Tr.bins + (size_t)node * S.B);
 }
 
 // Per-tree levels: one-wave workgroups (as the batch autotuner picks for the
@@ -814,6 +766,18 @@ __global__ __launch_bounds__(kTreeTraceThreads) void k_trace(MapDev M, SensorDev
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
     const int32_t node = nodes[item];
     trace_tile<kMarginal, kTreeTraceThreads, kSeg>(M, S, Tr, node, tile, depth || Tr.mask_slot[node] >= 0);
+}
+
+// The rays of each node's window yaw[node], counted into total[node].
+template <int kSeg>
+__global__ __launch_bounds__(kTreeTraceThreads) void k_trace_window(MapDev M, SensorDev S, TreeDev Tr,
+                                                                    const int32_t* __restrict__ nodes,
+                                                                    const int32_t* __restrict__ yaw,
+                                                                    uint32_t* __restrict__ total) {
+    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x / (uint32_t)S.T));
+    const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
+    const int32_t node = nodes[item];
+    trace_tile<true, kTreeTraceThreads, kSeg, true>(M, S, Tr, node, tile, false, S.c0_of_win[yaw[node]], total + node);
 }
 
 // ---------------------------------------------------------------- window selection
@@ -1200,18 +1164,19 @@ size_t lds_limit() {
 // 623 -> 608, 500 nodes 1006 -> 971, 29000 nodes even; limits of 8192, 12288 and
 // 24576 waves: 517, 517 and 520 us for the 100 nodes, 985, 976 and 974 for the 500.
 constexpr int64_t kSplitWaves = 16384;
-static int trace_segments(const SensorDev& sd, int32_t n_nodes) {
-    const int64_t waves = (int64_t)n_nodes * sd.n_blocks;
+static int trace_segments(const SensorDev& sd, int32_t n_nodes, int32_t columns) {
+    const int64_t waves = (int64_t)n_nodes * ((columns + kRayBlockCols - 1) / kRayBlockCols) * sd.nrb;
     for (int seg = 8; seg > 1; seg >>= 1)
         if (waves * seg <= kSplitWaves) return seg;
     return 1;
 }
 
-// The sensor as a trace launch of `threads` lanes a workgroup and `seg` lanes a ray takes it.
-static SensorDev trace_sensor(const SensorDev& sd, int seg, int32_t threads) {
+// The sensor as a trace launch over `columns` columns takes it, with `threads`
+// lanes a workgroup and `seg` lanes a ray.
+static SensorDev trace_sensor(const SensorDev& sd, int seg, int32_t threads, int32_t columns) {
     SensorDev st = sd;
     const int32_t cols = kRayBlockCols / seg;
-    st.n_blocks = (sd.W + cols - 1) / cols * sd.nrb;
+    st.n_blocks = (columns + cols - 1) / cols * sd.nrb;
     st.T = (st.n_blocks * 64 + threads - 1) / threads;
     return st;
 }
@@ -1223,8 +1188,8 @@ int32_t tiles_per_node(const SensorDev& sd, int shape) {
 hipError_t launch_trace(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
                         int32_t n_nodes, bool marginal, bool depth, hipStream_t s) {
     if (n_nodes <= 0) return hipSuccess;
-    const int seg = trace_segments(sd, n_nodes);
-    const SensorDev st = trace_sensor(sd, seg, kTreeTraceThreads);
+    const int seg = trace_segments(sd, n_nodes, sd.W);
+    const SensorDev st = trace_sensor(sd, seg, kTreeTraceThreads, sd.W);
     const dim3 grid((unsigned)n_nodes * (unsigned)st.T);
     if (marginal) {
         if (seg == 8)
@@ -1245,6 +1210,24 @@ hipError_t launch_trace(const MapDev& m, const SensorDev& sd, const TreeDev& td,
         else
             hipLaunchKernelGGL((k_trace<false, 1>), grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes, depth);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_trace_window(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
+                               int32_t n_nodes, const int32_t* yaw, uint32_t* total, hipStream_t s) {
+    if (n_nodes <= 0) return hipSuccess;
+    const int seg = trace_segments(sd, n_nodes, sd.WB);
+    const SensorDev st = trace_sensor(sd, seg, kTreeTraceThreads, sd.WB);
+    const dim3 grid((unsigned)n_nodes * (unsigned)st.T);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes, yaw, total); };
+    if (seg == 8)
+        go(k_trace_window<8>);
+    else if (seg == 4)
+        go(k_trace_window<4>);
+    else if (seg == 2)
+        go(k_trace_window<2>);
+    else
+        go(k_trace_window<1>);
     return hipGetLastError();
 }
 
@@ -1430,8 +1413,8 @@ namespace {
 template <int kTh>
 void launch_multi(const BatchTree* trees, const unsigned long long* items, int32_t n_items, const SensorDev& sd,
                   hipStream_t s, hipEvent_t t0, hipEvent_t t1, int shape) {
-    const int seg = trace_segments(sd, n_items);
-    const SensorDev st = trace_sensor(sd, seg, seg > 1 ? 64 : kTh);
+    const int seg = trace_segments(sd, n_items, sd.W);
+    const SensorDev st = trace_sensor(sd, seg, seg > 1 ? 64 : kTh, sd.W);
     const dim3 grid((unsigned)n_items * (unsigned)st.T);
     auto go = [&](auto kernel, int threads) {
         if (t0 && t1)

@@ -150,3 +150,23 @@ def test_exact_own_yaw_step_sampled(mg, orc):
     dep = t.depth()
     mask = orc.ancestor_closure(t.parent, np.flatnonzero(dep == dep.max())[:2])
     _check_own_yaw(mg, orc, w.map, t, w.sensor, "step", mask=mask)
+
+
+@pytest.mark.parametrize("fan, deep", [(300, 3), (1, 2)])
+def test_exact_levels_wider_than_the_set_pool(mg, orc, fan, deep):
+    """A level of more nodes than sets are held at once (1 GiB of a bit per voxel of this map: 256), and a
+    pool of one node; nodes on block boundaries, wholly unknown and mixed blocks, with the union's codes
+    read by the levels below."""
+    rng = np.random.Generator(np.random.PCG64(fan))
+    dims = (512, 512, 128)
+    st = np.zeros(dims[::-1], np.uint8)
+    st[32:96, 200:330, 190:340] = W.FREE
+    st[rng.integers(30, 98, 4000), rng.integers(198, 332, 4000), rng.integers(188, 342, 4000)] = W.UNK
+    st[rng.integers(30, 98, 800), rng.integers(198, 332, 800), rng.integers(188, 342, 800)] = W.OCC
+    m = W.Map(states=st, voxel_m=1.0, origin_m=np.zeros(3, np.float32))
+    n = 1 + fan + 4 * deep
+    par = np.array([-1] + [0] * fan + [1 + fan + k - 4 if k >= 4 else 1 + k % fan for k in range(4 * deep)], np.int32)
+    pos = rng.uniform([200, 210, 40], [330, 320, 90], (n, 3)).astype(np.float32)
+    pos[::3] = np.floor(pos[::3])
+    sen = W.Sensor(n_az=48, n_el=9, fov_h_deg=90.0, fov_v_deg=60.0, range_m=70.0, yaw_bins=12)
+    _check(mg, orc, m, W.Tree(pos_m=pos, parent=par), sen, f"wide level {fan}")
