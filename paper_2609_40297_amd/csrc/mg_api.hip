@@ -14,6 +14,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -201,7 +202,9 @@ void build_tables(const mg_sensor* s, int32_t w, int32_t wb, HostTables* T) {
 }
 
 // Device copy of one sensor's tables, shared by all trees with that sensor on
-// that device (reference counted).
+// that device (reference counted). Tables that the last tree has dropped stay
+// for the next one (a replan's tree is usually alone), up to kIdleSensors bytes
+// of them per device, until the device's last map is destroyed.
 struct SensorRes {
     SensorKey key;
     int refs = 0;
@@ -214,6 +217,7 @@ struct SensorRes {
     size_t bytes = 0;
 };
 
+constexpr size_t kIdleSensors = size_t(64) << 20;
 std::mutex g_sensor_mu;
 std::map<SensorKey, SensorRes*> g_sensors;
 
@@ -281,12 +285,24 @@ int acquire_sensor(const mg_sensor* s, hipStream_t stream, SensorRes** out) {
     return MG_OK;
 }
 
+// Frees the device's tables without a tree, those past `keep` bytes (g_sensor_mu held).
+void trim_sensors(int device, size_t keep) {
+    size_t idle = 0;
+    for (auto it = g_sensors.begin(); it != g_sensors.end();) {
+        SensorRes* r = it->second;
+        if (r->refs == 0 && r->key.device == device && idle + r->bytes > keep) {
+            it = g_sensors.erase(it);
+            free_sensor(r);
+            continue;
+        }
+        if (r->refs == 0 && r->key.device == device) idle += r->bytes;
+        ++it;
+    }
+}
+
 void release_sensor(SensorRes* r) {
     std::lock_guard<std::mutex> lk(g_sensor_mu);
-    if (--r->refs == 0) {
-        g_sensors.erase(r->key);
-        free_sensor(r);
-    }
+    if (--r->refs == 0) trim_sensors(r->key.device, kIdleSensors);
 }
 
 SensorDev sensor_dev(const SensorRes* r, float rv) {
@@ -334,6 +350,105 @@ extern "C" int mg_sensor_tables(const mg_sensor* sensor, float* dir, float* inv,
     if (c0) std::memcpy(c0, T.c0.data(), T.c0.size() * sizeof(int32_t));
     return MG_OK;
 }
+
+// ---------------------------------------------------------------- device blocks
+
+namespace {
+
+// Blocks given back by destroyed trees and plans, for the next ones: a replan
+// uploads a tree, evaluates it and drops it, and a hipMalloc and hipFree of tens
+// of megabytes, and rebuilding its sensor's tables, took longer than its host
+// work (500 nodes, 70 MB: upload 966 -> 38 us with blocks and tables kept and one
+// copy instead of ten, drop 391 -> 82 us). Per device, blocks of at most
+// kPoolBlock bytes and kPoolHeld in all, found again by their size class; the
+// pool is emptied when the device's last map is destroyed and when an allocation
+// fails.
+constexpr size_t kPoolBlock = size_t(256) << 20, kPoolHeld = size_t(512) << 20;
+struct DevicePool {
+    std::multimap<size_t, void*> blocks;     // by size class
+    std::set<void*> exact;                   // blocks in use that are smaller than their class
+    size_t held = 0;
+    int maps = 0;                            // live maps on the device
+    void drain() {
+        for (auto& b : blocks) (void)hipFree(b.second);
+        blocks.clear();
+        held = 0;
+    }
+};
+struct Pools {
+    std::mutex mu;
+    std::map<int, DevicePool> of;
+};
+// (never destroyed: plans that outlive main's end still give their blocks back)
+Pools& pools() {
+    static Pools* p = new Pools();
+    return *p;
+}
+
+// Sizes in steps of an eighth to a sixteenth of themselves, so that trees of similar size share blocks.
+size_t size_class(size_t bytes) {
+    size_t step = 4096;
+    while (step * 16 <= bytes) step *= 2;
+    return (bytes + step - 1) / step * step;
+}
+
+int count_map(int device, int delta) {
+    Pools& G = pools();
+    std::lock_guard<std::mutex> lk(G.mu);
+    DevicePool& P = G.of[device];
+    P.maps += delta;
+    if (P.maps == 0) P.drain();
+    return P.maps;
+}
+
+}  // namespace
+
+namespace mgb {
+
+hipError_t pool_get(void** block, size_t bytes, int device) {
+    const size_t cls = size_class(bytes);
+    Pools& G = pools();
+    std::lock_guard<std::mutex> lk(G.mu);
+    DevicePool& P = G.of[device];
+    if (cls > kPoolBlock) return hipMalloc(block, bytes);
+    auto it = P.blocks.find(cls);
+    if (it != P.blocks.end()) {
+        *block = it->second;
+        P.held -= cls;
+        P.blocks.erase(it);
+        return hipSuccess;
+    }
+    hipError_t e = hipMalloc(block, cls);
+    if (e == hipErrorOutOfMemory) {              // without the pool's blocks and the class's rounding
+        (void)hipGetLastError();
+        P.drain();
+        e = hipMalloc(block, bytes);
+        if (e == hipSuccess) P.exact.insert(*block);
+    }
+    return e;
+}
+
+void pool_put(void* block, size_t bytes, int device) {
+    const size_t cls = size_class(bytes);
+    Pools& G = pools();
+    std::lock_guard<std::mutex> lk(G.mu);
+    DevicePool& P = G.of[device];
+    if (P.exact.erase(block) != 0 || cls > kPoolBlock || P.held + cls > kPoolHeld || P.maps == 0) {
+        (void)hipFree(block);
+        return;
+    }
+    P.blocks.emplace(cls, block);
+    P.held += cls;
+}
+
+void sync_device(int device) {
+    int dev = device;
+    const bool other = hipGetDevice(&dev) == hipSuccess && dev != device && hipSetDevice(device) == hipSuccess;
+    (void)hipDeviceSynchronize();
+    if (other) (void)hipSetDevice(dev);
+}
+
+}  // namespace mgb
 
 // ---------------------------------------------------------------- maps
 
@@ -408,6 +523,12 @@ int map_alloc(int32_t nx, int32_t ny, int32_t nz, float voxel_m, const float ori
     return MG_OK;
 }
 
+// A finished map is handed to the caller.
+mg_map publish(std::unique_ptr<mg_map_s>& m) {
+    count_map(m->device, 1);
+    return m.release();
+}
+
 }  // namespace
 
 extern "C" int mg_map_create(const uint8_t* states, int32_t nx, int32_t ny, int32_t nz, float voxel_m,
@@ -435,7 +556,7 @@ extern "C" int mg_map_create(const uint8_t* states, int32_t nx, int32_t ny, int3
         (void)hipFree(m->bricks);
         return fail(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, "map upload: %s", hipGetErrorString(e));
     }
-    *out = m.release();
+    *out = publish(m);
     return MG_OK;
 }
 
@@ -461,7 +582,7 @@ extern "C" int mg_map_create_tsdf(const float* distance, const float* weight, in
         (void)hipFree(m->bricks);
         return fail(MG_E_DEVICE, "TSDF conversion: %s", hipGetErrorString(e));
     }
-    *out = m.release();
+    *out = publish(m);
     return MG_OK;
 }
 
@@ -529,6 +650,10 @@ extern "C" int mg_map_destroy(mg_map map) {
     if (map->trees.load() != 0)
         return fail(MG_E_BUSY, "%d trees or server requests still use this map", map->trees.load());
     (void)hipFree(map->bricks);
+    if (count_map(map->device, -1) == 0) {
+        std::lock_guard<std::mutex> lk(g_sensor_mu);
+        trim_sensors(map->device, 0);
+    }
     delete map;
     return MG_OK;
 }
@@ -568,8 +693,9 @@ struct HostTree {
     // path masks: slot per node (-1 for leaves), nodes with children by level
     std::vector<int32_t> mask_slot, mask_level_ptr, mask_nodes;
     // device block layout
-    size_t o_q4 = 0, o_pm = 0, o_ap = 0, o_ai = 0, o_ln = 0, o_cp = 0, o_ci = 0, o_c0 = 0, o_g = 0, o_y = 0, o_bins = 0,
-           o_dpan = 0, o_ms = 0, o_mn = 0, o_masks = 0, o_tm = 0, o_mc = 0, total = 0;
+    // (the uploaded arrays first, up_bytes in all)
+    size_t o_q4 = 0, o_pm = 0, o_ap = 0, o_ai = 0, o_ln = 0, o_c0 = 0, o_ms = 0, o_mn = 0, up_bytes = 0, o_g = 0, o_y = 0,
+           o_bins = 0, o_dpan = 0, o_masks = 0, o_tm = 0, o_mc = 0, total = 0;
 };
 
 }  // namespace mgb
@@ -655,8 +781,8 @@ int prepare_tree(mg_map map, const float* pos_m, const int32_t* parent, int32_t 
     H->n_masks = (int32_t)H->mask_nodes.size();
     const size_t R = (size_t)sensor->n_az * sensor->n_el;
     if (R * (size_t)n >= (1ull << 32)) return fail(MG_E_UNSUPPORTED, "nodes x rays = %zu exceeds 2^32 per tree", R * (size_t)n);
-    // one device block: q4 | pm | anc_ptr | anc_ids | level_nodes | child_ptr | child_ids | c0 | gain | yaw | bins |
-    // dpan | mask_slot | mask_nodes | masks | tile maxima | mask brick codes
+    // one device block: q4 | pm | anc_ptr | anc_ids | level_nodes | c0 | mask_slot | mask_nodes | gain | yaw | bins |
+    // dpan | masks | tile maxima | mask brick codes
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     H->o_q4 = take(sizeof(float4) * n);
@@ -664,15 +790,14 @@ int prepare_tree(mg_map map, const float* pos_m, const int32_t* parent, int32_t 
     H->o_ap = take(sizeof(int32_t) * (n + 1));
     H->o_ai = take(sizeof(int32_t) * H->anc_ids.size());
     H->o_ln = take(sizeof(int32_t) * n);
-    H->o_cp = take(sizeof(int32_t) * (n + 1));
-    H->o_ci = take(sizeof(int32_t) * n);
     H->o_c0 = take(sizeof(int32_t) * n);
+    H->o_ms = take(sizeof(int32_t) * n);
+    H->o_mn = take(sizeof(int32_t) * std::max<size_t>(H->mask_nodes.size(), 1));
+    H->up_bytes = off;
     H->o_g = take(sizeof(uint32_t) * n);
     H->o_y = take(sizeof(int32_t) * n);
     H->o_bins = take(sizeof(uint32_t) * sensor->yaw_bins * (size_t)n);
     H->o_dpan = take(sizeof(float) * R * (size_t)n);
-    H->o_ms = take(sizeof(int32_t) * n);
-    H->o_mn = take(sizeof(int32_t) * std::max<size_t>(H->mask_nodes.size(), 1));
     H->o_masks = take(sizeof(uint32_t) * (size_t)map->dev.mask_words * (size_t)H->n_masks);
     const size_t n_tiles = (size_t)((wb + kTileCols - 1) / kTileCols) * (size_t)((sensor->n_el + kTileRows - 1) / kTileRows);
     H->o_tm = take(sizeof(float) * 2 * n_tiles * (size_t)std::max(H->n_masks, 1));
@@ -692,20 +817,17 @@ int finish_upload(mg_map map, const mgb::HostTree& H, const mg_sensor* sensor, h
     if (rc != MG_OK) return rc;
     const int32_t n = H.n;
     char* base = (char*)block;
-    auto up = [&](size_t o, const void* src, size_t bytes) {
-        return bytes ? hipMemcpyAsync(base + o, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
-    };
-    std::vector<int32_t> zeros_c0(n, 0);
-    hipError_t e = up(H.o_q4, H.q4.data(), sizeof(float4) * n);
-    if (e == hipSuccess) e = up(H.o_pm, H.pm.data(), sizeof(float4) * n);
-    if (e == hipSuccess) e = up(H.o_ap, H.anc_ptr.data(), sizeof(int32_t) * (n + 1));
-    if (e == hipSuccess) e = up(H.o_ai, H.anc_ids.data(), sizeof(int32_t) * H.anc_ids.size());
-    if (e == hipSuccess) e = up(H.o_ln, H.level_nodes.data(), sizeof(int32_t) * n);
-    if (e == hipSuccess) e = up(H.o_cp, H.child_ptr.data(), sizeof(int32_t) * (n + 1));
-    if (e == hipSuccess) e = up(H.o_ci, H.child_ids.data(), sizeof(int32_t) * n);
-    if (e == hipSuccess) e = up(H.o_c0, zeros_c0.data(), sizeof(int32_t) * n);
-    if (e == hipSuccess) e = up(H.o_ms, H.mask_slot.data(), sizeof(int32_t) * n);
-    if (e == hipSuccess) e = up(H.o_mn, H.mask_nodes.data(), sizeof(int32_t) * H.mask_nodes.size());
+    // the uploaded arrays in one copy (c0 starts at 0)
+    std::vector<char> host(H.up_bytes, 0);
+    auto put = [&](size_t o, const void* src, size_t bytes) { if (bytes) std::memcpy(host.data() + o, src, bytes); };
+    put(H.o_q4, H.q4.data(), sizeof(float4) * n);
+    put(H.o_pm, H.pm.data(), sizeof(float4) * n);
+    put(H.o_ap, H.anc_ptr.data(), sizeof(int32_t) * (n + 1));
+    put(H.o_ai, H.anc_ids.data(), sizeof(int32_t) * H.anc_ids.size());
+    put(H.o_ln, H.level_nodes.data(), sizeof(int32_t) * n);
+    put(H.o_ms, H.mask_slot.data(), sizeof(int32_t) * n);
+    put(H.o_mn, H.mask_nodes.data(), sizeof(int32_t) * H.mask_nodes.size());
+    hipError_t e = hipMemcpyAsync(base, host.data(), H.up_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         release_sensor(t->sensor);
@@ -716,8 +838,8 @@ int finish_upload(mg_map map, const mgb::HostTree& H, const mg_sensor* sensor, h
     t->dev.anc_ptr = (const int32_t*)(base + H.o_ap);
     t->dev.anc_ids = (const int32_t*)(base + H.o_ai);
     t->dev.level_nodes = (const int32_t*)(base + H.o_ln);
-    t->dev.child_ptr = (const int32_t*)(base + H.o_cp);
-    t->dev.child_ids = (const int32_t*)(base + H.o_ci);
+    t->dev.gain = (uint32_t*)(base + H.o_g);
+    t->dev.yaw = (int32_t*)(base + H.o_y);
     t->dev.c0 = (int32_t*)(base + H.o_c0);
     t->dev.bins = (uint32_t*)(base + H.o_bins);
     t->dev.dpan = (float*)(base + H.o_dpan);
@@ -728,8 +850,8 @@ int finish_upload(mg_map map, const mgb::HostTree& H, const mg_sensor* sensor, h
     t->dev.mcode = (uint32_t*)(base + H.o_mc);
     t->dev.n = n;
     t->dev.anc_cap = kMaxAnc;
-    t->scratch_gain = (uint32_t*)(base + H.o_g);
-    t->scratch_yaw = (int32_t*)(base + H.o_y);
+    t->scratch_gain = t->dev.gain;
+    t->scratch_yaw = t->dev.yaw;
     t->sd = sensor_dev(t->sensor, sensor->range_m / map->voxel_m);
     if (build_lds_total(t->sd) > lds_limit()) {
         release_sensor(t->sensor);
@@ -777,21 +899,28 @@ extern "C" int mg_tree_upload(mg_map map, const float* pos_m, const int32_t* par
     int rc = prepare_tree(map, pos_m, parent, n, sensor, &H);
     if (rc != MG_OK) return rc;
     void* block = nullptr;
-    hipError_t e = hipMalloc(&block, H.total);
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    hipError_t e = mgb::pool_get(&block, H.total, dev);
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, "tree allocation (%zu bytes): %s", H.total,
                     hipGetErrorString(e));
     rc = finish_upload(map, H, sensor, (hipStream_t)hip_stream, block, true, out);
-    if (rc != MG_OK) (void)hipFree(block);
+    if (rc != MG_OK) {
+        mgb::sync_device(dev);
+        mgb::pool_put(block, H.total, dev);
+    }
     return rc;
 }
 
 extern "C" int mg_tree_destroy(mg_tree t) {
     if (!t) return fail(MG_E_INVALID, "tree is NULL");
+    // (work on the tree may still be queued on any stream)
+    if (t->owns_block) mgb::sync_device(t->device);
     mgb::forget_tree(t);
     mgb::forget_interval(t);
     mgb::forget_exact(t);
-    if (t->owns_block) (void)hipFree(t->block);
+    if (t->owns_block) mgb::pool_put(t->block, t->bytes, t->device);
     release_sensor(t->sensor);
     t->map->trees--;
     delete t;

@@ -31,10 +31,9 @@ namespace {
 
 struct Plan {
     std::vector<mg_tree> trees;
-    uint32_t* gain = nullptr;             // output buffers the descriptors point into
-    int32_t* yaw = nullptr;
-    float* depth = nullptr;
-    void* block = nullptr;                 // BatchTree[n_trees] | items[total] | mitems (nodes with children)
+    BatchOut out{};                        // output buffers of the captured graph (the other forms take each call's)
+    void* block = nullptr;                 // BatchTree[n_trees] | items[total] | mitems (nodes with children) | ...
+    size_t block_bytes = 0;
     const BatchTree* dtrees = nullptr;
     const unsigned long long* ditems = nullptr;
     const unsigned long long* dmitems = nullptr;
@@ -67,7 +66,10 @@ struct Plan {
     ~Plan() {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
-        if (block) (void)hipFree(block);
+        if (block) {
+            mgb::sync_device(device);              // its launches may still be queued
+            mgb::pool_put(block, block_bytes, device);
+        }
         if (h_abort) (void)hipHostFree(h_abort);
     }
 };
@@ -105,8 +107,7 @@ bool same_geometry(const mg_sensor& a, const mg_sensor& b) {
            a.fov_v_deg == b.fov_v_deg && a.az_offset_deg == b.az_offset_deg;
 }
 
-int build_plan(const std::vector<mg_tree>& trees, uint32_t* gain, int32_t* yaw, float* depth, hipStream_t stream,
-               std::unique_ptr<Plan>* out) {
+int build_plan(const std::vector<mg_tree>& trees, hipStream_t stream, std::unique_ptr<Plan>* out) {
     std::unique_ptr<Plan> P(new Plan());
     P->trees = trees;
     const int32_t nt = (int32_t)trees.size();
@@ -127,9 +128,6 @@ int build_plan(const std::vector<mg_tree>& trees, uint32_t* gain, int32_t* yaw, 
         bt[i].rv2 = v.sd->rv2;
         bt[i].vox3 = (double)v.voxel_m * (double)v.voxel_m * (double)v.voxel_m;
         bt[i].out_off = P->total;
-        bt[i].gain = gain + P->total;
-        bt[i].yaw = yaw + P->total;
-        bt[i].depth = depth ? depth + (size_t)P->total * v.sd->H * v.sd->WB : nullptr;
         if ((uint64_t)P->total + (uint64_t)v.n >= (1ull << 31))
             return mgb::set_error(MG_E_UNSUPPORTED, "batch has 2^31 nodes or more");
         P->total += (uint32_t)v.n;
@@ -272,33 +270,24 @@ int build_plan(const std::vector<mg_tree>& trees, uint32_t* gain, int32_t* yaw, 
     const size_t o_plevel = take(sizeof(int32_t) * plevel.size());
     const size_t o_pmlevel = take(sizeof(int32_t) * pmlevel.size());
     const size_t o_psync = take(sizeof(uint32_t) * 2);
-    hipError_t e = hipMalloc(&P->block, off);
+    hipError_t e = mgb::pool_get(&P->block, off, P->device);
     if (e != hipSuccess) return hip_fail(e, "batch plan allocation");
+    P->block_bytes = off;
+    // one copy of everything
+    std::vector<char> host(off, 0);
+    auto put = [&](size_t o, const void* src, size_t bytes) { if (bytes) std::memcpy(host.data() + o, src, bytes); };
+    put(o_trees, bt.data(), sizeof(BatchTree) * nt);
+    put(o_items, items.data(), sizeof(unsigned long long) * items.size());
+    put(o_mitems, mitems.data(), sizeof(unsigned long long) * mitems.size());
+    put(o_pitems, pitems.data(), sizeof(unsigned long long) * pitems.size());
+    put(o_pmitems, pmitems.data(), sizeof(unsigned long long) * pmitems.size());
+    put(o_plevel, plevel.data(), sizeof(int32_t) * plevel.size());
+    put(o_pmlevel, pmlevel.data(), sizeof(int32_t) * pmlevel.size());
     char* base = (char*)P->block;
-    e = hipMemcpyAsync(base + o_trees, bt.data(), sizeof(BatchTree) * nt, hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(base + o_items, items.data(), sizeof(unsigned long long) * items.size(),
-                           hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && !mitems.empty())
-        e = hipMemcpyAsync(base + o_mitems, mitems.data(), sizeof(unsigned long long) * mitems.size(),
-                           hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(base + o_pitems, pitems.data(), sizeof(unsigned long long) * pitems.size(),
-                           hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && !pmitems.empty())
-        e = hipMemcpyAsync(base + o_pmitems, pmitems.data(), sizeof(unsigned long long) * pmitems.size(),
-                           hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(base + o_plevel, plevel.data(), sizeof(int32_t) * plevel.size(), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(base + o_pmlevel, pmlevel.data(), sizeof(int32_t) * pmlevel.size(), hipMemcpyHostToDevice,
-                           stream);
+    e = hipMemcpyAsync(base, host.data(), off, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return hip_fail(e, "batch plan upload");
     P->dtrees = (const BatchTree*)(base + o_trees);
-    P->gain = gain;
-    P->yaw = yaw;
-    P->depth = depth;
     P->ditems = (const unsigned long long*)(base + o_items);
     P->dmitems = (const unsigned long long*)(base + o_mitems);
     P->pitems = (const unsigned long long*)(base + o_pitems);
@@ -387,7 +376,7 @@ int group_streams(int device, GroupStreams** out) {
 // Enqueues the plan's launches: the shared prefix on s, then each group on its
 // own stream, forked from s and joined back to it. `timed` lets the kernel
 // timer attach events.
-int run_plan(const Plan& P, hipStream_t s, bool timed) {
+int run_plan(const Plan& P, const BatchOut& out, hipStream_t s, bool timed) {
     hipError_t e = launch_batch_zero(P.dtrees, (int32_t)P.trees.size(), P.max_nodes, P.sd, s);
     if (e != hipSuccess) return hip_fail(e, "batch zero");
     GroupStreams* GS = nullptr;
@@ -411,7 +400,7 @@ int run_plan(const Plan& P, hipStream_t s, bool timed) {
         }
         hipStream_t ls = L.stream == 0 ? s : GS->stream[L.stream - 1];
         e = launch_batch_level(P.dtrees, P.ditems + L.begin, L.count, P.dmitems + L.mbegin, L.mcount, P.mask_bricks,
-                               P.sd, ls, P.shape, t0, t1, b0, b1);
+                               P.sd, out, ls, P.shape, t0, t1, b0, b1);
         if (e != hipSuccess) return hip_fail(e, "batch level");
         if (t0) {
             std::lock_guard<std::mutex> lk(g_timing.mu);
@@ -430,7 +419,7 @@ int run_plan(const Plan& P, hipStream_t s, bool timed) {
 
 // The persistent form: bins cleared, one cooperative launch, then the barrier's
 // give-up flag read back. Blocks on s (the flag decides the return code).
-int run_persistent(const Plan& P, hipStream_t s, bool timed) {
+int run_persistent(const Plan& P, const BatchOut& out, hipStream_t s, bool timed) {
     hipEvent_t t0 = nullptr, t1 = nullptr;
     if (timed) {
         int rc = next_events(P.device, &t0, &t1);
@@ -440,7 +429,7 @@ int run_persistent(const Plan& P, hipStream_t s, bool timed) {
     if (e == hipSuccess && t0) e = hipEventRecord(t0, s);
     if (e == hipSuccess)
         e = launch_batch_persistent(P.dtrees, P.pitems, P.plevel, P.pmitems, P.pmlevel, P.levels, P.mask_bricks, P.sd,
-                                    P.psync, g_barrier_polls, s);
+                                    out, P.psync, g_barrier_polls, s);
     if (e == hipSuccess && t1) e = hipEventRecord(t1, s);
     if (e == hipSuccess) e = hipMemcpyAsync(P.h_abort, P.psync + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -467,7 +456,7 @@ std::vector<int64_t> tune_key(const Plan& P) {
 
 // Times every launch shape on the plan itself (second of two runs each) and
 // keeps the fastest. Blocks on s.
-int autotune(Plan& P, hipStream_t s) {
+int autotune(Plan& P, const BatchOut& out, hipStream_t s) {
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t e = hipEventCreate(&a);
     if (e == hipSuccess) e = hipEventCreate(&b);
@@ -480,7 +469,7 @@ int autotune(Plan& P, hipStream_t s) {
         for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
             e = hipEventRecord(a, s);
             if (e != hipSuccess) break;
-            int rc = run_plan(P, s, false);
+            int rc = run_plan(P, out, s, false);
             if (rc != MG_OK) {
                 (void)hipEventDestroy(a);
                 (void)hipEventDestroy(b);
@@ -504,14 +493,15 @@ int autotune(Plan& P, hipStream_t s) {
 }
 
 // Records the plan's launches into a graph on a private stream.
-int capture(Plan& P) {
+int capture(Plan& P, const BatchOut& out) {
+    P.out = out;
     hipStream_t cs = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
     if (e != hipSuccess) return hip_fail(e, "capture stream");
     e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     int rc = MG_OK;
     if (e == hipSuccess) {
-        rc = run_plan(P, cs, false);
+        rc = run_plan(P, out, cs, false);
         hipGraph_t g = nullptr;
         const hipError_t e2 = hipStreamEndCapture(cs, &g);
         if (rc == MG_OK && e2 == hipSuccess) {
@@ -552,7 +542,7 @@ int replay(const Plan& P, hipStream_t s) {
 }
 
 // Launch shape (configured, cached or tuned now) and graph of a new plan.
-int configure(Plan& P, hipStream_t s) {
+int configure(Plan& P, const BatchOut& out, hipStream_t s) {
     if (g_cfg_persistent) {
         int32_t grid = 0;
         hipError_t e = persistent_grid(P.sd, &grid);
@@ -571,12 +561,12 @@ int configure(Plan& P, hipStream_t s) {
         if (t != g_tuned.end()) {
             P.shape = t->second;
         } else {
-            int rc = autotune(P, s);
+            int rc = autotune(P, out, s);
             if (rc != MG_OK) return rc;
             g_tuned[key] = P.shape;
         }
     }
-    if (g_cfg_graph) return capture(P);
+    if (g_cfg_graph) return capture(P, out);
     return MG_OK;
 }
 
@@ -618,8 +608,10 @@ extern "C" int mg_eval_marginal_batch(const mg_tree* trees, int32_t n_trees, voi
     hipStream_t s = (hipStream_t)hip_stream;
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_plans.find(key);
-    if (it != g_plans.end() && (it->second->gain != gain || it->second->yaw != yaw_bin || it->second->depth != depth)) {
-        (void)hipStreamSynchronize(s);          // the old descriptors may still be read
+    const BatchOut out{gain, yaw_bin, depth};
+    if (it != g_plans.end() && it->second->exec &&
+        (it->second->out.gain != gain || it->second->out.yaw != yaw_bin || it->second->out.depth != depth)) {
+        (void)hipStreamSynchronize(s);          // the graph holds the old buffers, and may still run
         g_plans.erase(it);
         it = g_plans.end();
     }
@@ -629,18 +621,18 @@ extern "C" int mg_eval_marginal_batch(const mg_tree* trees, int32_t n_trees, voi
             g_plans.clear();
         }
         std::unique_ptr<Plan> P;
-        int rc = build_plan(key, gain, yaw_bin, depth, s, &P);
+        int rc = build_plan(key, s, &P);
         if (rc != MG_OK) return rc;
         if (P->device != dev) return mgb::set_error(MG_E_INVALID, "batch trees live on another device");
-        rc = configure(*P, s);
+        rc = configure(*P, out, s);
         if (rc != MG_OK) return rc;
         it = g_plans.emplace(key, std::move(P)).first;
     }
     const Plan& P = *it->second;
     if (P.device != dev) return mgb::set_error(MG_E_INVALID, "batch trees live on another device");
-    if (P.persistent) return run_persistent(P, s, timing_on());
+    if (P.persistent) return run_persistent(P, out, s, timing_on());
     // the kernel timer needs the launches made one by one
-    if (!P.exec || timing_on()) return run_plan(P, s, true);
+    if (!P.exec || timing_on()) return run_plan(P, out, s, true);
     return replay(P, s);
 }
 

@@ -332,8 +332,8 @@ struct TreeDev {
     const int32_t* anc_ptr;    // [n+1] CSR into anc_ids
     const int32_t* anc_ids;    // ancestors, nearest first
     const int32_t* level_nodes;// [n] nodes sorted by depth
-    const int32_t* child_ptr;  // [n+1]
-    const int32_t* child_ids;
+    uint32_t* gain;            // [n] scratch outputs
+    int32_t* yaw;
     uint32_t* bins;            // [n][B]: the evaluation's counts (absolute, or marginal)
     float* dpan;               // [n][R]
     int32_t* c0;               // [n]
@@ -353,13 +353,19 @@ struct BatchTree {
     TreeDev td;
     float rv, rv2;
     double vox3;               // voxel volume (m^3): a gain count times this is a volume
-    uint32_t out_off;          // first node of this tree in the concatenated outputs
-    uint32_t* gain;            // [n]
-    int32_t* yaw;              // [n]
-    float* depth;              // [n][H][WB] or NULL
+    uint32_t out_off;          // first node of this tree in the launch's outputs (BatchOut)
     // Device status word of the tree's request, or NULL: nonzero marks the
     // request failed, and every later kernel of it returns at once.
     const int32_t* status;
+};
+
+// Where a multi-tree launch puts its results (a launch argument, so a plan does
+// not depend on the buffers): node i of tree t at t's out_off + i. At gain NULL
+// every tree's results go to its own scratch arrays (TreeDev::gain, yaw).
+struct BatchOut {
+    uint32_t* gain;
+    int32_t* yaw;
+    float* depth;              // [node][H][WB] or NULL
 };
 
 // Launchers (mg_kernels.hip).
@@ -413,7 +419,7 @@ hipError_t launch_batch_zero(const BatchTree* trees, int32_t n_trees, uint32_t m
 // mask_bricks: build slots (MapDev::build_slots) of the largest map among the launch's trees.
 hipError_t launch_batch_level(const BatchTree* trees, const unsigned long long* items, int32_t n_items,
                               const unsigned long long* mitems, int32_t n_mitems, uint32_t mask_bricks,
-                              const SensorDev& sd, hipStream_t s, int shape = 0, hipEvent_t t0 = nullptr,
+                              const SensorDev& sd, const BatchOut& out, hipStream_t s, int shape = 0, hipEvent_t t0 = nullptr,
                               hipEvent_t t1 = nullptr, hipEvent_t b0 = nullptr, hipEvent_t b1 = nullptr);
 // The whole batch in one cooperative launch of co-resident workgroups: for each
 // depth level d, the trace of items[level_ptr[d] .. level_ptr[d + 1]), their
@@ -422,8 +428,8 @@ hipError_t launch_batch_level(const BatchTree* trees, const unsigned long long* 
 // sync[1] != 0 afterwards when a barrier wait gave up after spin_limit polls.
 hipError_t launch_batch_persistent(const BatchTree* trees, const unsigned long long* items, const int32_t* level_ptr,
                                    const unsigned long long* mitems, const int32_t* mlevel_ptr, int32_t levels,
-                                   uint32_t mask_bricks, const SensorDev& sd, uint32_t* sync, uint32_t spin_limit,
-                                   hipStream_t s);
+                                   uint32_t mask_bricks, const SensorDev& sd, const BatchOut& out, uint32_t* sync,
+                                   uint32_t spin_limit, hipStream_t s);
 // Workgroups of the persistent launch: the co-resident capacity of the device.
 hipError_t persistent_grid(const SensorDev& sd, int32_t* grid);
 

@@ -895,7 +895,8 @@ __device__ __forceinline__ uint32_t xcd_grouped(uint32_t g, uint32_t n) {
 // `items` (tree << 32 | node), T workgroups per item.
 template <int kTh, int kSeg>
 __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict__ trees,
-                                                     const unsigned long long* __restrict__ items, SensorDev S) {
+                                                     const unsigned long long* __restrict__ items, SensorDev S,
+                                                     bool depth) {
     // (workgroup-uniform values kept in scalar registers)
     const uint32_t g = xcd_grouped(blockIdx.x, gridDim.x);
     const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(g / (uint32_t)S.T));
@@ -909,7 +910,7 @@ __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict
     const MapDev M = BT.map;     // copies: loaded once, not re-read through the descriptor
     const TreeDev Tr = BT.td;
     const int32_t node = (int32_t)(uint32_t)it;
-    trace_tile<true, kTh, kSeg>(M, St, Tr, node, tile, BT.depth != nullptr || Tr.mask_slot[node] >= 0);
+    trace_tile<true, kTh, kSeg>(M, St, Tr, node, tile, depth || Tr.mask_slot[node] >= 0);
 }
 
 // Path masks of one depth level's nodes with children, all trees at once:
@@ -938,7 +939,8 @@ __global__ __launch_bounds__(kBuildThreads) void k_mask_build_multi(const BatchT
 // window's first column, the depth-cull tile maxima and, when asked for, the
 // node's depth buffer. One workgroup of kThreads.
 __device__ __forceinline__ void finish_item(const BatchTree* __restrict__ trees, unsigned long long it,
-                                            const SensorDev& S, uint32_t* s_p, unsigned long long* s_best) {
+                                            const SensorDev& S, const BatchOut& out, uint32_t* s_p,
+                                            unsigned long long* s_best) {
     const BatchTree& BT = trees[(uint32_t)(it >> 32)];
     if (BT.status != nullptr && *BT.status != 0) return;      // (the request has failed)
     const int32_t node = (int32_t)(uint32_t)it;
@@ -946,15 +948,15 @@ __device__ __forceinline__ void finish_item(const BatchTree* __restrict__ trees,
     const int32_t k = S.B - 1 - (int32_t)(uint32_t)(best & 0xffffffffull);
     const int32_t c0 = S.c0_of_win[k];
     if (threadIdx.x == 0) {
-        BT.gain[node] = (uint32_t)(best >> 32);
-        BT.yaw[node] = k;
+        (out.gain ? out.gain + BT.out_off : BT.td.gain)[node] = (uint32_t)(best >> 32);
+        (out.gain ? out.yaw + BT.out_off : BT.td.yaw)[node] = k;
         BT.td.c0[node] = c0;
     }
     tile_max(S, BT.td, node, c0);
-    if (BT.depth) {
+    if (out.depth) {
         const int32_t per = S.H * S.WB;
         const float* src = BT.td.dpan + (size_t)node * S.R;
-        float* dst = BT.depth + (size_t)node * per;
+        float* dst = out.depth + ((size_t)BT.out_off + (size_t)node) * per;
         for (int32_t o = threadIdx.x; o < per; o += kThreads) {
             const int32_t j = o / S.WB, ii = o - j * S.WB;
             int32_t c = c0 + ii;
@@ -966,10 +968,11 @@ __device__ __forceinline__ void finish_item(const BatchTree* __restrict__ trees,
 
 // Window selection for one depth level of all trees: one workgroup per item.
 __global__ __launch_bounds__(kThreads) void k_finish_multi(const BatchTree* __restrict__ trees,
-                                                           const unsigned long long* __restrict__ items, SensorDev S) {
+                                                           const unsigned long long* __restrict__ items, SensorDev S,
+                                                           BatchOut out) {
     __shared__ uint32_t s_p[2 * kMaxBins + 1];
     __shared__ unsigned long long s_best[kThreads / 64];
-    finish_item(trees, items[blockIdx.x], S, s_p, s_best);
+    finish_item(trees, items[blockIdx.x], S, out, s_p, s_best);
 }
 
 // ---------------------------------------------------------------- persistent batch
@@ -1018,7 +1021,7 @@ __device__ bool grid_barrier(uint32_t* sync, uint32_t* target, uint32_t spin_lim
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_batch_persistent(
     const BatchTree* __restrict__ trees, const unsigned long long* __restrict__ items,
     const int32_t* __restrict__ level_ptr, const unsigned long long* __restrict__ mitems,
-    const int32_t* __restrict__ mlevel_ptr, int32_t levels, SensorDev S, int32_t chunks, int32_t bricks,
+    const int32_t* __restrict__ mlevel_ptr, int32_t levels, SensorDev S, BatchOut out, int32_t chunks, int32_t bricks,
     uint32_t* sync, uint32_t spin_limit) {
     extern __shared__ char smem[];
     __shared__ uint32_t s_p[2 * kMaxBins + 1];
@@ -1044,12 +1047,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                 const MapDev M = BT.map;
                 const TreeDev Tr = BT.td;
                 const int32_t node = (int32_t)(uint32_t)it;
-                trace_tile<true, kThreads>(M, St, Tr, node, tile, BT.depth != nullptr || Tr.mask_slot[node] >= 0);
+                trace_tile<true, kThreads>(M, St, Tr, node, tile, out.depth != nullptr || Tr.mask_slot[node] >= 0);
             }
         }
         if (!grid_barrier(sync, &target, spin_limit, &s_ok)) return;
         for (uint32_t u = blockIdx.x; u < (uint32_t)n; u += G) {
-            finish_item(trees, items[i0 + (int32_t)u], S, s_p, s_best);
+            finish_item(trees, items[i0 + (int32_t)u], S, out, s_p, s_best);
             __syncthreads();
         }
         if (!grid_barrier(sync, &target, spin_limit, &s_ok)) return;
@@ -1412,15 +1415,15 @@ namespace {
 
 template <int kTh>
 void launch_multi(const BatchTree* trees, const unsigned long long* items, int32_t n_items, const SensorDev& sd,
-                  hipStream_t s, hipEvent_t t0, hipEvent_t t1, int shape) {
+                  bool depth, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int shape) {
     const int seg = trace_segments(sd, n_items, sd.W);
     const SensorDev st = trace_sensor(sd, seg, seg > 1 ? 64 : kTh, sd.W);
     const dim3 grid((unsigned)n_items * (unsigned)st.T);
     auto go = [&](auto kernel, int threads) {
         if (t0 && t1)
-            hipExtLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, t0, t1, 0u, trees, items, st);
+            hipExtLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, t0, t1, 0u, trees, items, st, depth);
         else
-            hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, trees, items, st);
+            hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, trees, items, st, depth);
     };
     if (seg == 8)
         go(k_trace_multi<64, 8>, 64);
@@ -1434,12 +1437,12 @@ void launch_multi(const BatchTree* trees, const unsigned long long* items, int32
 
 template <int I>
 void launch_multi_shape(int shape, const BatchTree* trees, const unsigned long long* items, int32_t n_items,
-                        const SensorDev& sd, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
+                        const SensorDev& sd, bool depth, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
     if constexpr (I < kNumShapes) {
         if (shape == I)
-            launch_multi<kShapes[I].threads>(trees, items, n_items, sd, s, t0, t1, I);
+            launch_multi<kShapes[I].threads>(trees, items, n_items, sd, depth, s, t0, t1, I);
         else
-            launch_multi_shape<I + 1>(shape, trees, items, n_items, sd, s, t0, t1);
+            launch_multi_shape<I + 1>(shape, trees, items, n_items, sd, depth, s, t0, t1);
     }
 }
 
@@ -1447,16 +1450,16 @@ void launch_multi_shape(int shape, const BatchTree* trees, const unsigned long l
 
 hipError_t launch_batch_level(const BatchTree* trees, const unsigned long long* items, int32_t n_items,
                               const unsigned long long* mitems, int32_t n_mitems, uint32_t mask_bricks,
-                              const SensorDev& sd, hipStream_t s, int shape, hipEvent_t t0, hipEvent_t t1,
+                              const SensorDev& sd, const BatchOut& out, hipStream_t s, int shape, hipEvent_t t0, hipEvent_t t1,
                               hipEvent_t b0, hipEvent_t b1) {
     if (n_items <= 0) return hipSuccess;
     if (shape < 0 || shape >= kNumShapes) return hipErrorInvalidValue;
     const size_t lds = build_lds_bytes(sd);
     if (lds + kBuildFixedLds > lds_limit()) return hipErrorInvalidConfiguration;
-    launch_multi_shape<0>(shape, trees, items, n_items, sd, s, t0, t1);
+    launch_multi_shape<0>(shape, trees, items, n_items, sd, out.depth != nullptr, s, t0, t1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finish_multi, dim3((unsigned)n_items), dim3(kThreads), 0, s, trees, items, sd);
+    hipLaunchKernelGGL(k_finish_multi, dim3((unsigned)n_items), dim3(kThreads), 0, s, trees, items, sd, out);
     e = hipGetLastError();
     if (e != hipSuccess || n_mitems <= 0) return e;
     const int32_t bricks = build_bricks(mask_bricks, n_mitems, kShapes[shape].bricks);
@@ -1487,8 +1490,8 @@ hipError_t persistent_grid(const SensorDev& sd, int32_t* grid) {
 
 hipError_t launch_batch_persistent(const BatchTree* trees, const unsigned long long* items, const int32_t* level_ptr,
                                    const unsigned long long* mitems, const int32_t* mlevel_ptr, int32_t levels,
-                                   uint32_t mask_bricks, const SensorDev& sd, uint32_t* sync, uint32_t spin_limit,
-                                   hipStream_t s) {
+                                   uint32_t mask_bricks, const SensorDev& sd, const BatchOut& out, uint32_t* sync,
+                                   uint32_t spin_limit, hipStream_t s) {
     if (levels <= 0) return hipSuccess;
     const size_t lds = build_lds_bytes(sd);
     if (lds + kBuildFixedLds > lds_limit()) return hipErrorInvalidConfiguration;
@@ -1502,7 +1505,7 @@ hipError_t launch_batch_persistent(const BatchTree* trees, const unsigned long l
     e = launch_zero_u32(sync, 2, s);
     if (e != hipSuccess) return e;
     void* args[] = {(void*)&trees, (void*)&items, (void*)&level_ptr, (void*)&mitems, (void*)&mlevel_ptr,
-                    (void*)&levels, (void*)&st, (void*)&chunks, (void*)&bricks, (void*)&sync, (void*)&spin_limit};
+                    (void*)&levels, (void*)&st, (void*)&out, (void*)&chunks, (void*)&bricks, (void*)&sync, (void*)&spin_limit};
     e = hipLaunchCooperativeKernel((const void*)k_batch_persistent, dim3((unsigned)grid), dim3(kThreads), args, lds, s);
     if (e != hipSuccess) return e;
     return hipGetLastError();

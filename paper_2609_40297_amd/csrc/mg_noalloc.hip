@@ -132,9 +132,6 @@ extern "C" int mg_eval_marginal_batch_noalloc(const mg_tree* trees, int32_t n_tr
         bt[i].rv2 = v.sd->rv2;
         bt[i].vox3 = (double)v.voxel_m * (double)v.voxel_m * (double)v.voxel_m;
         bt[i].out_off = off;
-        bt[i].gain = gain + off;
-        bt[i].yaw = yaw_bin + off;
-        bt[i].depth = depth ? depth + (size_t)off * v.sd->H * v.sd->WB : nullptr;
         off += (uint32_t)v.n;
     }
     int64_t k = 0, km = 0;
@@ -169,7 +166,7 @@ extern "C" int mg_eval_marginal_batch_noalloc(const mg_tree* trees, int32_t n_tr
     for (int32_t d = 0; d < levels && e == hipSuccess; ++d)
         e = launch_batch_level(dtrees, ditems + g_level_item[d], (int32_t)(g_level_item[d + 1] - g_level_item[d]),
                                dmitems + g_level_mitem[d], (int32_t)(g_level_mitem[d + 1] - g_level_mitem[d]),
-                               mask_bricks, *v0.sd, s, 0);
+                               mask_bricks, *v0.sd, BatchOut{gain, yaw_bin, depth}, s, 0);
     if (e != hipSuccess) return hip_fail(e, "batch level");
     return MG_OK;
 }

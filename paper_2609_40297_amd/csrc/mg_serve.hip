@@ -390,9 +390,7 @@ int mg_server_s::step() {
         bt.td = *v.td;
         bt.rv = v.sd->rv;
         bt.rv2 = v.sd->rv2;
-        bt.gain = v.scratch_gain;
-        bt.yaw = v.scratch_yaw;
-        bt.depth = nullptr;
+        bt.out_off = 0;
         bt.status = d_status + r->slot;
         for (int32_t j = (*r->level_ptr)[r->level]; j < (*r->level_ptr)[r->level + 1]; ++j)
             h_items[k++] = ((unsigned long long)i << 32) | (uint32_t)(*r->level_nodes)[j];
@@ -405,7 +403,7 @@ int mg_server_s::step() {
                            compute);
     if (e == hipSuccess)
         e = launch_batch_level(d_trees, d_items, (int32_t)n_items, d_items + n_items, (int32_t)n_mitems, mask_bricks, sd,
-                               compute, serve_shape());
+                               BatchOut{}, compute, serve_shape());   // (results to the trees' scratch arrays)
     size_t so = 0;
     std::vector<std::pair<Request*, size_t>> finishing;
     for (Request* r : active) {
