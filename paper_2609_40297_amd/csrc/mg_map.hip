@@ -149,14 +149,41 @@ __global__ void k_map_scatter(const uint32_t* __restrict__ ids, const uint8_t* _
     }
 }
 
-// Dense x-fastest copy of the grid's states.
-__global__ void k_unbrick(const uint8_t* __restrict__ bricks, MapDev m, uint8_t* __restrict__ dense, uint32_t keep) {
-    const size_t nxy = (size_t)m.nx * (size_t)m.ny;
-    const size_t nvox = nxy * (size_t)m.nz;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox; i += (size_t)gridDim.x * blockDim.x) {
-        const int32_t x = (int32_t)(i % (size_t)m.nx), y = (int32_t)((i / (size_t)m.nx) % (size_t)m.ny);
-        const int32_t z = (int32_t)(i / nxy);
-        dense[i] = bricks[voxel_addr(x, y, z, m)] & keep;   // (the state, or the state with its block mark)
+// Dense x-fastest copy of the grid's bytes, `keep` bits of each (the state, or the
+// state with its block mark): one workgroup per run of up to 32 bricks along x at
+// one (by, bz), read in 16-byte loads (the run is contiguous) into LDS and written
+// row by row, kBytes (8, 4 or 1, as the rows' alignment allows) per thread. Bound
+// by HBM: 1 B read and 1 B written a voxel. 512 x 512 x 128: 14 us, 4.8 TB/s; a
+// byte per thread, its address found by two divisions: 78 us.
+constexpr int kRowBrick = 528;      // LDS stride of a brick: rows of neighbouring bricks in other banks
+template <int kBytes>
+__global__ __launch_bounds__(256) void k_unbrick(const uint8_t* __restrict__ bricks, MapDev m,
+                                                 uint8_t* __restrict__ dense, uint32_t keep) {
+    __shared__ __align__(16) uint8_t tile[kTileBricks * kRowBrick];
+    const int32_t tb = m.nbx < kTileBricks ? m.nbx : kTileBricks;   // (nbx is a power of two)
+    const int32_t bx0 = (int32_t)blockIdx.x * tb, by = (int32_t)blockIdx.y, bz = (int32_t)blockIdx.z;
+    const int32_t tid = (int32_t)threadIdx.x;
+    const size_t base = ((size_t)bx0 + (size_t)m.nbx * ((size_t)by + (size_t)m.nby * (size_t)bz)) * 512u;
+    const uint4* src = (const uint4*)(bricks + base);
+    const uint32_t k4 = keep * 0x01010101u;
+    for (int32_t o = tid; o < tb * 32; o += 256) {
+        const uint4 v = src[o];
+        *(uint4*)&tile[(o >> 5) * kRowBrick + (o & 31) * 16] = make_uint4(v.x & k4, v.y & k4, v.z & k4, v.w & k4);
+    }
+    __syncthreads();
+    const int32_t x0 = bx0 * 8, width = min(tb * 8, m.nx - x0), per = (width + kBytes - 1) / kBytes;   // pieces of a row
+    for (int32_t o = tid; o < per * 64; o += 256) {
+        const int32_t r = o / per, x = (o - r * per) * kBytes;
+        const int32_t y = by * 8 + (r & 7), z = bz * 8 + (r >> 3);
+        if (y >= m.ny || z >= m.nz) continue;
+        const uint8_t* p = &tile[(x >> 3) * kRowBrick + (x & 7) + r * 8];
+        uint8_t* to = dense + (size_t)(x0 + x) + (size_t)m.nx * ((size_t)y + (size_t)m.ny * (size_t)z);
+        if (kBytes == 8)
+            *(uint64_t*)to = *(const uint64_t*)p;
+        else if (kBytes == 4)
+            *(uint32_t*)to = *(const uint32_t*)p;
+        else
+            *to = *p;
     }
 }
 
@@ -214,8 +241,16 @@ hipError_t launch_map_scatter(const uint32_t* ids, const uint8_t* states, uint32
 }
 
 hipError_t launch_unbrick(const MapDev& m, uint8_t* dense, hipStream_t s, bool marks) {
-    const size_t nvox = (size_t)m.nx * m.ny * m.nz;
-    hipLaunchKernelGGL(k_unbrick, dim3(blocks_for(nvox)), dim3(256), 0, s, m.bricks, m, dense, marks ? 0xffu : 3u);
+    const int32_t tb = m.nbx < kTileBricks ? m.nbx : kTileBricks;
+    const dim3 grid(((unsigned)m.mbx + (unsigned)tb - 1u) / (unsigned)tb, m.mby, m.mbz);
+    const uint32_t keep = marks ? 0xffu : 3u;
+    // (rows start at multiples of nx from dense: a piece never straddles a row's end)
+    if (m.nx % 8 == 0 && (uintptr_t)dense % 8 == 0)
+        hipLaunchKernelGGL(k_unbrick<8>, grid, dim3(256), 0, s, m.bricks, m, dense, keep);
+    else if (m.nx % 4 == 0 && (uintptr_t)dense % 4 == 0)
+        hipLaunchKernelGGL(k_unbrick<4>, grid, dim3(256), 0, s, m.bricks, m, dense, keep);
+    else
+        hipLaunchKernelGGL(k_unbrick<1>, grid, dim3(256), 0, s, m.bricks, m, dense, keep);
     return hipGetLastError();
 }
 
