@@ -152,64 +152,6 @@ __device__ __forceinline__ uint32_t mask_brick(int32_t x, int32_t y, int32_t z, 
     return (uint32_t)(x >> 3) + __umul24(M.mbx, (uint32_t)(y >> 3) + __umul24(M.mby, (uint32_t)(z >> 3)));
 }
 
-// How many of one axis's boundaries b0, b0 + db, b0 + 2 db, ... the DDA
-// crosses before the crossing at parameter Tc: those with parameter
-// t = (b - q) * f below Tc (a caller that wants ties counted passes the next
-// float above the crossing). Parameters grow by at least 1 from one boundary
-// to the next, so these boundaries are a prefix; the caller's crossing leaves
-// a block of at most 16 voxels a side, so the prefix ends at the axis's own
-// exit from that block, at most 15 boundaries on. Three probes (at 3, then
-// 3 +- 2, then +- 1) find its length when the block's edge is at most 8; a
-// first probe at 7 (then 11 or 3) extends the search to 15 (`wide`). Boundaries are evaluated exactly as the single step
-// evaluates them (the fused multiply-add of integers is exact). Returned as a
-// float count.
-__device__ __forceinline__ float crossings_before(float b0, float db, float q, float f, float Tc, bool wide) {
-    float m = 3.f;
-    if (wide) m = ((__builtin_fmaf(7.f, db, b0) - q) * f < Tc) ? 11.f : 3.f;
-    m += ((__builtin_fmaf(m, db, b0) - q) * f < Tc) ? 2.f : -2.f;
-    m += ((__builtin_fmaf(m, db, b0) - q) * f < Tc) ? 1.f : -1.f;
-    return m + (((__builtin_fmaf(m, db, b0) - q) * f < Tc) ? 1.f : 0.f);
-}
-
-// One step over the marked block (wholly free or wholly unknown, `edge` voxels
-// a side) that voxel (ix, iy, iz) lies in, taken as the per-voxel trace
-// takes it: the block is left through the face whose boundary parameter comes
-// first (ties x, then y, then z), and every axis has crossed the boundaries
-// whose parameters come before that crossing in the same order, which is where
-// the voxel-by-voxel DDA stands once it has left the block. Updates the voxel,
-// the next boundaries (integers) and their parameters, and returns the entry
-// parameter of the voxel it enters.
-__device__ __forceinline__ float cross_block(int32_t edge, float4 p, float4 inv, int32_t sx, int32_t sy, int32_t sz,
-                                             int32_t& ix, int32_t& iy, int32_t& iz, int32_t& bx, int32_t& by,
-                                             int32_t& bz, float& tx, float& ty, float& tz) {
-    const float inf = __builtin_inff();
-    // (an axis the ray does not move along: boundary +inf, node -inf, factor 1,
-    // so each of its parameters is +inf)
-    const float qx = sx ? p.x : -inf, qy = sy ? p.y : -inf, qz = sz ? p.z : -inf;
-    const float fx = sx ? inv.x : 1.f, fy = sy ? inv.y : 1.f, fz = sz ? inv.z : 1.f;
-    const float Tx = ((float)((ix & -edge) + (sx > 0 ? edge : 0)) - qx) * fx;
-    const float Ty = ((float)((iy & -edge) + (sy > 0 ? edge : 0)) - qy) * fy;
-    const float Tz = ((float)((iz & -edge) + (sz > 0 ? edge : 0)) - qz) * fz;
-    const bool ex = (Tx <= Ty) & (Tx <= Tz);
-    const bool ey = !ex & (Ty <= Tz);
-    const bool ez = !ex & !ey;
-    const float T = ex ? Tx : (ey ? Ty : Tz);
-    // an axis before the exit axis in the tie order also crosses a boundary at
-    // exactly T: it compares with the next float above T (T >= 0; +0 for -0)
-    const float Tn = __uint_as_float(__float_as_uint(T + 0.f) + 1u);
-    const bool wide = edge > 8;
-    const int32_t kx = (int32_t)crossings_before(sx ? (float)bx : inf, (float)sx, qx, fx, ex ? T : Tn, wide) + (ex ? 1 : 0);
-    const int32_t ky = (int32_t)crossings_before(sy ? (float)by : inf, (float)sy, qy, fy, ez ? Tn : T, wide) + (ey ? 1 : 0);
-    const int32_t kz = (int32_t)crossings_before(sz ? (float)bz : inf, (float)sz, qz, fz, T, wide) + (ez ? 1 : 0);
-    ix += kx * sx; bx += kx * sx;
-    iy += ky * sy; by += ky * sy;
-    iz += kz * sz; bz += kz * sz;
-    tx = sx ? ((float)bx - p.x) * inv.x : inf;
-    ty = sy ? ((float)by - p.y) * inv.y : inf;
-    tz = sz ? ((float)bz - p.z) * inv.z : inf;
-    return T;
-}
-
 // A ray walked by the Amanatides-Woo 3D DDA (face-crossing parameters recomputed
 // as (boundary - q) * (1/d); ties step x, then y, then z), an aligned block at a
 // time.
@@ -266,6 +208,13 @@ struct RayWalk {
         ux = max(ux, (int32_t)ex - ((ex - qx) * fx <= ax ? 0 : 1));
         uy = max(uy, (int32_t)ey - ((ey - qy) * fy <= ay ? 0 : 1));
         uz = max(uz, (int32_t)ez - ((ez - qz) * fz <= az ? 0 : 1));
+    }
+    // The parameter at which the aligned block of e1 + 1 voxels a side is left.
+    __device__ __forceinline__ float exit(uint32_t e1) const {
+        const float Tx = ((float)((ux | (int32_t)e1) + 1) - qx) * fx;
+        const float Ty = ((float)((uy | (int32_t)e1) + 1) - qy) * fy;
+        const float Tz = ((float)((uz | (int32_t)e1) + 1) - qz) * fz;
+        return fminf(fminf(Tx, Ty), Tz);
     }
     // Leaves the aligned block of e1 + 1 voxels a side and returns the parameter T
     // at which it is left. Where the walk's end lies inside the block (T is not
