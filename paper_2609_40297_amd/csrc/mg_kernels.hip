@@ -782,92 +782,116 @@ __global__ __launch_bounds__(kTreeTraceThreads) void k_trace_window(MapDev M, Se
 
 // ---------------------------------------------------------------- window selection
 
+// A level's window selection stands between its trace and its mask builder, so
+// its time is the latency of one workgroup's chain of loads: bins, then the
+// window's first hits. Hence every load that does not depend on the window is
+// requested at once, the scan takes three barriers, a tile's 16 first hits are
+// in flight together, and a small level deals a node's tiles (and depth image)
+// to several workgroups, which all repeat the selection. With a scan of a
+// barrier pair per step and tiles read value by value, 500 nodes in 9 levels took
+// 957 us, 920 us so; 20 nodes in 5 levels 97.5 and 89.3 us.
+struct FinishLds {
+    uint32_t p[2 * kMaxBins + 1];
+    uint32_t tot[kThreads / 64];
+    unsigned long long best[kThreads / 64];
+    int32_t c0[kMaxBins];
+};
+
 // Window sums from a prefix sum over the bins taken circularly
 // (P[i+1] = P[i] + bins[i mod B], S(k) = P[k+w] - P[k]), then the largest sum
 // with the smallest k. Whole workgroup; returns (sum << 32) | (B - 1 - k) to
-// every thread. Bins are read with atomic loads (they were accumulated with
-// device-scope atomics, possibly by other workgroups).
+// every thread, and the window's first column in *c0. Bins are read with atomic
+// loads (they were accumulated with device-scope atomics, possibly by other
+// workgroups). The workgroup synchronises before it uses `s` again.
+__device__ __forceinline__ unsigned long long select_window(const uint32_t* bins, const SensorDev& S, FinishLds& s,
+                                                            int32_t* c0) {
+    static_assert(2 * kThreads >= 2 * kMaxBins, "two bins a thread");
+    const int32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t L = S.B + S.w;   // extended length <= 2 * S.B
+    uint32_t v[2];
+#pragma unroll
+    for (int32_t e = 0; e < 2; ++e) {
+        const int32_t i = 2 * tid + e;
+        v[e] = i < L ? __hip_atomic_load(&bins[i < S.B ? i : i - S.B], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    }
+    if (tid < S.B) s.c0[tid] = S.c0_of_win[tid];
+    uint32_t x = v[0] + v[1];
+    for (int32_t off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(x, off, 64);
+        x += lane >= off ? o : 0u;
+    }
+    if (lane == 63) s.tot[wave] = x;
+    __syncthreads();
+    for (int32_t i = 0; i < kThreads / 64 - 1; ++i) x += i < wave ? s.tot[i] : 0u;
+    if (tid == 0) s.p[0] = 0u;
+    s.p[2 * tid + 1] = x - v[1];
+    s.p[2 * tid + 2] = x;
+    __syncthreads();
+    unsigned long long key = 0ull;
+    if (tid < S.B) key = ((unsigned long long)(s.p[tid + S.w] - s.p[tid]) << 32) | (uint32_t)(S.B - 1 - tid);
+    for (int32_t off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(key, off, 64);
+        key = o > key ? o : key;
+    }
+    if (lane == 0) s.best[wave] = key;
+    __syncthreads();
+    unsigned long long best = s.best[0];
+    for (int32_t i = 1; i < kThreads / 64; ++i) best = s.best[i] > best ? s.best[i] : best;
+    *c0 = s.c0[S.B - 1 - (int32_t)(uint32_t)(best & 0xffffffffull)];
+    return best;
+}
+
 // The largest and the smallest first hit of each tile of a node's window
 // (kTileCols x kTileRows pixels, partial at the window's edges), for the mask
 // builder's whole-brick tests of the node's bricks; only nodes with children
-// have a path mask to build.
+// (slot >= 0) have a path mask to build.
 // Consecutive threads take consecutive tiles of a tile column, so their reads
-// of the column-major panorama are contiguous.
-__device__ __forceinline__ void tile_max(const SensorDev& S, const TreeDev& Tr, int32_t node, int32_t c0) {
-    const int32_t slot = Tr.mask_slot[node];
+// of the column-major panorama are contiguous. A partial tile reads its last
+// column and row again instead of stopping early.
+__device__ __forceinline__ void tile_max(const SensorDev& S, const TreeDev& Tr, int32_t node, int32_t slot, int32_t c0,
+                                         int32_t part, int32_t parts) {
     if (slot < 0) return;
     const float* src = Tr.dpan + (size_t)node * S.R;
     float* dst = Tr.tmax + (size_t)slot * 2 * S.n_tiles;
-    for (int32_t t = threadIdx.x; t < S.n_tiles; t += blockDim.x) {
-        const int32_t tc = t / S.trows, tr = t - tc * S.trows;
-        const int32_t j0 = tr * kTileRows, j1 = min(j0 + kTileRows, S.H);
-        float m = 0.f, mn = __builtin_inff();
-        for (int32_t i = tc * kTileCols; i < min((tc + 1) * kTileCols, S.WB); ++i) {
-            const float* col = src + (size_t)wrap(c0 + i, S.W) * S.H;
-            for (int32_t j = j0; j < j1; ++j) {
-                m = fmaxf(m, col[j]);
-                mn = fminf(mn, col[j]);
-            }
+    for (int32_t t = part * kThreads + (int32_t)threadIdx.x; t < S.n_tiles; t += parts * kThreads) {
+        const int32_t tc = t / S.trows, j0 = (t - tc * S.trows) * kTileRows;
+        float f[kTileCols][kTileRows];
+#pragma unroll
+        for (int32_t i = 0; i < kTileCols; ++i) {
+            const float* col = src + (size_t)wrap(c0 + min(tc * kTileCols + i, S.WB - 1), S.W) * S.H;
+#pragma unroll
+            for (int32_t j = 0; j < kTileRows; ++j) f[i][j] = col[min(j0 + j, S.H - 1)];
         }
+        float m = 0.f, mn = __builtin_inff();
+#pragma unroll
+        for (int32_t i = 0; i < kTileCols; ++i)
+#pragma unroll
+            for (int32_t j = 0; j < kTileRows; ++j) {
+                m = fmaxf(m, f[i][j]);
+                mn = fminf(mn, f[i][j]);
+            }
         dst[t] = m;
         dst[S.n_tiles + t] = mn;
     }
 }
 
-__device__ __forceinline__ unsigned long long select_window(const uint32_t* bins, const SensorDev& S,
-                                                            uint32_t* s_p, unsigned long long* s_best) {
-    const int32_t tid = threadIdx.x;
-    const int32_t L = S.B + S.w;   // extended length <= 2*kMaxBins
-    for (int32_t i = tid; i < L; i += kThreads)
-        s_p[i + 1] = __hip_atomic_load(&bins[i % S.B], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 0) s_p[0] = 0u;
-    __syncthreads();
-    // inclusive Hillis-Steele scan of s_p[1..L]
-    for (int32_t off = 1; off < L; off <<= 1) {
-        uint32_t v0 = 0, v1 = 0;
-        const int32_t i0 = tid + 1, i1 = tid + 1 + kThreads;
-        if (i0 <= L && i0 - off >= 1) v0 = s_p[i0 - off];
-        if (i1 <= L && i1 - off >= 1) v1 = s_p[i1 - off];
-        __syncthreads();
-        if (i0 <= L) s_p[i0] += v0;
-        if (i1 <= L) s_p[i1] += v1;
-        __syncthreads();
-    }
-    unsigned long long key = 0ull;
-    for (int32_t k = tid; k < S.B; k += kThreads) {
-        const uint32_t sum = s_p[k + S.w] - s_p[k];
-        const unsigned long long kk = ((unsigned long long)sum << 32) | (uint32_t)(S.B - 1 - k);
-        key = kk > key ? kk : key;
-    }
-    for (int32_t off = 32; off > 0; off >>= 1) {
-        const unsigned long long o = __shfl_xor(key, off, 64);
-        key = o > key ? o : key;
-    }
-    if ((tid & 63) == 0) s_best[tid >> 6] = key;
-    __syncthreads();
-    unsigned long long best = s_best[0];
-    for (int32_t i = 1; i < kThreads / 64; ++i) best = s_best[i] > best ? s_best[i] : best;
-    __syncthreads();
-    return best;
-}
-
-// One workgroup per node of a level: gain and window; in marginal mode also
+// `parts` workgroups per node of a level: gain and window; in marginal mode also
 // the node's window start column for its descendants.
 __global__ __launch_bounds__(kThreads) void k_finish(SensorDev S, TreeDev Tr, const int32_t* __restrict__ nodes,
                                                      int marginal, uint32_t* __restrict__ gain,
-                                                     int32_t* __restrict__ yaw) {
-    __shared__ uint32_t s_p[2 * kMaxBins + 1];
-    __shared__ unsigned long long s_best[kThreads / 64];
-    const int32_t node = nodes[blockIdx.x];
-    const unsigned long long best =
-        select_window(Tr.bins + (size_t)node * S.B, S, s_p, s_best);
-    const int32_t k = S.B - 1 - (int32_t)(uint32_t)(best & 0xffffffffull);
-    if (threadIdx.x == 0) {
+                                                     int32_t* __restrict__ yaw, int32_t parts) {
+    __shared__ FinishLds s;
+    const int32_t item = (int32_t)(blockIdx.x / (uint32_t)parts), part = (int32_t)blockIdx.x - item * parts;
+    const int32_t node = nodes[item];
+    const int32_t slot = marginal ? Tr.mask_slot[node] : -1;
+    int32_t c0;
+    const unsigned long long best = select_window(Tr.bins + (size_t)node * S.B, S, s, &c0);
+    if (threadIdx.x == 0 && part == 0) {
         gain[node] = (uint32_t)(best >> 32);
-        yaw[node] = k;
-        if (marginal) Tr.c0[node] = S.c0_of_win[k];
+        yaw[node] = S.B - 1 - (int32_t)(uint32_t)(best & 0xffffffffull);
+        if (marginal) Tr.c0[node] = c0;
     }
-    if (marginal) tile_max(S, Tr, node, S.c0_of_win[k]);
+    tile_max(S, Tr, node, slot, c0, part, parts);
 }
 
 // ---------------------------------------------------------------- multi-tree, level by level
@@ -937,27 +961,28 @@ __global__ __launch_bounds__(kBuildThreads) void k_mask_build_multi(const BatchT
 
 // Window selection of one (tree, node) item of a batch: gain, window, the
 // window's first column, the depth-cull tile maxima and, when asked for, the
-// node's depth buffer. One workgroup of kThreads.
+// node's depth buffer. Workgroup `part` of the `parts` that share the item.
 __device__ __forceinline__ void finish_item(const BatchTree* __restrict__ trees, unsigned long long it,
-                                            const SensorDev& S, const BatchOut& out, uint32_t* s_p,
-                                            unsigned long long* s_best) {
+                                            const SensorDev& S, const BatchOut& out, FinishLds& s, int32_t part,
+                                            int32_t parts) {
     const BatchTree& BT = trees[(uint32_t)(it >> 32)];
     if (BT.status != nullptr && *BT.status != 0) return;      // (the request has failed)
     const int32_t node = (int32_t)(uint32_t)it;
-    const unsigned long long best = select_window(BT.td.bins + (size_t)node * S.B, S, s_p, s_best);
-    const int32_t k = S.B - 1 - (int32_t)(uint32_t)(best & 0xffffffffull);
-    const int32_t c0 = S.c0_of_win[k];
-    if (threadIdx.x == 0) {
+    const int32_t slot = BT.td.mask_slot[node];
+    int32_t c0;
+    const unsigned long long best = select_window(BT.td.bins + (size_t)node * S.B, S, s, &c0);
+    if (threadIdx.x == 0 && part == 0) {
+        const int32_t k = S.B - 1 - (int32_t)(uint32_t)(best & 0xffffffffull);
         (out.gain ? out.gain + BT.out_off : BT.td.gain)[node] = (uint32_t)(best >> 32);
         (out.gain ? out.yaw + BT.out_off : BT.td.yaw)[node] = k;
         BT.td.c0[node] = c0;
     }
-    tile_max(S, BT.td, node, c0);
+    tile_max(S, BT.td, node, slot, c0, part, parts);
     if (out.depth) {
         const int32_t per = S.H * S.WB;
         const float* src = BT.td.dpan + (size_t)node * S.R;
         float* dst = out.depth + ((size_t)BT.out_off + (size_t)node) * per;
-        for (int32_t o = threadIdx.x; o < per; o += kThreads) {
+        for (int32_t o = part * kThreads + (int32_t)threadIdx.x; o < per; o += parts * kThreads) {
             const int32_t j = o / S.WB, ii = o - j * S.WB;
             int32_t c = c0 + ii;
             c = c >= S.W ? c - S.W : c;
@@ -966,13 +991,13 @@ __device__ __forceinline__ void finish_item(const BatchTree* __restrict__ trees,
     }
 }
 
-// Window selection for one depth level of all trees: one workgroup per item.
+// Window selection for one depth level of all trees: `parts` workgroups per item.
 __global__ __launch_bounds__(kThreads) void k_finish_multi(const BatchTree* __restrict__ trees,
                                                            const unsigned long long* __restrict__ items, SensorDev S,
-                                                           BatchOut out) {
-    __shared__ uint32_t s_p[2 * kMaxBins + 1];
-    __shared__ unsigned long long s_best[kThreads / 64];
-    finish_item(trees, items[blockIdx.x], S, out, s_p, s_best);
+                                                           BatchOut out, int32_t parts) {
+    __shared__ FinishLds s;
+    const int32_t item = (int32_t)(blockIdx.x / (uint32_t)parts);
+    finish_item(trees, items[item], S, out, s, (int32_t)blockIdx.x - item * parts, parts);
 }
 
 // ---------------------------------------------------------------- persistent batch
@@ -1024,11 +1049,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     const int32_t* __restrict__ mlevel_ptr, int32_t levels, SensorDev S, BatchOut out, int32_t chunks, int32_t bricks,
     uint32_t* sync, uint32_t spin_limit) {
     extern __shared__ char smem[];
-    __shared__ uint32_t s_p[2 * kMaxBins + 1];
-    __shared__ unsigned long long s_best[kThreads / 64];
     __shared__ uint8_t s_live[kMaxBuildBricks];
-    __shared__ uint32_t s_cw[kMaxBuildBricks];
-    __shared__ uint32_t s_b[kMaxBuildBricks];
+    __shared__ union {                       // (a phase each, a barrier between them)
+        FinishLds fin;
+        struct { uint32_t cw[kMaxBuildBricks], b[kMaxBuildBricks]; } build;
+    } s_u;
     __shared__ int32_t s_any, s_ok;
     uint32_t target = 0;
     const uint32_t G = gridDim.x;
@@ -1052,7 +1077,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         }
         if (!grid_barrier(sync, &target, spin_limit, &s_ok)) return;
         for (uint32_t u = blockIdx.x; u < (uint32_t)n; u += G) {
-            finish_item(trees, items[i0 + (int32_t)u], S, out, s_p, s_best);
+            finish_item(trees, items[i0 + (int32_t)u], S, out, s_u.fin, 0, 1);
             __syncthreads();
         }
         if (!grid_barrier(sync, &target, spin_limit, &s_ok)) return;
@@ -1069,7 +1094,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                 St.rv2 = BT.rv2;
                 const MapDev M = BT.map;
                 const TreeDev Tr = BT.td;
-                build_chunk(M, St, Tr, (int32_t)(uint32_t)it, chunk, bricks, smem, s_live, s_cw, s_b, &s_any);
+                build_chunk(M, St, Tr, (int32_t)(uint32_t)it, chunk, bricks, smem, s_live, s_u.build.cw, s_u.build.b, &s_any);
             }
             __syncthreads();
         }
@@ -1263,10 +1288,23 @@ hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev
     return hipGetLastError();
 }
 
+// Workgroups that share a node's window selection: one tile a thread, while the
+// launch stays within kFinishFill workgroups. 500 nodes of 345 tiles (two
+// workgroups for levels of up to 512): 926 us with one each, 920 us; up to 4096
+// workgroups gains nothing more and repeats selections that fill the chip anyway
+// (16 trees of up to 2000 nodes: 8.45 and 8.54 ms).
+constexpr int32_t kFinishFill = 1024;
+static int32_t finish_parts(const SensorDev& sd, int32_t n_items, bool tiles) {
+    const int32_t work = tiles ? (sd.n_tiles + kThreads - 1) / kThreads : 1;
+    return std::max(std::min(work, kFinishFill / n_items), 1);
+}
+
 hipError_t launch_finish(const SensorDev& sd, const TreeDev& td, const int32_t* nodes, int32_t n_nodes,
                          bool marginal, uint32_t* gain, int32_t* yaw, hipStream_t s) {
     if (n_nodes <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finish, dim3(n_nodes), dim3(kThreads), 0, s, sd, td, nodes, marginal ? 1 : 0, gain, yaw);
+    const int32_t parts = finish_parts(sd, n_nodes, marginal);
+    hipLaunchKernelGGL(k_finish, dim3((unsigned)(n_nodes * parts)), dim3(kThreads), 0, s, sd, td, nodes,
+                       marginal ? 1 : 0, gain, yaw, parts);
     return hipGetLastError();
 }
 
@@ -1460,7 +1498,9 @@ hipError_t launch_batch_level(const BatchTree* trees, const unsigned long long* 
     launch_multi_shape<0>(shape, trees, items, n_items, sd, out.depth != nullptr, s, t0, t1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finish_multi, dim3((unsigned)n_items), dim3(kThreads), 0, s, trees, items, sd, out);
+    const int32_t parts = finish_parts(sd, n_items, n_mitems > 0);
+    hipLaunchKernelGGL(k_finish_multi, dim3((unsigned)(n_items * parts)), dim3(kThreads), 0, s, trees, items, sd, out,
+                       parts);
     e = hipGetLastError();
     if (e != hipSuccess || n_mitems <= 0) return e;
     const int32_t bricks = build_bricks(mask_bricks, n_mitems, kShapes[shape].bricks);

@@ -103,3 +103,28 @@ def test_hits_at_parameter_zero(mg, seed):
     assert 0 < int(np.signbit(ref["D"][zeros]).sum()) < int(zeros.sum())
     assert_same(gpu_eval_tree(mg, m, tree, sensor), ref)
     assert_same(gpu_eval_tree(mg, m, tree, sensor, mode="batch"), ref)
+
+
+@pytest.mark.parametrize("n_az, n_el, bins, wide, copies", [(512, 61, 256, 127, 1), (512, 61, 256, 127, 300),
+                                                           (512, 61, 256, 1, 700), (432, 33, 144, 70, 40), (3, 1, 3, 1, 5),
+                                                           (270, 5, 45, 22, 2)])
+def test_window_selection_by_several_workgroups(mg, n_az, n_el, bins, wide, copies):
+    """The most bins, windows of one bin and of almost half of them, one tile and 1024 of them, whole and
+    partial ones, selected by 4, 3 and 1 workgroups a node: a child of each of `copies` nodes sees what
+    its parent's mask, built from the tiles, leaves it."""
+    from oracle import mgref
+    rng = np.random.Generator(np.random.PCG64(bins + copies))
+    dims = (61, 66, 40)
+    m = W.Map(states=_blocks(rng, dims), voxel_m=1.0, origin_m=np.zeros(3, np.float32))
+    n = 1 + 2 * copies
+    pos = (rng.uniform(0.0, 1.0, (n, 3)) * (np.array(dims) - 0.01)).astype(np.float32)
+    pos[1 + copies:] = pos[1:1 + copies] + np.float32(0.25)
+    pos = np.minimum(pos, np.array(dims, np.float32) - np.float32(0.01))
+    par = np.array([-1] + [0] * copies + list(range(1, 1 + copies)), np.int32)
+    tree = W.Tree(pos_m=pos, parent=par)
+    sensor = W.Sensor(n_az=n_az, n_el=n_el, fov_h_deg=360.0 * wide / bins, fov_v_deg=60.0, range_m=12.0, yaw_bins=bins,
+                      az_offset_deg=1.0)
+    log(f"[select] {n_az}x{n_el}, {bins} bins, {copies} nodes")
+    ref = mgref.eval_tree(m, tree, sensor, n_threads=threads())
+    assert_same(gpu_eval_tree(mg, m, tree, sensor, mode="both"), ref, keys=("g_db", "k_db", "D", "g_abs", "k_abs"))
+    assert_same(gpu_eval_tree(mg, m, tree, sensor, mode="batch"), ref)
