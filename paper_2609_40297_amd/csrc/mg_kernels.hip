@@ -142,6 +142,7 @@ constexpr int kMaxBuildBricks = 1024;
 // the builder's fixed LDS beside its tables: a flag byte, a code word and a brick index per slot, and a word
 constexpr size_t kBuildFixedLds = (size_t)kMaxBuildBricks * 9u + 16u;
 constexpr int kBuildThreads = 256;
+constexpr int kFewThreads = 512, kFewLanes = 8;   // of a launch of few workgroups (few_chunks)
 
 struct TableLDS {
     float2* bv;
@@ -188,9 +189,12 @@ __device__ __forceinline__ void load_tables(const TableLDS& L, const SensorDev& 
 // kViewSome (the node is within a voxel of the box horizontally, the rectangle
 // covers more than 64 tiles, or the voxels must be tested one by one).
 // tm: the node's tile maxima, then its tile minima.
+// `kLanes` neighbouring lanes (a power of two) hold the same brick and share its
+// tiles; lane g is one of them.
 enum : int { kViewNone = 0, kViewSome = 1, kViewAll = 2 };
+template <int kLanes>
 __device__ int brick_view(const SensorDev& S, const float* __restrict__ tm, float4 q, int32_t c0, uint32_t bx,
-                          uint32_t by, uint32_t bz) {
+                          uint32_t by, uint32_t bz, int32_t g) {
     const float x0 = (float)(bx * 8u) + 0.5f - q.x, x1 = x0 + 7.f;
     const float y0 = (float)(by * 8u) + 0.5f - q.y, y1 = y0 + 7.f;
     const float z0 = (float)(bz * 8u) + 0.5f - q.z, z1 = z0 + 7.f;
@@ -222,13 +226,25 @@ __device__ int brick_view(const SensorDev& S, const float* __restrict__ tm, floa
     if (r_hi < 0.f || r_lo > (float)(S.H - 1)) return kViewNone;
     const int32_t j_lo = (int32_t)fmaxf(r_lo, 0.f), j_hi = (int32_t)fminf(r_hi, (float)(S.H - 1));
     const int32_t tc0 = c_lo / kTileCols, tc1 = c_hi / kTileCols, tr0 = j_lo / kTileRows, tr1 = j_hi / kTileRows;
-    if ((tc1 - tc0 + 1) * (tr1 - tr0 + 1) > 64) return kViewSome;
+    const int32_t rows = tr1 - tr0 + 1, tiles = (tc1 - tc0 + 1) * rows;
+    if (tiles > 64) return kViewSome;
     float m = 0.f, mn = __builtin_inff();
-    for (int32_t tc = tc0; tc <= tc1; ++tc)
-        for (int32_t tr = tr0; tr <= tr1; ++tr) {
-            m = fmaxf(m, tm[tc * S.trows + tr]);
-            mn = fminf(mn, tm[S.n_tiles + tc * S.trows + tr]);
+    const float per_row = 1.0f / (float)rows;
+    for (int32_t k = g; k < tiles; k += 4 * kLanes) {
+#pragma unroll
+        for (int32_t e = 0; e < 4; ++e) {                    // four tiles' loads in flight (500 nodes: 921 us one by one, 910)
+            const int32_t t = min(k + e * kLanes, tiles - 1);
+            const int32_t c = (int32_t)(((float)t + 0.5f) * per_row);   // t / rows: t < 64
+            const int32_t at = (tc0 + c) * S.trows + tr0 + (t - c * rows);
+            m = fmaxf(m, tm[at]);
+            mn = fminf(mn, tm[S.n_tiles + at]);
         }
+    }
+#pragma unroll
+    for (int32_t off = 1; off < kLanes; off <<= 1) {
+        m = fmaxf(m, __shfl_xor(m, off, 64));
+        mn = fminf(mn, __shfl_xor(mn, off, 64));
+    }
     const float dmin2 = dx * dx + dy * dy + dz * dz;
     if (!(m * m * 1.0001f + 0.01f >= dmin2)) return kViewNone;
     const bool inside = (fc_lo >= 0.f) & (fc_hi <= (float)(S.WB - 1)) & (r_lo >= 0.f) & (r_hi <= (float)(S.H - 1));
@@ -258,8 +274,9 @@ __device__ int brick_view(const SensorDev& S, const float* __restrict__ tm, floa
 __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
                                            const WindowGeom& A, float4 q, const uint32_t* par, uint32_t* out,
                                            char* smem, const uint8_t* s_live, uint32_t* s_cw, const uint32_t* s_b,
-                                           int32_t cnt);
+                                           int32_t cnt, bool loaded);
 
+template <bool kFew>
 __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
                                             int32_t chunk, int32_t bricks, char* smem, uint8_t* s_live,
                                             uint32_t* s_cw, uint32_t* s_b, int32_t* s_any) {
@@ -286,7 +303,9 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
     const float2 b0 = S.bv[c0], b1 = S.bv[c1];
     A.b0x = b0.x; A.b0y = b0.y; A.b1x = b1.x; A.b1y = b1.y;
     const int32_t cnt = bricks;
+    constexpr int32_t kLanes = kFew ? kFewLanes : 1;         // lanes that share a brick's view
     if (tid == 0) *s_any = 0;
+    if (kFew) load_tables(carve_tables(smem, S), S, c0);
     // The chunk's slots, a block of 2x2x2 bricks per 8 slots: s_b holds each slot's
     // brick (~0 for a slot past the grid's bricks).
     const uint32_t mbx2 = (M.mbx + 1u) >> 1, mby2 = (M.mby + 1u) >> 1;
@@ -300,9 +319,9 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
     // per brick of the chunk (s_live): bit 4 live, bits 2-3 its brick_unk value,
     // bits 0-1 the parent's code (kMaskNone at the root); a slot past the grid's
     // bricks holds no unknown voxel
-    for (int32_t i = tid; i < cnt; i += (int32_t)blockDim.x) {
+    for (int32_t i = tid / kLanes; i < cnt; i += (int32_t)blockDim.x / kLanes) {
         const uint32_t b = s_b[i];
-        if (b == ~0u) {
+        if (b == ~0u) {                                      // (its lanes write the same)
             s_live[i] = (uint8_t)(kBrickKnown << 2);
             continue;
         }
@@ -319,7 +338,8 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
         // (a brick without unknown voxels needs no bits: only unknown voxels' bits
         // are read; nor does one whose voxels an ancestor all observes)
         const int view = (near && wedge && bu != kBrickKnown && pc != kMaskAll)
-                             ? brick_view(S, Tr.tmax + (size_t)slot * 2 * S.n_tiles, q, c0, bx, by, bz)
+                             ? brick_view<kLanes>(S, Tr.tmax + (size_t)slot * 2 * S.n_tiles, q, c0, bx, by, bz,
+                                                  tid & (kLanes - 1))
                              : kViewNone;
         // (a brick whose voxels the node observes all gets every bit set, as the
         // per-voxel test would give it)
@@ -341,7 +361,7 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
         out[wi] = pc == kMaskMixed ? par[wi] : (pc == kMaskAll ? ~0u : 0u);
     }
     uint32_t* code = Tr.mcode + (size_t)slot * nb;
-    if (*s_any) build_live(M, S, Tr, node, A, q, par, out, smem, s_live, s_cw, s_b, cnt);
+    if (*s_any) build_live(M, S, Tr, node, A, q, par, out, smem, s_live, s_cw, s_b, cnt, kFew);
     __syncthreads();
     // Code words of the chunk's bricks that hold an unknown voxel, with the code
     // of their block of 2x2x2 bricks (bits 18-19): uniform when the block's 8
@@ -369,12 +389,14 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
 __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
                                            const WindowGeom& A, float4 q, const uint32_t* par, uint32_t* out,
                                            char* smem, const uint8_t* s_live, uint32_t* s_cw, const uint32_t* s_b,
-                                           int32_t cnt) {
+                                           int32_t cnt, bool loaded) {
     const int32_t tid = threadIdx.x;
     const int32_t c0 = A.c0;
     const TableLDS L = carve_tables(smem, S);
-    load_tables(L, S, c0);
-    __syncthreads();
+    if (!loaded) {
+        load_tables(L, S, c0);
+        __syncthreads();
+    }
     const int32_t lane = tid & 63;
     const float ts0 = L.ts[0], tsH = L.ts[S.H];
     const gfloats_t dnode = as_global(uniform_ptr(Tr.dpan + (size_t)node * S.R));   // the node's panorama
@@ -509,7 +531,8 @@ __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, 
     }
 }
 
-__global__ __launch_bounds__(kBuildThreads) void k_mask_build(MapDev M, SensorDev S, TreeDev Tr,
+template <bool kFew>
+__global__ __launch_bounds__(kFew ? kFewThreads : kBuildThreads) void k_mask_build(MapDev M, SensorDev S, TreeDev Tr,
                                                               const int32_t* __restrict__ nodes, int32_t chunks,
                                                               int32_t bricks) {
     extern __shared__ char smem[];
@@ -517,7 +540,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_mask_build(MapDev M, SensorDe
     __shared__ uint32_t s_cw[kMaxBuildBricks];
     __shared__ uint32_t s_b[kMaxBuildBricks];
     __shared__ int32_t s_any;
-    build_chunk(M, S, Tr, nodes[blockIdx.x / chunks], (int32_t)(blockIdx.x % chunks), bricks, smem, s_live, s_cw, s_b, &s_any);
+    build_chunk<kFew>(M, S, Tr, nodes[blockIdx.x / chunks], (int32_t)(blockIdx.x % chunks), bricks, smem, s_live, s_cw, s_b, &s_any);
 }
 
 // ---------------------------------------------------------------- ray traversal
@@ -939,7 +962,8 @@ __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict
 
 // Path masks of one depth level's nodes with children, all trees at once:
 // `chunks` workgroups per item, `bricks` bricks each.
-__global__ __launch_bounds__(kBuildThreads) void k_mask_build_multi(const BatchTree* __restrict__ trees,
+template <bool kFew>
+__global__ __launch_bounds__(kFew ? kFewThreads : kBuildThreads) void k_mask_build_multi(const BatchTree* __restrict__ trees,
                                                                     const unsigned long long* __restrict__ items,
                                                                     SensorDev S, int32_t chunks, int32_t bricks) {
     extern __shared__ char smem[];
@@ -956,7 +980,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_mask_build_multi(const BatchT
     St.rv2 = BT.rv2;
     const MapDev M = BT.map;
     const TreeDev Tr = BT.td;
-    build_chunk(M, St, Tr, (int32_t)(uint32_t)it, (int32_t)(g % (uint32_t)chunks), bricks, smem, s_live, s_cw, s_b, &s_any);
+    build_chunk<kFew>(M, St, Tr, (int32_t)(uint32_t)it, (int32_t)(g % (uint32_t)chunks), bricks, smem, s_live, s_cw, s_b, &s_any);
 }
 
 // Window selection of one (tree, node) item of a batch: gain, window, the
@@ -1094,7 +1118,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                 St.rv2 = BT.rv2;
                 const MapDev M = BT.map;
                 const TreeDev Tr = BT.td;
-                build_chunk(M, St, Tr, (int32_t)(uint32_t)it, chunk, bricks, smem, s_live, s_u.build.cw, s_u.build.b, &s_any);
+                build_chunk<false>(M, St, Tr, (int32_t)(uint32_t)it, chunk, bricks, smem, s_live, s_u.build.cw, s_u.build.b, &s_any);
             }
             __syncthreads();
         }
@@ -1274,6 +1298,16 @@ static int32_t build_bricks(uint32_t slots, int32_t n_nodes, int32_t most) {
     while (bricks > 8 && (int64_t)n_nodes * ((slots + (uint32_t)bricks - 1u) / (uint32_t)bricks) < kBuildFill) bricks >>= 1;
     return bricks;
 }
+// A launch of chunks of one block of bricks whose workgroups are all resident at
+// once even with a wave per brick (1024 of 8 waves fill the chip): bound by one
+// workgroup's chain of loads, so each brick gets a wave of its own, 8 lanes share
+// a brick's view, and the tables are requested at the start, needed or not. 20
+// nodes in 4 levels (up to 160 workgroups a launch): 86.7 us with four waves,
+// 77.2 us (lanes 16 or 1024 threads: 77.7 and 77.2); 500 nodes, of whose levels
+// one is that small: 910 and 908. Larger launches lose by it: with chunks of up
+// to 16 and 32 bricks in 8 waves the 500 nodes take 954 and 971 us against 920.
+constexpr uint64_t kFewChunks = 1024;
+static bool few_chunks(uint64_t chunks, int32_t bricks) { return bricks == 8 && chunks <= kFewChunks; }
 constexpr int32_t kTreeBuildBricks = 256;     // the most a per-tree level takes
 
 hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
@@ -1283,8 +1317,11 @@ hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev
     const int32_t chunks = (int32_t)((m.build_slots + (uint32_t)bricks - 1u) / (uint32_t)bricks);
     const size_t lds = build_lds_bytes(sd);
     if (lds + kBuildFixedLds > lds_limit()) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_mask_build, dim3((unsigned)n_nodes * (unsigned)chunks), dim3(kBuildThreads), lds, s, m, sd,
-                       td, nodes, chunks, bricks);
+    const dim3 grid((unsigned)n_nodes * (unsigned)chunks);
+    if (few_chunks(grid.x, bricks))
+        hipLaunchKernelGGL(k_mask_build<true>, grid, dim3(kFewThreads), lds, s, m, sd, td, nodes, chunks, bricks);
+    else
+        hipLaunchKernelGGL(k_mask_build<false>, grid, dim3(kBuildThreads), lds, s, m, sd, td, nodes, chunks, bricks);
     return hipGetLastError();
 }
 
@@ -1507,11 +1544,13 @@ hipError_t launch_batch_level(const BatchTree* trees, const unsigned long long* 
     const int32_t chunks = (int32_t)((mask_bricks + (uint32_t)bricks - 1) / (uint32_t)bricks);
     if ((uint64_t)n_mitems * (uint64_t)chunks >= (1ull << 32)) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)n_mitems * (unsigned)chunks);
+    const bool few = few_chunks(grid.x, bricks);
+    const auto kernel = few ? k_mask_build_multi<true> : k_mask_build_multi<false>;
+    const dim3 threads(few ? kFewThreads : kBuildThreads);
     if (b0 && b1)
-        hipExtLaunchKernelGGL(k_mask_build_multi, grid, dim3(kBuildThreads), lds, s, b0, b1, 0u, trees, mitems, sd,
-                              chunks, bricks);
+        hipExtLaunchKernelGGL(kernel, grid, threads, lds, s, b0, b1, 0u, trees, mitems, sd, chunks, bricks);
     else
-        hipLaunchKernelGGL(k_mask_build_multi, grid, dim3(kBuildThreads), lds, s, trees, mitems, sd, chunks, bricks);
+        hipLaunchKernelGGL(kernel, grid, threads, lds, s, trees, mitems, sd, chunks, bricks);
     return hipGetLastError();
 }
 
