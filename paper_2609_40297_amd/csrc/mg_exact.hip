@@ -16,13 +16,14 @@
 //   - the own set is merged with U(parent): its size (A_set), its members
 //     outside U(parent) (X_set), and U(n) with its code words for a node with
 //     children; the own set is cleared for the next node that takes its place.
-// Bounded by the walk of single unknown voxels and the set's scattered atomic
-// ors: each lane gathers the bits of a word before it sends them, without waiting
-// for an answer (looking first whether the word lacks a bit waits for memory:
-// 3.1 ms instead of 2.7 below). Own-yaw gains and then the three counts at their
-// windows, on a 500-node tree (360 x 60 rays, 200 x 200 x 60 grid): 2.7 ms; with
-// hash sets (32-bit ids, open addressing, every ancestor's table probed for every
-// incidence) 16.8 ms.
+// Bounded by the walk of single unknown voxels and by the atomic ors of the sets'
+// words: a lane gathers the bits of a word along its ray, a workgroup those of its
+// 64 rays in LDS (the rays near the node, and neighbours far from it, meet the same
+// words), and small levels give a ray to several lanes. Own-yaw gains and then the
+// three counts at their windows, on a 500-node tree (360 x 60 rays, 200 x 200 x 60
+// grid): 2.66 ms with each lane's words sent to memory (2.62 eight at a time), 2.47
+// with rays split, 2.07 with the words gathered in LDS; 16.8 ms with hash sets
+// (32-bit ids, open addressing, every ancestor's table probed for every incidence).
 #pragma clang fp contract(off)
 #include <hip/hip_runtime.h>
 
@@ -37,49 +38,95 @@ using namespace mgk;
 
 namespace mgx {
 
-constexpr int kSetThreads = 64;              // one wave: a block of kRayBlockCols x kRayBlockRows window rays
+// One wave: a block of kRayBlockCols x kRayBlockRows window rays. Its LDS words: with
+// 2^8, 2^9 and 2^10 of them 2.10, 2.08 and 2.13 ms; four waves that share 2^11: 2.11.
+constexpr int kSetThreads = 64, kSetWordsLog = 9, kSetWords = 1 << kSetWordsLog;
+// Lanes a ray while the launch has at most this many waves: a small level lasts as
+// long as its longest ray's chain of steps. With one lane 2.28 ms; limits of 8192,
+// 16384, 32768, 65536 and 131072 waves: 2.10, 2.11, 2.07, 2.13 and 2.15.
+constexpr int64_t kSetWaves = 32768;
 constexpr int kMergeThreads = 256;           // one thread per brick
 constexpr size_t kPoolBytes = size_t(1) << 30;   // own sets held at once (at least one node's)
 
 // The unknown voxels met by the rays of each listed node's window, set in
 // own[item * mask_words ...] (all clear before). Work item = (node, block of
-// window rays); free blocks are crossed in one step.
+// window rays); free blocks are crossed in one step. kSeg lanes share a ray: each
+// walks the stretch between two parameters, equal parts of the way to the ray's
+// first hit (which the level's trace has stored), the last one to the ray's end.
+// A stretch starts in the voxel that the walk stands in when every boundary with a
+// parameter below its start is crossed; the stretch before sets the same bit.
+template <int kSeg>
 __global__ __launch_bounds__(kSetThreads) void k_exact_set(MapDev M, SensorDev S, TreeDev Tr,
                                                            const int32_t* __restrict__ nodes,
                                                            const int32_t* __restrict__ yaw, int32_t blocks,
                                                            uint32_t* own) {
+    constexpr int32_t kCols = kRayBlockCols / kSeg, kPix = kSetThreads / kSeg;
+    __shared__ uint32_t s_word[kSetWords], s_bits[kSetWords];
+    for (int32_t k = (int32_t)threadIdx.x; k < kSetWords; k += kSetThreads) {
+        s_word[k] = ~0u;
+        s_bits[k] = 0u;
+    }
+    __syncthreads();
     const int32_t item = (int32_t)(blockIdx.x / (uint32_t)blocks), blk = (int32_t)blockIdx.x - item * blocks;
     const int32_t node = nodes[item];
-    const int32_t cb = blk / S.nrb, lane = (int32_t)threadIdx.x;
-    const int32_t i = cb * kRayBlockCols + (lane & (kRayBlockCols - 1));
-    const int32_t j = (blk - cb * S.nrb) * kRayBlockRows + lane / kRayBlockCols;
-    if (i >= S.WB || j >= S.H) return;
-    int32_t c = S.c0_of_win[yaw[node]] + i;
-    c = c >= S.W ? c - S.W : c;
-    const int32_t r = c * S.H + j;
+    const int32_t cb = blk / S.nrb, lane = (int32_t)threadIdx.x, seg = lane / kPix;
+    const int32_t i = cb * kCols + (lane & (kCols - 1));
+    const int32_t j = (blk - cb * S.nrb) * kRayBlockRows + (lane & (kPix - 1)) / kCols;
     uint32_t* mine = own + (size_t)item * M.mask_words;
-    RayWalk w;
-    w.start(Tr.q4[node], S.d4[r], S.iv4[r], M);
-    const int32_t before = (int32_t)__float_as_uint(S.rv) - 1;
-    const float most = __uint_as_float((uint32_t)before);
-    uint32_t word = 0u, bits = 0u;           // bits of one word gathered along the ray
-    uint32_t st = M.bricks[w.addr(M)];
-    while ((st & 2u) == 0u) {                // (occupied, or outside the grid: the ray ends)
-        uint32_t e1 = __builtin_amdgcn_ubfe(kEdgeOfLevel, st & (kLevelMask << kLevelShift), 4u);
-        if (is_unknown(st)) {
-            const uint32_t to = mask_word(w.x(), w.y(), w.z(), M);
-            if (to != word) {
-                if (bits) atomicOr(&mine[word], bits);
-                word = to;
-                bits = 0u;
+    // the bits of a word: into its slot, or to memory where another word holds the slot
+    auto put = [&](uint32_t word, uint32_t bits) {
+        const uint32_t at = (word * 0x9e3779b1u) >> (32 - kSetWordsLog);
+        const uint32_t was = atomicCAS(&s_word[at], ~0u, word);
+        if (was == ~0u || was == word)
+            atomicOr(&s_bits[at], bits);
+        else
+            atomicOr(&mine[word], bits);
+    };
+    auto walk = [&]() {
+        int32_t c = S.c0_of_win[yaw[node]] + i;
+        c = c >= S.W ? c - S.W : c;
+        const int32_t r = c * S.H + j;
+        RayWalk w;
+        w.start(Tr.q4[node], S.d4[r], S.iv4[r], M);
+        float end = S.rv;
+        if (kSeg > 1) {
+            // (a ray of less than a voxel a stretch is left to its first lane)
+            const float h = Tr.dpan[(size_t)node * S.R + r];
+            const bool split = h >= (float)kSeg;
+            if (seg > 0) {
+                if (!split) return;
+                const float most = __uint_as_float(__float_as_uint(h * ((float)seg / (float)kSeg)) - 1u);
+                w.pass(most, most, most, most);
+                if (!w.in_grid(M)) return;
             }
-            bits |= 1u << mask_bit(w.x(), w.y());
-            e1 = 0u;
+            if (split && seg < kSeg - 1) end = h * ((float)(seg + 1) / (float)kSeg);
         }
-        if (!(w.cross(e1, before, most) < S.rv)) break;
-        st = M.bricks[w.addr(M)];
-    }
-    if (bits) atomicOr(&mine[word], bits);
+        const int32_t before = (int32_t)__float_as_uint(end) - 1;
+        const float most = fminf(__uint_as_float((uint32_t)before), end);
+        uint32_t word = 0u, bits = 0u;           // bits of one word gathered along the ray
+        uint32_t st = M.bricks[w.addr(M)];
+        while ((st & 2u) == 0u) {                // (occupied, or outside the grid: the ray ends)
+            uint32_t e1 = __builtin_amdgcn_ubfe(kEdgeOfLevel, st & (kLevelMask << kLevelShift), 4u);
+            if (is_unknown(st)) {
+                const uint32_t to = mask_word(w.x(), w.y(), w.z(), M);
+                if (to != word) {
+                    if (bits) put(word, bits);
+                    word = to;
+                    bits = 0u;
+                }
+                bits |= 1u << mask_bit(w.x(), w.y());
+                e1 = 0u;
+            }
+            if (!(w.cross(e1, before, most) < end)) break;
+            st = M.bricks[w.addr(M)];
+        }
+        if (bits) put(word, bits);
+    };
+    if (i < S.WB && j < S.H) walk();
+    __syncthreads();
+#pragma unroll
+    for (int32_t k = (int32_t)threadIdx.x; k < kSetWords; k += kSetThreads)
+        if (s_word[k] != ~0u) atomicOr(&mine[s_word[k]], s_bits[k]);
 }
 
 // The code word of a brick's 512 bits without its block's code (mg_internal.h).
@@ -220,12 +267,25 @@ int own_sets(State& st, const MapDev& M, const std::vector<int32_t>& level_ptr, 
 hipError_t merge_level(const State& st, const mgb::TreeView& v, const int32_t* nodes, int32_t n, const int32_t* yaw,
                        uint32_t* a_set, uint32_t* x_set, hipStream_t s) {
     const SensorDev& S = *v.sd;
-    const int32_t blocks = (S.WB + kRayBlockCols - 1) / kRayBlockCols * S.nrb;
     const int32_t chunks = (int32_t)((v.map->build_slots + kMergeThreads - 1) / kMergeThreads);
     for (int32_t at = 0; at < n; at += st.nodes) {
         const int32_t cnt = std::min(st.nodes, n - at);
-        hipLaunchKernelGGL(k_exact_set, dim3((unsigned)cnt * (unsigned)blocks), dim3(kSetThreads), 0, s, *v.map, S, *v.td,
-                           nodes + at, yaw, blocks, st.own);
+        const int64_t waves = (int64_t)cnt * ((S.WB + kRayBlockCols - 1) / kRayBlockCols) * S.nrb;
+        int seg = 8;
+        while (seg > 1 && waves * seg > kSetWaves) seg >>= 1;
+        const int32_t cols = kRayBlockCols / seg, blocks = (S.WB + cols - 1) / cols * S.nrb;
+        const dim3 grid((unsigned)cnt * (unsigned)blocks);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(kSetThreads), 0, s, *v.map, S, *v.td, nodes + at, yaw, blocks, st.own);
+        };
+        if (seg == 8)
+            go(k_exact_set<8>);
+        else if (seg == 4)
+            go(k_exact_set<4>);
+        else if (seg == 2)
+            go(k_exact_set<2>);
+        else
+            go(k_exact_set<1>);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_exact_merge, dim3((unsigned)cnt * (unsigned)chunks), dim3(kMergeThreads), 0, s, *v.map,
@@ -283,7 +343,7 @@ extern "C" int mg_eval_exact(mg_tree t, void* hip_stream, const int32_t* yaw_bin
     for (int32_t d = 0; d < v.levels && e == hipSuccess; ++d) {
         const int32_t b = (*v.level_ptr)[d], cnt = (*v.level_ptr)[d + 1] - b;
         const int32_t mb = (*v.mask_level_ptr)[d], mcnt = (*v.mask_level_ptr)[d + 1] - mb;
-        e = launch_trace_window(*v.map, S, Tr, Tr.level_nodes + b, cnt, yaw_bin, x_ray, s);
+        e = launch_trace_window(*v.map, S, Tr, Tr.level_nodes + b, cnt, yaw_bin, x_ray, sets, s);
         if (e == hipSuccess)
             e = sets ? merge_level(st, v, Tr.level_nodes + b, cnt, yaw_bin, a_set, x_set, s)
                      : merge_level(st, v, Tr.mask_nodes + mb, mcnt, yaw_bin, nullptr, nullptr, s);

@@ -338,9 +338,10 @@ hipError_t launch_blocks16(const MapDev& m, hipStream_t s);
 hipError_t launch_trace(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
                         int32_t n_nodes, bool marginal, bool depth, hipStream_t s);   // depth: keep every node's first hits
 // Unknown voxels met by the rays of each listed node's window yaw[node] and not
-// in its parent's path mask, added to total[node].
+// in its parent's path mask, added to total[node]. The window's first hits are kept
+// for nodes with children, with `hits` for every node.
 hipError_t launch_trace_window(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
-                               int32_t n_nodes, const int32_t* yaw, uint32_t* total, hipStream_t s);
+                               int32_t n_nodes, const int32_t* yaw, uint32_t* total, bool hits, hipStream_t s);
 // Path masks of the listed nodes (all with children), after their windows are chosen.
 hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
                              int32_t n_nodes, hipStream_t s);

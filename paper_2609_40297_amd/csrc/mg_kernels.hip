@@ -796,11 +796,11 @@ template <int kSeg>
 __global__ __launch_bounds__(kTreeTraceThreads) void k_trace_window(MapDev M, SensorDev S, TreeDev Tr,
                                                                     const int32_t* __restrict__ nodes,
                                                                     const int32_t* __restrict__ yaw,
-                                                                    uint32_t* __restrict__ total) {
+                                                                    uint32_t* __restrict__ total, bool hits) {
     const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x / (uint32_t)S.T));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
     const int32_t node = nodes[item];
-    trace_tile<true, kTreeTraceThreads, kSeg, true>(M, S, Tr, node, tile, false, S.c0_of_win[yaw[node]], total + node);
+    trace_tile<true, kTreeTraceThreads, kSeg, true>(M, S, Tr, node, tile, hits || Tr.mask_slot[node] >= 0, S.c0_of_win[yaw[node]], total + node);
 }
 
 // ---------------------------------------------------------------- window selection
@@ -1267,12 +1267,13 @@ hipError_t launch_trace(const MapDev& m, const SensorDev& sd, const TreeDev& td,
 }
 
 hipError_t launch_trace_window(const MapDev& m, const SensorDev& sd, const TreeDev& td, const int32_t* nodes,
-                               int32_t n_nodes, const int32_t* yaw, uint32_t* total, hipStream_t s) {
+                               int32_t n_nodes, const int32_t* yaw, uint32_t* total, bool hits,
+                               hipStream_t s) {
     if (n_nodes <= 0) return hipSuccess;
     const int seg = trace_segments(sd, n_nodes, sd.WB);
     const SensorDev st = trace_sensor(sd, seg, kTreeTraceThreads, sd.WB);
     const dim3 grid((unsigned)n_nodes * (unsigned)st.T);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes, yaw, total); };
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kTreeTraceThreads), 0, s, m, st, td, nodes, yaw, total, hits); };
     if (seg == 8)
         go(k_trace_window<8>);
     else if (seg == 4)

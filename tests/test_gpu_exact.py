@@ -170,3 +170,22 @@ def test_exact_levels_wider_than_the_set_pool(mg, orc, fan, deep):
     pos[::3] = np.floor(pos[::3])
     sen = W.Sensor(n_az=48, n_el=9, fov_h_deg=90.0, fov_v_deg=60.0, range_m=70.0, yaw_bins=12)
     _check(mg, orc, m, W.Tree(pos_m=pos, parent=par), sen, f"wide level {fan}")
+
+
+@pytest.mark.parametrize("fan, range_vox", [(1, 64.0), (60, 40.0), (150, 40.0), (300, 40.0), (480, 40.0), (3, 7.5), (3, 0.25)])
+def test_exact_sets_of_split_rays(mg, orc, fan, range_vox):
+    """Levels whose sets are walked by 8, 8, 4, 2 and 1 lanes a ray: rays that end at a hit, at the range and
+    at the grid's faces, nodes on voxel corners, more words than a wave's slots hold, and ranges of less
+    than a voxel per lane."""
+    rng = np.random.Generator(np.random.PCG64(fan))
+    dims = (72, 66, 51)
+    st = np.zeros(dims[::-1], np.uint8)
+    st[12:40, 16:48, 8:56] = W.FREE
+    st[rng.integers(0, 51, 3000), rng.integers(0, 66, 3000), rng.integers(0, 72, 3000)] = W.FREE
+    st[rng.integers(0, 51, 40), rng.integers(0, 66, 40), rng.integers(0, 72, 40)] = W.OCC
+    m = W.Map(states=st, voxel_m=1.0, origin_m=np.zeros(3, np.float32))
+    pos = rng.uniform([0, 0, 0], [71.9, 65.9, 50.9], (2 + fan, 3)).astype(np.float32)
+    pos[::3] = np.floor(pos[::3])
+    par = np.array([-1] + [0] * fan + [1], np.int32)
+    sen = W.Sensor(n_az=216, n_el=33, fov_h_deg=90.0, fov_v_deg=60.0, range_m=range_vox, yaw_bins=8, az_offset_deg=-(5.0 / 6.0))
+    _check(mg, orc, m, W.Tree(pos_m=pos, parent=par), sen, f"split sets {fan}")
