@@ -791,7 +791,7 @@ int prepare_tree(mg_map map, const float* pos_m, const int32_t* parent, int32_t 
     H->o_ai = take(sizeof(int32_t) * H->anc_ids.size());
     H->o_ln = take(sizeof(int32_t) * n);
     H->o_c0 = take(sizeof(int32_t) * n);
-    H->o_ms = take(sizeof(int32_t) * n);
+    H->o_ms = take(sizeof(int2) * n);
     H->o_mn = take(sizeof(int32_t) * std::max<size_t>(H->mask_nodes.size(), 1));
     H->up_bytes = off;
     H->o_g = take(sizeof(uint32_t) * n);
@@ -825,7 +825,8 @@ int finish_upload(mg_map map, const mgb::HostTree& H, const mg_sensor* sensor, h
     put(H.o_ap, H.anc_ptr.data(), sizeof(int32_t) * (n + 1));
     put(H.o_ai, H.anc_ids.data(), sizeof(int32_t) * H.anc_ids.size());
     put(H.o_ln, H.level_nodes.data(), sizeof(int32_t) * n);
-    put(H.o_ms, H.mask_slot.data(), sizeof(int32_t) * n);
+    int2* slots = (int2*)(host.data() + H.o_ms);
+    for (int32_t i = 0; i < n; ++i) slots[i] = make_int2(H.mask_slot[i], H.parent[i] >= 0 ? H.mask_slot[H.parent[i]] : -1);
     put(H.o_mn, H.mask_nodes.data(), sizeof(int32_t) * H.mask_nodes.size());
     hipError_t e = hipMemcpyAsync(base, host.data(), H.up_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -843,7 +844,7 @@ int finish_upload(mg_map map, const mgb::HostTree& H, const mg_sensor* sensor, h
     t->dev.c0 = (int32_t*)(base + H.o_c0);
     t->dev.bins = (uint32_t*)(base + H.o_bins);
     t->dev.dpan = (float*)(base + H.o_dpan);
-    t->dev.mask_slot = (const int32_t*)(base + H.o_ms);
+    t->dev.mask_slot = (const int2*)(base + H.o_ms);
     t->dev.mask_nodes = (const int32_t*)(base + H.o_mn);
     t->dev.masks = (uint32_t*)(base + H.o_masks);
     t->dev.tmax = (float*)(base + H.o_tm);

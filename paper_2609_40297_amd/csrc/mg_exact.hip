@@ -161,9 +161,10 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
                                                                uint32_t* __restrict__ x_set) {
     const int32_t item = (int32_t)(blockIdx.x / (uint32_t)chunks);
     const uint32_t sl = (blockIdx.x - (uint32_t)item * (uint32_t)chunks) * kMergeThreads + threadIdx.x;
-    const int32_t node = nodes[item], slot = Tr.mask_slot[node], a0 = Tr.anc_ptr[node];
+    const int32_t node = nodes[item];
+    const int2 slots = Tr.mask_slot[node];
+    const int32_t slot = slots.x, ps = slots.y;      // (the parent's union)
     const uint32_t nb = M.mask_words >> 4;
-    const int32_t ps = Tr.anc_ptr[node + 1] > a0 ? Tr.mask_slot[Tr.anc_ids[a0]] : -1;     // the parent's union
     const uint32_t mbx2 = (M.mbx + 1u) >> 1, mby2 = (M.mby + 1u) >> 1, blk = sl >> 3, j = sl & 7u;
     const uint32_t bx = 2u * (blk % mbx2) + (j & 1u), by = 2u * ((blk / mbx2) % mby2) + ((j >> 1) & 1u),
                    bz = 2u * (blk / (mbx2 * mby2)) + (j >> 2);

@@ -272,7 +272,7 @@ struct SensorDev {
 // One tree's device state. Depth buffers are kept as full panoramas: the
 // first-hit parameter of every ray of node n lives at dpan[n*R + r] and the
 // node's buffer is the window slice starting at column c0[n]. Every node with
-// children has a path mask (mask_slot[n] >= 0): the set of voxels that n or
+// children has a path mask (mask_slot[n].x >= 0): the set of voxels that n or
 // one of its ancestors observes (with anc_cap = 1: that n observes), which is
 // what conditions n's children.
 struct TreeDev {
@@ -287,7 +287,7 @@ struct TreeDev {
     float* dpan;               // [n][R]
     int32_t* c0;               // [n]
     uint32_t* masks;           // [nodes with children][mask_words]
-    const int32_t* mask_slot;  // [n] index into masks, -1 for a leaf
+    const int2* mask_slot;     // [n] index into masks: the node's (-1 for a leaf) and its parent's (-1 for the root)
     const int32_t* mask_nodes; // nodes with children, by depth level
     float* tmax;               // [nodes with children][2][n_tiles]: largest, then smallest first hit of each tile of the window
     uint32_t* mcode;           // [nodes with children][mask bricks]: code words

@@ -281,16 +281,15 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
                                             int32_t chunk, int32_t bricks, char* smem, uint8_t* s_live,
                                             uint32_t* s_cw, uint32_t* s_b, int32_t* s_any) {
     const int32_t tid = threadIdx.x;
-    const int32_t slot = Tr.mask_slot[node];
+    const int2 slots = Tr.mask_slot[node];
+    const int32_t slot = slots.x, ps = slots.y;
     const uint32_t nb = M.mask_words >> 4;
     const uint32_t lo = (uint32_t)chunk * (uint32_t)bricks;  // first build slot (bricks is a multiple of 8)
     if (slot < 0 || lo >= M.build_slots) return;             // a leaf (nothing reads its mask), or past the map
     uint32_t* out = Tr.masks + (size_t)slot * M.mask_words;
-    const int32_t a0 = Tr.anc_ptr[node];
     const uint32_t* par = nullptr;
     const uint32_t* pcode = nullptr;
-    if (Tr.anc_cap > 1 && Tr.anc_ptr[node + 1] > a0) {
-        const int32_t ps = Tr.mask_slot[Tr.anc_ids[a0]];
+    if (Tr.anc_cap > 1 && ps >= 0) {
         par = Tr.masks + (size_t)ps * M.mask_words;
         pcode = Tr.mcode + (size_t)ps * nb;
     }
@@ -635,9 +634,8 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     const uint32_t* pmask = nullptr;     // the parent's path mask
     const uint32_t* pcode = nullptr;     // and its bricks' code words
     if (kMarginal) {
-        const int32_t a0 = Tr.anc_ptr[node];
-        if (Tr.anc_cap > 0 && Tr.anc_ptr[node + 1] > a0) {
-            const int32_t ps = Tr.mask_slot[Tr.anc_ids[a0]];
+        const int32_t ps = Tr.mask_slot[node].y;
+        if (Tr.anc_cap > 0 && ps >= 0) {
             pmask = Tr.masks + (size_t)ps * M.mask_words;
             pcode = Tr.mcode + (size_t)ps * (M.mask_words >> 4);
         }
@@ -788,7 +786,7 @@ __global__ __launch_bounds__(kTreeTraceThreads) void k_trace(MapDev M, SensorDev
     const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x / (uint32_t)S.T));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
     const int32_t node = nodes[item];
-    trace_tile<kMarginal, kTreeTraceThreads, kSeg>(M, S, Tr, node, tile, depth || Tr.mask_slot[node] >= 0);
+    trace_tile<kMarginal, kTreeTraceThreads, kSeg>(M, S, Tr, node, tile, depth || Tr.mask_slot[node].x >= 0);
 }
 
 // The rays of each node's window yaw[node], counted into total[node].
@@ -800,7 +798,7 @@ __global__ __launch_bounds__(kTreeTraceThreads) void k_trace_window(MapDev M, Se
     const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x / (uint32_t)S.T));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
     const int32_t node = nodes[item];
-    trace_tile<true, kTreeTraceThreads, kSeg, true>(M, S, Tr, node, tile, hits || Tr.mask_slot[node] >= 0, S.c0_of_win[yaw[node]], total + node);
+    trace_tile<true, kTreeTraceThreads, kSeg, true>(M, S, Tr, node, tile, hits || Tr.mask_slot[node].x >= 0, S.c0_of_win[yaw[node]], total + node);
 }
 
 // ---------------------------------------------------------------- window selection
@@ -906,7 +904,7 @@ __global__ __launch_bounds__(kThreads) void k_finish(SensorDev S, TreeDev Tr, co
     __shared__ FinishLds s;
     const int32_t item = (int32_t)(blockIdx.x / (uint32_t)parts), part = (int32_t)blockIdx.x - item * parts;
     const int32_t node = nodes[item];
-    const int32_t slot = marginal ? Tr.mask_slot[node] : -1;
+    const int32_t slot = marginal ? Tr.mask_slot[node].x : -1;
     int32_t c0;
     const unsigned long long best = select_window(Tr.bins + (size_t)node * S.B, S, s, &c0);
     if (threadIdx.x == 0 && part == 0) {
@@ -957,7 +955,7 @@ __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict
     const MapDev M = BT.map;     // copies: loaded once, not re-read through the descriptor
     const TreeDev Tr = BT.td;
     const int32_t node = (int32_t)(uint32_t)it;
-    trace_tile<true, kTh, kSeg>(M, St, Tr, node, tile, depth || Tr.mask_slot[node] >= 0);
+    trace_tile<true, kTh, kSeg>(M, St, Tr, node, tile, depth || Tr.mask_slot[node].x >= 0);
 }
 
 // Path masks of one depth level's nodes with children, all trees at once:
@@ -992,7 +990,7 @@ __device__ __forceinline__ void finish_item(const BatchTree* __restrict__ trees,
     const BatchTree& BT = trees[(uint32_t)(it >> 32)];
     if (BT.status != nullptr && *BT.status != 0) return;      // (the request has failed)
     const int32_t node = (int32_t)(uint32_t)it;
-    const int32_t slot = BT.td.mask_slot[node];
+    const int32_t slot = BT.td.mask_slot[node].x;
     int32_t c0;
     const unsigned long long best = select_window(BT.td.bins + (size_t)node * S.B, S, s, &c0);
     if (threadIdx.x == 0 && part == 0) {
@@ -1096,7 +1094,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                 const MapDev M = BT.map;
                 const TreeDev Tr = BT.td;
                 const int32_t node = (int32_t)(uint32_t)it;
-                trace_tile<true, kThreads>(M, St, Tr, node, tile, out.depth != nullptr || Tr.mask_slot[node] >= 0);
+                trace_tile<true, kThreads>(M, St, Tr, node, tile, out.depth != nullptr || Tr.mask_slot[node].x >= 0);
             }
         }
         if (!grid_barrier(sync, &target, spin_limit, &s_ok)) return;
