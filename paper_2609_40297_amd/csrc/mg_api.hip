@@ -314,6 +314,8 @@ SensorDev sensor_dev(const SensorRes* r, float rv) {
     sd.nrb = (T.H + kRayBlockRows - 1) / kRayBlockRows;
     sd.n_blocks = (T.W + kRayBlockCols - 1) / kRayBlockCols * sd.nrb;
     sd.T = (sd.n_blocks * 64 + kThreads - 1) / kThreads;
+    sd.T_mul = divisor_mul((uint32_t)sd.T);
+    sd.nrb_mul = divisor_mul((uint32_t)sd.nrb);
     sd.tcols = (T.WB + kTileCols - 1) / kTileCols;
     sd.trows = (T.H + kTileRows - 1) / kTileRows;
     sd.n_tiles = sd.tcols * sd.trows;
@@ -514,7 +516,9 @@ int map_alloc(int32_t nx, int32_t ny, int32_t nz, float voxel_m, const float ori
     m->dev.mby = (uint32_t)(ny + 7) / 8u;
     m->dev.mbz = (uint32_t)(nz + 7) / 8u;
     m->dev.mask_words = 16u * m->dev.mbx * m->dev.mby * m->dev.mbz;    // < 2^32 / 32 (voxels < 2^32)
-    m->dev.build_slots = 8u * ((m->dev.mbx + 1u) / 2u) * ((m->dev.mby + 1u) / 2u) * ((m->dev.mbz + 1u) / 2u);
+    m->dev.mbx2 = (m->dev.mbx + 1u) / 2u; m->dev.mby2 = (m->dev.mby + 1u) / 2u;
+    m->dev.mbx2_mul = divisor_mul(m->dev.mbx2); m->dev.mby2_mul = divisor_mul(m->dev.mby2);
+    m->dev.build_slots = 8u * m->dev.mbx2 * m->dev.mby2 * ((m->dev.mbz + 1u) / 2u);
     m->dev.brick_unk = m->bricks + padded;
     m->voxel_m = voxel_m;
     for (int a = 0; a < 3; ++a) m->origin[a] = origin_m[a];

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kSetThreads) void k_exact_set(MapDev M, SensorDev S
     __syncthreads();
     const int32_t item = (int32_t)(blockIdx.x / (uint32_t)blocks), blk = (int32_t)blockIdx.x - item * blocks;
     const int32_t node = nodes[item];
-    const int32_t cb = blk / S.nrb, lane = (int32_t)threadIdx.x, seg = lane / kPix;
+    const int32_t cb = (int32_t)divide((uint32_t)blk, (uint32_t)S.nrb, S.nrb_mul), lane = (int32_t)threadIdx.x, seg = lane / kPix;
     const int32_t i = cb * kCols + (lane & (kCols - 1));
     const int32_t j = (blk - cb * S.nrb) * kRayBlockRows + (lane & (kPix - 1)) / kCols;
     uint32_t* mine = own + (size_t)item * M.mask_words;
@@ -165,9 +165,8 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
     const int2 slots = Tr.mask_slot[node];
     const int32_t slot = slots.x, ps = slots.y;      // (the parent's union)
     const uint32_t nb = M.mask_words >> 4;
-    const uint32_t mbx2 = (M.mbx + 1u) >> 1, mby2 = (M.mby + 1u) >> 1, blk = sl >> 3, j = sl & 7u;
-    const uint32_t bx = 2u * (blk % mbx2) + (j & 1u), by = 2u * ((blk / mbx2) % mby2) + ((j >> 1) & 1u),
-                   bz = 2u * (blk / (mbx2 * mby2)) + (j >> 2);
+    const uint3 at = slot_brick(sl, M);
+    const uint32_t bx = at.x, by = at.y, bz = at.z;
     const bool in_map = bx < M.mbx && by < M.mby && bz < M.mbz;
     const uint32_t b = in_map ? bx + M.mbx * (by + M.mby * bz) : 0u;
     const uint32_t bu = in_map ? (M.brick_unk[b] & 3u) : (uint32_t)kBrickKnown;

@@ -109,6 +109,14 @@ __device__ __forceinline__ uint8_t brick_summary(bool any_unk, bool all_unk, boo
 // least one padding voxel past the grid on every axis, so a voxel's byte
 // address is a bit-field merge of its coordinates; coordinate -1 wraps to the
 // last padding voxel of its axis, which holds kOutside like all padding.
+// Division by a count that the host knows, exact for every n: `mul` falls short of
+// 2^32 / d by less than 1, so the product's high word is the quotient or one less.
+inline uint32_t divisor_mul(uint32_t d) { return d > 1u ? (uint32_t)((1ull << 32) / d) : ~0u; }
+__device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint32_t mul) {
+    const uint32_t q = __umulhi(n, mul);
+    return q + (n - q * d >= d ? 1u : 0u);
+}
+
 struct MapDev {
     const uint8_t* bricks;
     int32_t nx, ny, nz;     // true extent in voxels
@@ -123,6 +131,7 @@ struct MapDev {
     // The mask builder visits bricks by blocks of 2x2x2 (ceil(mb / 2) blocks per
     // axis, x fastest; in a block x, then y, then z): slots = 8 * blocks.
     uint32_t build_slots;
+    uint32_t mbx2, mby2, mbx2_mul, mby2_mul;   // blocks along x and y, and their divisor_mul
     // [mbx * mby * mbz] per mask brick: kBrickKnown, kBrickSomeUnknown or
     // kBrickAllUnknown, with kBrickAllFree (kept current, with the block
     // marks, by every write of the map's states)
@@ -150,6 +159,13 @@ __device__ __forceinline__ uint32_t mask_word(int32_t x, int32_t y, int32_t z, c
 __device__ __forceinline__ uint32_t mask_bit(int32_t x, int32_t y) { return (uint32_t)(x & 7) | ((uint32_t)(y & 3) << 3); }
 __device__ __forceinline__ uint32_t mask_brick(int32_t x, int32_t y, int32_t z, const MapDev& M) {
     return (uint32_t)(x >> 3) + __umul24(M.mbx, (uint32_t)(y >> 3) + __umul24(M.mby, (uint32_t)(z >> 3)));
+}
+
+// The mask brick of build slot `sl` (past the grid's bricks in a partial block).
+__device__ __forceinline__ uint3 slot_brick(uint32_t sl, const MapDev& M) {
+    const uint32_t blk = sl >> 3, row = divide(blk, M.mbx2, M.mbx2_mul), bz = divide(row, M.mby2, M.mby2_mul);
+    return make_uint3(2u * (blk - row * M.mbx2) + (sl & 1u), 2u * (row - bz * M.mby2) + ((sl >> 1) & 1u),
+                      2u * bz + ((sl >> 2) & 1u));
 }
 
 // A ray walked by the Amanatides-Woo 3D DDA (face-crossing parameters recomputed
@@ -249,6 +265,7 @@ struct SensorDev {
     // at similar steps); blocks are numbered row block fastest.
     int32_t nrb;               // row blocks, ceil(H / kRayBlockRows)
     int32_t n_blocks;          // ceil(W / kRayBlockCols) * nrb
+    uint32_t T_mul, nrb_mul;   // divisor_mul of T and nrb
     // Depth cull of the path-mask builder: a window's pixels in tiles of
     // kTileCols x kTileRows (tcols x trows tiles, column-major), and float
     // angles that place a direction's pixel to within a pixel: azimuth of

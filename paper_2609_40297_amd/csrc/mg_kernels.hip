@@ -274,7 +274,7 @@ __device__ int brick_view(const SensorDev& S, const float* __restrict__ tm, floa
 __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
                                            const WindowGeom& A, float4 q, const uint32_t* par, uint32_t* out,
                                            char* smem, const uint8_t* s_live, uint32_t* s_cw, const uint32_t* s_b,
-                                           int32_t cnt, bool loaded);
+                                           uint32_t lo, int32_t cnt, bool loaded);
 
 template <bool kFew>
 __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
@@ -307,11 +307,9 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
     if (kFew) load_tables(carve_tables(smem, S), S, c0);
     // The chunk's slots, a block of 2x2x2 bricks per 8 slots: s_b holds each slot's
     // brick (~0 for a slot past the grid's bricks).
-    const uint32_t mbx2 = (M.mbx + 1u) >> 1, mby2 = (M.mby + 1u) >> 1;
     for (int32_t i = tid; i < cnt; i += (int32_t)blockDim.x) {
-        const uint32_t sl = lo + (uint32_t)i, blk = sl >> 3, j = sl & 7u;
-        const uint32_t bx = 2u * (blk % mbx2) + (j & 1u), by = 2u * ((blk / mbx2) % mby2) + ((j >> 1) & 1u),
-                       bz = 2u * (blk / (mbx2 * mby2)) + (j >> 2);
+        const uint3 at = slot_brick(lo + (uint32_t)i, M);
+        const uint32_t bx = at.x, by = at.y, bz = at.z;
         s_b[i] = (bx < M.mbx && by < M.mby && bz < M.mbz) ? bx + M.mbx * (by + M.mby * bz) : ~0u;
     }
     __syncthreads();
@@ -324,7 +322,8 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
             s_live[i] = (uint8_t)(kBrickKnown << 2);
             continue;
         }
-        const uint32_t bx = b % M.mbx, by = (b / M.mbx) % M.mby, bz = b / (M.mbx * M.mby);
+        const uint3 at = slot_brick(lo + (uint32_t)i, M);
+        const uint32_t bx = at.x, by = at.y, bz = at.z;
         const float rx = (float)(bx * 8u) + 4.0f - q.x, ry = (float)(by * 8u) + 4.0f - q.y,
                     rz = (float)(bz * 8u) + 4.0f - q.z;
         const float reach = S.rv + 6.6f;                     // 3.5 sqrt(3) = 6.06, plus rounding
@@ -360,7 +359,7 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
         out[wi] = pc == kMaskMixed ? par[wi] : (pc == kMaskAll ? ~0u : 0u);
     }
     uint32_t* code = Tr.mcode + (size_t)slot * nb;
-    if (*s_any) build_live(M, S, Tr, node, A, q, par, out, smem, s_live, s_cw, s_b, cnt, kFew);
+    if (*s_any) build_live(M, S, Tr, node, A, q, par, out, smem, s_live, s_cw, s_b, lo, cnt, kFew);
     __syncthreads();
     // Code words of the chunk's bricks that hold an unknown voxel, with the code
     // of their block of 2x2x2 bricks (bits 18-19): uniform when the block's 8
@@ -388,7 +387,7 @@ __device__ __forceinline__ void build_chunk(const MapDev& M, const SensorDev& S,
 __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,
                                            const WindowGeom& A, float4 q, const uint32_t* par, uint32_t* out,
                                            char* smem, const uint8_t* s_live, uint32_t* s_cw, const uint32_t* s_b,
-                                           int32_t cnt, bool loaded) {
+                                           uint32_t lo, int32_t cnt, bool loaded) {
     const int32_t tid = threadIdx.x;
     const int32_t c0 = A.c0;
     const TableLDS L = carve_tables(smem, S);
@@ -405,7 +404,8 @@ __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, 
         const uint32_t f = s_live[i];
         if (!(f & 16u)) continue;
         const uint32_t b = s_b[i];
-        const int32_t bx = (int32_t)(b % M.mbx), by = (int32_t)((b / M.mbx) % M.mby), bz = (int32_t)(b / (M.mbx * M.mby));
+        const uint3 at = slot_brick(lo + (uint32_t)i, M);
+        const int32_t bx = (int32_t)at.x, by = (int32_t)at.y, bz = (int32_t)at.z;
         const int32_t x = bx * 8 + (lane & 7), y = by * 8 + (lane >> 3);
         const float cx = (float)x + 0.5f, cy = (float)y + 0.5f;
         const uint32_t wbase = b << 4;
@@ -533,13 +533,15 @@ __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, 
 template <bool kFew>
 __global__ __launch_bounds__(kFew ? kFewThreads : kBuildThreads) void k_mask_build(MapDev M, SensorDev S, TreeDev Tr,
                                                               const int32_t* __restrict__ nodes, int32_t chunks,
-                                                              int32_t bricks) {
+                                                              int32_t bricks, uint32_t chunks_mul) {
     extern __shared__ char smem[];
     __shared__ uint8_t s_live[kMaxBuildBricks];
     __shared__ uint32_t s_cw[kMaxBuildBricks];
     __shared__ uint32_t s_b[kMaxBuildBricks];
     __shared__ int32_t s_any;
-    build_chunk<kFew>(M, S, Tr, nodes[blockIdx.x / chunks], (int32_t)(blockIdx.x % chunks), bricks, smem, s_live, s_cw, s_b, &s_any);
+    const uint32_t item = divide(blockIdx.x, (uint32_t)chunks, chunks_mul);
+    build_chunk<kFew>(M, S, Tr, nodes[item], (int32_t)(blockIdx.x - item * (uint32_t)chunks), bricks, smem, s_live, s_cw,
+                      s_b, &s_any);
 }
 
 // ---------------------------------------------------------------- ray traversal
@@ -644,7 +646,7 @@ __device__ __forceinline__ void trace_tile(const MapDev& M, const SensorDev& S, 
     const gwords_t pc = as_global(uniform_ptr(pcode));
     // this wave's pixel block and this lane's pixel in it (column c, row j)
     const int32_t blk = __builtin_amdgcn_readfirstlane(tile * (kTh / 64) + (tid >> 6));
-    const int32_t cb = __builtin_amdgcn_readfirstlane(blk / S.nrb);
+    const int32_t cb = __builtin_amdgcn_readfirstlane((int32_t)divide((uint32_t)blk, (uint32_t)S.nrb, S.nrb_mul));
     constexpr int32_t kCols = kRayBlockCols / kSeg, kPix = 64 / kSeg;
     const int32_t seg = (tid & 63) / kPix;               // this lane's stretch of its ray
     const int32_t i = cb * kCols + (tid & (kCols - 1));
@@ -783,7 +785,7 @@ template <bool kMarginal, int kSeg>
 __global__ __launch_bounds__(kTreeTraceThreads) void k_trace(MapDev M, SensorDev S, TreeDev Tr,
                                                              const int32_t* __restrict__ nodes, bool depth) {
     // (workgroup-uniform values kept in scalar registers)
-    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x / (uint32_t)S.T));
+    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(blockIdx.x, (uint32_t)S.T, S.T_mul));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
     const int32_t node = nodes[item];
     trace_tile<kMarginal, kTreeTraceThreads, kSeg>(M, S, Tr, node, tile, depth || Tr.mask_slot[node].x >= 0);
@@ -795,7 +797,7 @@ __global__ __launch_bounds__(kTreeTraceThreads) void k_trace_window(MapDev M, Se
                                                                     const int32_t* __restrict__ nodes,
                                                                     const int32_t* __restrict__ yaw,
                                                                     uint32_t* __restrict__ total, bool hits) {
-    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(blockIdx.x / (uint32_t)S.T));
+    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(blockIdx.x, (uint32_t)S.T, S.T_mul));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
     const int32_t node = nodes[item];
     trace_tile<true, kTreeTraceThreads, kSeg, true>(M, S, Tr, node, tile, hits || Tr.mask_slot[node].x >= 0, S.c0_of_win[yaw[node]], total + node);
@@ -944,7 +946,7 @@ __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict
                                                      bool depth) {
     // (workgroup-uniform values kept in scalar registers)
     const uint32_t g = xcd_grouped(blockIdx.x, gridDim.x);
-    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(g / (uint32_t)S.T));
+    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(g, (uint32_t)S.T, S.T_mul));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)g - item * S.T);
     const unsigned long long it = items[item];
     const BatchTree& BT = trees[(uint32_t)(it >> 32)];
@@ -963,14 +965,15 @@ __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict
 template <bool kFew>
 __global__ __launch_bounds__(kFew ? kFewThreads : kBuildThreads) void k_mask_build_multi(const BatchTree* __restrict__ trees,
                                                                     const unsigned long long* __restrict__ items,
-                                                                    SensorDev S, int32_t chunks, int32_t bricks) {
+                                                                    SensorDev S, int32_t chunks, int32_t bricks, uint32_t chunks_mul) {
     extern __shared__ char smem[];
     __shared__ uint8_t s_live[kMaxBuildBricks];
     __shared__ uint32_t s_cw[kMaxBuildBricks];
     __shared__ uint32_t s_b[kMaxBuildBricks];
     __shared__ int32_t s_any;
     const uint32_t g = xcd_grouped(blockIdx.x, gridDim.x);
-    const unsigned long long it = items[g / (uint32_t)chunks];
+    const uint32_t item = divide(g, (uint32_t)chunks, chunks_mul);
+    const unsigned long long it = items[item];
     const BatchTree& BT = trees[(uint32_t)(it >> 32)];
     if (BT.status != nullptr && *BT.status != 0) return;      // (the request has failed)
     SensorDev St = S;
@@ -978,7 +981,8 @@ __global__ __launch_bounds__(kFew ? kFewThreads : kBuildThreads) void k_mask_bui
     St.rv2 = BT.rv2;
     const MapDev M = BT.map;
     const TreeDev Tr = BT.td;
-    build_chunk<kFew>(M, St, Tr, (int32_t)(uint32_t)it, (int32_t)(g % (uint32_t)chunks), bricks, smem, s_live, s_cw, s_b, &s_any);
+    build_chunk<kFew>(M, St, Tr, (int32_t)(uint32_t)it, (int32_t)(g - item * (uint32_t)chunks), bricks, smem, s_live, s_cw,
+                      s_b, &s_any);
 }
 
 // Window selection of one (tree, node) item of a batch: gain, window, the
@@ -1083,7 +1087,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         const int32_t i0 = level_ptr[d], n = level_ptr[d + 1] - i0;
         const uint32_t units = (uint32_t)n * (uint32_t)S.T;
         for (uint32_t u = blockIdx.x; u < units; u += G) {
-            const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)(u / (uint32_t)S.T));
+            const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(u, (uint32_t)S.T, S.T_mul));
             const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)u - item * S.T);
             const unsigned long long it = items[i0 + item];
             const BatchTree& BT = trees[(uint32_t)(it >> 32)];
@@ -1229,6 +1233,7 @@ static SensorDev trace_sensor(const SensorDev& sd, int seg, int32_t threads, int
     const int32_t cols = kRayBlockCols / seg;
     st.n_blocks = (columns + cols - 1) / cols * sd.nrb;
     st.T = (st.n_blocks * 64 + threads - 1) / threads;
+    st.T_mul = divisor_mul((uint32_t)st.T);
     return st;
 }
 
@@ -1317,10 +1322,11 @@ hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev
     const size_t lds = build_lds_bytes(sd);
     if (lds + kBuildFixedLds > lds_limit()) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)n_nodes * (unsigned)chunks);
+    const uint32_t mul = divisor_mul((uint32_t)chunks);
     if (few_chunks(grid.x, bricks))
-        hipLaunchKernelGGL(k_mask_build<true>, grid, dim3(kFewThreads), lds, s, m, sd, td, nodes, chunks, bricks);
+        hipLaunchKernelGGL(k_mask_build<true>, grid, dim3(kFewThreads), lds, s, m, sd, td, nodes, chunks, bricks, mul);
     else
-        hipLaunchKernelGGL(k_mask_build<false>, grid, dim3(kBuildThreads), lds, s, m, sd, td, nodes, chunks, bricks);
+        hipLaunchKernelGGL(k_mask_build<false>, grid, dim3(kBuildThreads), lds, s, m, sd, td, nodes, chunks, bricks, mul);
     return hipGetLastError();
 }
 
@@ -1543,13 +1549,14 @@ hipError_t launch_batch_level(const BatchTree* trees, const unsigned long long* 
     const int32_t chunks = (int32_t)((mask_bricks + (uint32_t)bricks - 1) / (uint32_t)bricks);
     if ((uint64_t)n_mitems * (uint64_t)chunks >= (1ull << 32)) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)n_mitems * (unsigned)chunks);
+    const uint32_t mul = divisor_mul((uint32_t)chunks);
     const bool few = few_chunks(grid.x, bricks);
     const auto kernel = few ? k_mask_build_multi<true> : k_mask_build_multi<false>;
     const dim3 threads(few ? kFewThreads : kBuildThreads);
     if (b0 && b1)
-        hipExtLaunchKernelGGL(kernel, grid, threads, lds, s, b0, b1, 0u, trees, mitems, sd, chunks, bricks);
+        hipExtLaunchKernelGGL(kernel, grid, threads, lds, s, b0, b1, 0u, trees, mitems, sd, chunks, bricks, mul);
     else
-        hipLaunchKernelGGL(kernel, grid, threads, lds, s, trees, mitems, sd, chunks, bricks);
+        hipLaunchKernelGGL(kernel, grid, threads, lds, s, trees, mitems, sd, chunks, bricks, mul);
     return hipGetLastError();
 }
 
@@ -1579,6 +1586,7 @@ hipError_t launch_batch_persistent(const BatchTree* trees, const unsigned long l
     if (e != hipSuccess) return e;
     SensorDev st = sd;
     st.T = tiles_per_node(sd, 0);
+    st.T_mul = divisor_mul((uint32_t)st.T);
     int32_t bricks = kShapes[0].bricks;
     int32_t chunks = (int32_t)((mask_bricks + (uint32_t)bricks - 1) / (uint32_t)bricks);
     e = launch_zero_u32(sync, 2, s);
