@@ -10,7 +10,7 @@ Workloads (seeded, synthetic): `large` (default, the headline: 8 trees of 3000
 nodes on a 512x512x128 grid at 0.05 m, 720x120 rays, 15 m), `step`, `batch64`,
 `tiny`, and `serve16` (its own serving line). With the default headline the
 line also carries `step` and `batch64` as extra keys, and the next-row paths
-(single-parent gain, interval mode, exact hash sets, path score, map
+(single-parent gain, interval mode, exact voxel sets, path score, map
 conversion) timed on `step`.
 
 Modes
@@ -152,7 +152,7 @@ def parse():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--sp-steps", type=int, default=5, help="timed single-parent (g_sp) passes; 0 skips")
     ap.add_argument("--ivl-steps", type=int, default=3, help="timed interval-mode passes; 0 skips")
-    ap.add_argument("--exact-steps", type=int, default=3, help="timed exact hash-set passes; 0 skips")
+    ap.add_argument("--exact-steps", type=int, default=3, help="timed exact set passes; 0 skips")
     ap.add_argument("--map-bench-only", action="store_true",
                     help="only run the map conversion / update timing (3 calls each) and exit")
     ap.add_argument("--no-map-bench", dest="map_bench", action="store_false",
@@ -680,7 +680,7 @@ def close(m):
 
 
 def next_rows(mg, m, args):
-    """The next-row paths on one measured workload: single-parent gain, interval mode, exact hash sets."""
+    """The next-row paths on one measured workload: single-parent gain, interval mode, exact voxel sets."""
     import torch
     w, trees, n_total, rays_per_step = m["w"], m["trees"], m["n_total"], m["rays_per_step"]
     sen = w.sensor
@@ -730,7 +730,7 @@ def next_rows(mg, m, args):
         out["interval"] = ivl
         log(f"[bench] interval: {ivl}")
     if args.exact_steps > 0 and "batched" in m["results"]:
-        # exact marginal gain with device hash sets at the depth-buffer windows just computed
+        # exact marginal gain with device voxel sets at the depth-buffer windows just computed
         # (the exact comparison of Sec. V-A), per tree: X_ray, X_set, A_set
         y_all = m["y_all"]
         batched_ms = m["results"]["batched"]["ms_per_step"]
@@ -752,8 +752,8 @@ def next_rows(mg, m, args):
         dt = (time.perf_counter() - t0) / args.exact_steps
         exact = {"ms_per_step": dt * 1e3, "window_rays_per_s": n_total * sen.n_el * sen.w_buf / dt,
                  "steps": args.exact_steps, "over_depth_buffer": dt * 1e3 / batched_ms,
-                 "path": "mg_eval_exact per tree (hash sets of the window rays' unknown voxels; X_ray, X_set, A_set)"}
-        # the exact planner gain with its own yaw choice (depth order, hash sets), the device
+                 "path": "mg_eval_exact per tree (sets of the window rays' unknown voxels; X_ray, X_set, A_set)"}
+        # the exact planner gain with its own yaw choice (depth order, voxel sets), the device
         # counterpart of the paper's exact CPU implementation
         ge, ye = torch.empty_like(xr), torch.empty_like(xr)
         for T in trees:

@@ -3,7 +3,7 @@
 For every node of a workload: the depth-buffer marginal gain (per-voxel
 test), the interval-mode gain (the paper's own test), the single-parent gain
 and the absolute gain, against the exact marginal gain counted with device
-hash sets (mg_eval_exact) at the depth-buffer windows (the interval mode
+voxel sets (mg_eval_exact) at the depth-buffer windows (the interval mode
 against the exact gain at its own windows); and how often the depth-buffer
 method picks the window the exact planner gain picks (mg_eval_exact_marginal,
 its own yaw choice on its own sets). Reports, as the CPU error report

@@ -45,6 +45,6 @@ void pool_put(void* block, size_t bytes, int device);
 void sync_device(int device);
 void forget_tree(mg_tree t);               // mg_batch.hip: drop cached launch plans that use t
 void forget_interval(mg_tree t);           // mg_interval.hip: free t's interval-mode buffers
-void forget_exact(mg_tree t);              // mg_exact.hip: free t's hash tables
+void forget_exact(mg_tree t);              // mg_exact.hip: free t's sets
 
 }  // namespace mgb

@@ -268,7 +268,7 @@ __device__ int brick_view(const SensorDev& S, const float* __restrict__ tm, floa
 // all (brick_view again) gets every bit set without testing. Of these bricks
 // only what can be read is written (the code, and the words when they can be
 // read). The window's tables are loaded into LDS only when some
-// brick of the chunk is tested. One wave tests one brick: each lane one (x, y)
+// brick of the chunk is tested (kFew: at the start). One wave tests one brick: each lane one (x, y)
 // column of 8 voxels. Whole workgroup; chunks past the map's last brick do
 // nothing (a batch launch covers its largest map).
 __device__ __forceinline__ void build_live(const MapDev& M, const SensorDev& S, const TreeDev& Tr, int32_t node,

@@ -425,7 +425,7 @@ class Tree:
         return g, y, d
 
     def eval_exact(self, yaw_bin, stream=None):
-        """Exact marginal gain with hash sets at the windows yaw_bin (device int32 [n]): (x_ray, x_set, a_set)."""
+        """Exact marginal gain with voxel sets at the windows yaw_bin (device int32 [n]): (x_ray, x_set, a_set)."""
         import torch
         xr = torch.empty(self.n, dtype=torch.int32, device=yaw_bin.device)
         xs = torch.empty_like(xr)
@@ -434,7 +434,7 @@ class Tree:
         return xr, xs, a
 
     def eval_exact_marginal(self, stream=None):
-        """Exact marginal gain with its own yaw choice (hash sets): (gain, yaw)."""
+        """Exact marginal gain with its own yaw choice (voxel sets): (gain, yaw)."""
         g, y, _ = self.outputs(False)
         mg_eval_exact_marginal(self.handle, g, y, stream)
         return g, y
