@@ -94,6 +94,15 @@ std::mutex g_mu;
 std::map<std::vector<mg_tree>, std::unique_ptr<Plan>> g_plans;
 constexpr size_t kMaxPlans = 64;
 constexpr int32_t kGroups = 3;             // independent groups of a plan, one stream each (3 measured best of 1/2/3/4/8)
+// A plan of little work keeps its levels whole, on the caller's stream: splitting
+// them over streams triples the launches, and levels this small are bound by those.
+// Work is waves times range in voxels, for maps of few mask bricks (the builder's
+// share grows with them, and overlaps other groups' traces). One tree, whole and
+// split: 20 nodes 79 and 198 us (64 x 64 x 32 grid), 100 nodes 363 and 412, 300
+// (8.3e6) 668 and 717, 500 (13.8e6) 924 and 888 (200 x 200 x 60 grid, 5408 slots);
+// 20 nodes 545 and 393 on a 512 x 512 x 128 grid (65536 slots).
+constexpr double kWholeWork = 8388608.0;
+constexpr uint32_t kWholeSlots = 16384;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -143,10 +152,18 @@ int build_plan(const std::vector<mg_tree>& trees, hipStream_t stream, std::uniqu
     // otherwise the levels above depth s (the first depth holding at least
     // kGroups nodes) form a shared prefix and the units are the subtrees
     // rooted at depth s.
+    // A plan of little work (kWholeWork) is all prefix.
+    double work = 0.0;
+    uint32_t slots = 0;
+    for (int32_t i = 0; i < nt; ++i) {
+        work += (double)views[i].n * (double)P->sd.n_blocks * (double)views[i].sd->rv;
+        slots = std::max(slots, views[i].map->build_slots);
+    }
+    const bool whole = work <= kWholeWork && slots <= kWholeSlots;
     int32_t split = 0;
-    if (nt < kGroups) {
+    if (nt < kGroups || whole) {
         split = levels;
-        for (int32_t d = 1; d < levels; ++d) {
+        for (int32_t d = 1; d < levels && !whole; ++d) {
             int64_t cnt = 0;
             for (int32_t i = 0; i < nt; ++i) {
                 const std::vector<int32_t>& lp = *views[i].level_ptr;
@@ -166,7 +183,7 @@ int build_plan(const std::vector<mg_tree>& trees, hipStream_t stream, std::uniqu
         const std::vector<int32_t>& dep = *views[i].depth;
         const int32_t n = views[i].n;
         unit_of[i].assign(n, -1);
-        if (nt >= kGroups) {
+        if (nt >= kGroups && !whole) {
             for (int32_t k = 0; k < n; ++k) unit_of[i][k] = i;
             unit_size.push_back(n);
             continue;

@@ -78,3 +78,26 @@ def test_a_plan_takes_every_call_its_own_buffers(mg):
     for T in trees:
         T.close()
     M.close()
+
+
+@pytest.mark.parametrize("counts", [(303,), (304,), (101, 101, 101), (102, 101, 101), (1,), (1, 1, 1, 1)])
+def test_batches_around_the_smallest_split_over_streams(mg, counts):
+    """Batches just below and above the work (304 nodes of this sensor) at which a plan's levels are split
+    over streams, of one tree and of several: the same gains and windows as tree by tree."""
+    import torch
+    w = W.make("step")
+    t = w.trees[0]
+    m = mg.Map(w.map.states, w.map.voxel_m, w.map.origin_m)
+    trees = [mg.Tree(m, t.pos_m[:n], t.parent[:n], w.sensor) for n in counts]
+    g, y, _ = mg.eval_batch(trees)
+    torch.cuda.synchronize()
+    at = 0
+    for n, x in zip(counts, trees):
+        rg, ry = x.eval_marginal()[:2]
+        torch.cuda.synchronize()
+        log(f"[split] {counts}: {n} nodes")
+        assert torch.equal(g[at:at + n], rg) and torch.equal(y[at:at + n], ry)
+        at += n
+    for x in trees:
+        x.close()
+    m.close()
