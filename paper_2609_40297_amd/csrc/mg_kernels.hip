@@ -129,6 +129,20 @@ __device__ __forceinline__ int32_t wrap(int32_t c, int32_t W) { return c >= W ? 
 // r lies at or to the left (counter-clockwise side) of boundary direction b.
 __device__ __forceinline__ bool left_of(float2 b, float rx, float ry) { return b.x * ry - b.y * rx >= 0.f; }
 
+// Workgroups are dealt to the chip's 8 XCDs (each with its own L2) in turn:
+// this permutation of the grid gives each XCD runs of kRun consecutive work
+// units (neighbouring pixel blocks, or bricks, of one node) while the runs
+// still alternate over the whole grid; the grid's last partial round keeps
+// the identity. Runs of 8 in the per-tree trace: 500 nodes 886 us in plain order,
+// 876 (16 and 64: 879 and 886); its builder gains nothing. Multi-tree launches take
+// 16 (128.9 ms against 136 in plain order, 24000 nodes).
+constexpr uint32_t kTreeRun = 8, kBatchRun = 16;
+template <uint32_t kRun>
+__device__ __forceinline__ uint32_t xcd_grouped(uint32_t g, uint32_t n) {
+    const uint32_t full = (n / (8u * kRun)) * (8u * kRun);
+    return g < full ? ((g >> 3) / kRun) * (8u * kRun) + (g & 7u) * kRun + (g >> 3) % kRun : g;
+}
+
 // ---------------------------------------------------------------- path masks
 
 // Mask builder launch shapes (rays per workgroup of the trace kernel, bricks
@@ -785,8 +799,9 @@ template <bool kMarginal, int kSeg>
 __global__ __launch_bounds__(kTreeTraceThreads) void k_trace(MapDev M, SensorDev S, TreeDev Tr,
                                                              const int32_t* __restrict__ nodes, bool depth) {
     // (workgroup-uniform values kept in scalar registers)
-    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(blockIdx.x, (uint32_t)S.T, S.T_mul));
-    const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
+    const uint32_t g = xcd_grouped<kTreeRun>(blockIdx.x, gridDim.x);
+    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(g, (uint32_t)S.T, S.T_mul));
+    const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)g - item * S.T);
     const int32_t node = nodes[item];
     trace_tile<kMarginal, kTreeTraceThreads, kSeg>(M, S, Tr, node, tile, depth || Tr.mask_slot[node].x >= 0);
 }
@@ -797,8 +812,9 @@ __global__ __launch_bounds__(kTreeTraceThreads) void k_trace_window(MapDev M, Se
                                                                     const int32_t* __restrict__ nodes,
                                                                     const int32_t* __restrict__ yaw,
                                                                     uint32_t* __restrict__ total, bool hits) {
-    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(blockIdx.x, (uint32_t)S.T, S.T_mul));
-    const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x - item * S.T);
+    const uint32_t g = xcd_grouped<kTreeRun>(blockIdx.x, gridDim.x);
+    const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(g, (uint32_t)S.T, S.T_mul));
+    const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)g - item * S.T);
     const int32_t node = nodes[item];
     trace_tile<true, kTreeTraceThreads, kSeg, true>(M, S, Tr, node, tile, hits || Tr.mask_slot[node].x >= 0, S.c0_of_win[yaw[node]], total + node);
 }
@@ -927,17 +943,6 @@ __global__ void k_batch_zero(const BatchTree* __restrict__ trees, int32_t B) {
         T.td.bins[i] = 0u;
 }
 
-// Workgroups are dealt to the chip's 8 XCDs (each with its own L2) in turn:
-// this permutation of the grid gives each XCD runs of kXcdRun consecutive work
-// units (neighbouring pixel blocks, or bricks, of one node) while the runs
-// still alternate over the whole grid; the grid's last partial round keeps
-// the identity.
-constexpr uint32_t kXcdRun = 16;
-__device__ __forceinline__ uint32_t xcd_grouped(uint32_t g, uint32_t n) {
-    const uint32_t full = (n / (8u * kXcdRun)) * (8u * kXcdRun);
-    return g < full ? ((g >> 3) / kXcdRun) * (8u * kXcdRun) + (g & 7u) * kXcdRun + (g >> 3) % kXcdRun : g;
-}
-
 // One depth level of all trees at once: work item = (tree, node) from
 // `items` (tree << 32 | node), T workgroups per item.
 template <int kTh, int kSeg>
@@ -945,7 +950,7 @@ __global__ __launch_bounds__(kTh) void k_trace_multi(const BatchTree* __restrict
                                                      const unsigned long long* __restrict__ items, SensorDev S,
                                                      bool depth) {
     // (workgroup-uniform values kept in scalar registers)
-    const uint32_t g = xcd_grouped(blockIdx.x, gridDim.x);
+    const uint32_t g = xcd_grouped<kBatchRun>(blockIdx.x, gridDim.x);
     const int32_t item = __builtin_amdgcn_readfirstlane((int32_t)divide(g, (uint32_t)S.T, S.T_mul));
     const int32_t tile = __builtin_amdgcn_readfirstlane((int32_t)g - item * S.T);
     const unsigned long long it = items[item];
@@ -971,7 +976,7 @@ __global__ __launch_bounds__(kFew ? kFewThreads : kBuildThreads) void k_mask_bui
     __shared__ uint32_t s_cw[kMaxBuildBricks];
     __shared__ uint32_t s_b[kMaxBuildBricks];
     __shared__ int32_t s_any;
-    const uint32_t g = xcd_grouped(blockIdx.x, gridDim.x);
+    const uint32_t g = xcd_grouped<kBatchRun>(blockIdx.x, gridDim.x);
     const uint32_t item = divide(g, (uint32_t)chunks, chunks_mul);
     const unsigned long long it = items[item];
     const BatchTree& BT = trees[(uint32_t)(it >> 32)];
