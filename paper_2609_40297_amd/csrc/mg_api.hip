@@ -408,6 +408,10 @@ int count_map(int device, int delta) {
 namespace mgb {
 
 hipError_t pool_get(void** block, size_t bytes, int device) {
+    int current = -1;
+    const hipError_t ec = hipGetDevice(&current);
+    if (ec != hipSuccess) return ec;
+    if (current != device) return hipErrorInvalidDevice;   // (hipMalloc's block would be another device's)
     const size_t cls = size_class(bytes);
     Pools& G = pools();
     std::lock_guard<std::mutex> lk(G.mu);

@@ -38,8 +38,8 @@ int prepare(mg_map map, const float* pos_m, const int32_t* parent, int32_t n, co
 size_t block_bytes(const HostTree& H);
 int upload_into(mg_map map, const HostTree& H, const mg_sensor* sensor, hipStream_t s, void* block, mg_tree* out);
 // Device blocks of trees and launch plans (mg_api.hip): kept when given back, up
-// to a bound, until the device's last map is destroyed. The caller of pool_put
-// has waited for every use of the block.
+// to a bound, until the device's last map is destroyed. pool_get is for the
+// current device. The caller of pool_put has waited for every use of the block.
 hipError_t pool_get(void** block, size_t bytes, int device);
 void pool_put(void* block, size_t bytes, int device);
 void sync_device(int device);

@@ -116,6 +116,7 @@ bool same_geometry(const mg_sensor& a, const mg_sensor& b) {
            a.fov_v_deg == b.fov_v_deg && a.az_offset_deg == b.az_offset_deg;
 }
 
+// (All trees live on the current device.)
 int build_plan(const std::vector<mg_tree>& trees, hipStream_t stream, std::unique_ptr<Plan>* out) {
     std::unique_ptr<Plan> P(new Plan());
     P->trees = trees;
@@ -130,7 +131,6 @@ int build_plan(const std::vector<mg_tree>& trees, hipStream_t stream, std::uniqu
         mgb::tree_view(trees[i], &v);
         if (!same_geometry(v.params, v0.params))
             return mgb::set_error(MG_E_INVALID, "trees in a batch must share the sensor geometry");
-        if (v.device != v0.device) return mgb::set_error(MG_E_INVALID, "trees in a batch must share a device");
         bt[i].map = *v.map;
         bt[i].td = *v.td;
         bt[i].rv = v.sd->rv;
@@ -633,6 +633,12 @@ extern "C" int mg_eval_marginal_batch(const mg_tree* trees, int32_t n_trees, voi
         it = g_plans.end();
     }
     if (it == g_plans.end()) {
+        // (before anything is allocated: it would be on this device)
+        for (int32_t i = 0; i < n_trees; ++i) {
+            mgb::TreeView v;
+            mgb::tree_view(trees[i], &v);
+            if (v.device != dev) return mgb::set_error(MG_E_INVALID, "batch trees live on another device");
+        }
         if (g_plans.size() >= kMaxPlans) {
             (void)hipDeviceSynchronize();
             g_plans.clear();
@@ -640,7 +646,6 @@ extern "C" int mg_eval_marginal_batch(const mg_tree* trees, int32_t n_trees, voi
         std::unique_ptr<Plan> P;
         int rc = build_plan(key, s, &P);
         if (rc != MG_OK) return rc;
-        if (P->device != dev) return mgb::set_error(MG_E_INVALID, "batch trees live on another device");
         rc = configure(*P, out, s);
         if (rc != MG_OK) return rc;
         it = g_plans.emplace(key, std::move(P)).first;

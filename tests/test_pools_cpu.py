@@ -1,0 +1,33 @@
+"""Device memory that outlives the objects it was made for (blocks of trees and plans, sensor tables, the
+exact gain's sets), on a fake HIP runtime with two devices: whose memory a call gets, what happens when
+a wait or an allocation fails, and what is given back."""
+import os
+
+import pytest
+
+from tests.fake_runtime import check
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    from paper_2609_40297_amd import mg
+    if not os.path.exists(mg.LIB_PATH):
+        from paper_2609_40297_amd import build
+        build.build()
+
+
+def test_a_batch_refused_on_another_device_leaves_no_memory_there():
+    """Trees of device 0 evaluated with device 1 current: refused before anything is allocated, and the
+    next tree and plan on device 0 get memory of device 0."""
+    check("""
+m = new_map()
+t = new_tree(m, 30)
+g, y = Out(64), Out(64)
+F.fake_set_device(1)
+assert code(mg.mg_eval_marginal_batch, [t], g, y, stream=0) == mg.MG_E_INVALID
+assert F.fake_live(1) == 0
+F.fake_set_device(0)
+before = F.fake_live(0)
+mg.mg_eval_marginal_batch([t], g, y, stream=0)
+assert F.fake_live(0) > before and F.fake_live(1) == 0
+""")
