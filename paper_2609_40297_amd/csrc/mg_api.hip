@@ -434,24 +434,28 @@ hipError_t pool_get(void** block, size_t bytes, int device) {
     return e;
 }
 
-void pool_put(void* block, size_t bytes, int device) {
+void pool_put(void* block, size_t bytes, int device, bool waited) {
     const size_t cls = size_class(bytes);
     Pools& G = pools();
     std::lock_guard<std::mutex> lk(G.mu);
     DevicePool& P = G.of[device];
-    if (P.exact.erase(block) != 0 || cls > kPoolBlock || P.held + cls > kPoolHeld || P.maps == 0) {
-        (void)hipFree(block);
+    // (hipFree waits by itself, or fails as the wait did: then the block is lost, not shared)
+    if (P.exact.erase(block) != 0 || !waited || cls > kPoolBlock || P.held + cls > kPoolHeld || P.maps == 0) {
+        if (hipFree(block) != hipSuccess) (void)hipGetLastError();
         return;
     }
     P.blocks.emplace(cls, block);
     P.held += cls;
 }
 
-void sync_device(int device) {
-    int dev = device;
-    const bool other = hipGetDevice(&dev) == hipSuccess && dev != device && hipSetDevice(device) == hipSuccess;
-    (void)hipDeviceSynchronize();
-    if (other) (void)hipSetDevice(dev);
+bool sync_device(int device) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    if (dev != device && hipSetDevice(device) != hipSuccess) return false;
+    const bool waited = hipDeviceSynchronize() == hipSuccess;
+    if (!waited) (void)hipGetLastError();          // (the next launch would report it)
+    if (dev != device) (void)hipSetDevice(dev);
+    return waited;
 }
 
 }  // namespace mgb
@@ -915,21 +919,18 @@ extern "C" int mg_tree_upload(mg_map map, const float* pos_m, const int32_t* par
         return fail(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, "tree allocation (%zu bytes): %s", H.total,
                     hipGetErrorString(e));
     rc = finish_upload(map, H, sensor, (hipStream_t)hip_stream, block, true, out);
-    if (rc != MG_OK) {
-        mgb::sync_device(dev);
-        mgb::pool_put(block, H.total, dev);
-    }
+    if (rc != MG_OK) mgb::pool_put(block, H.total, dev, mgb::sync_device(dev));
     return rc;
 }
 
 extern "C" int mg_tree_destroy(mg_tree t) {
     if (!t) return fail(MG_E_INVALID, "tree is NULL");
     // (work on the tree may still be queued on any stream)
-    if (t->owns_block) mgb::sync_device(t->device);
+    const bool waited = t->owns_block && mgb::sync_device(t->device);
     mgb::forget_tree(t);
     mgb::forget_interval(t);
     mgb::forget_exact(t);
-    if (t->owns_block) mgb::pool_put(t->block, t->bytes, t->device);
+    if (t->owns_block) mgb::pool_put(t->block, t->bytes, t->device, waited);
     release_sensor(t->sensor);
     t->map->trees--;
     delete t;

@@ -39,10 +39,12 @@ size_t block_bytes(const HostTree& H);
 int upload_into(mg_map map, const HostTree& H, const mg_sensor* sensor, hipStream_t s, void* block, mg_tree* out);
 // Device blocks of trees and launch plans (mg_api.hip): kept when given back, up
 // to a bound, until the device's last map is destroyed. pool_get is for the
-// current device. The caller of pool_put has waited for every use of the block.
+// current device. `waited`: the device has finished every use of the block
+// (sync_device says whether its wait succeeded; under a stream capture it fails);
+// a block without that is freed, never handed out again.
 hipError_t pool_get(void** block, size_t bytes, int device);
-void pool_put(void* block, size_t bytes, int device);
-void sync_device(int device);
+void pool_put(void* block, size_t bytes, int device, bool waited);
+bool sync_device(int device);
 void forget_tree(mg_tree t);               // mg_batch.hip: drop cached launch plans that use t
 void forget_interval(mg_tree t);           // mg_interval.hip: free t's interval-mode buffers
 void forget_exact(mg_tree t);              // mg_exact.hip: free t's sets

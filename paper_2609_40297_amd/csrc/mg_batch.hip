@@ -64,12 +64,10 @@ struct Plan {
     uint32_t* psync = nullptr;
     uint32_t* h_abort = nullptr;
     ~Plan() {
+        const bool waited = block && mgb::sync_device(device);     // its launches may still be queued
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
-        if (block) {
-            mgb::sync_device(device);              // its launches may still be queued
-            mgb::pool_put(block, block_bytes, device);
-        }
+        if (block) mgb::pool_put(block, block_bytes, device, waited);
         if (h_abort) (void)hipHostFree(h_abort);
     }
 };

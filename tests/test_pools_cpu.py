@@ -31,3 +31,26 @@ before = F.fake_live(0)
 mg.mg_eval_marginal_batch([t], g, y, stream=0)
 assert F.fake_live(0) > before and F.fake_live(1) == 0
 """)
+
+
+def test_a_block_whose_use_could_not_be_waited_for_is_not_given_to_the_next_tree():
+    """A tree and its plan dropped while the device cannot be waited for (a stream is being captured): work
+    on their blocks may still be queued, so no later tree or plan gets them."""
+    check("""
+m = new_map()
+g, y = Out(64), Out(64)
+t = new_tree(m, 30)
+mg.mg_eval_marginal_batch([t], g, y, stream=0)
+F.fake_fail_sync(1)
+mg.mg_tree_destroy(t)
+F.fake_fail_sync(0)
+before = F.fake_mallocs()
+t = new_tree(m, 30)
+assert F.fake_mallocs() == before + 1
+mg.mg_eval_marginal_batch([t], g, y, stream=0)
+assert F.fake_mallocs() == before + 2
+mg.mg_tree_destroy(t)
+t = new_tree(m, 30)                     # (with a wait that succeeds the blocks are reused)
+mg.mg_eval_marginal_batch([t], g, y, stream=0)
+assert F.fake_mallocs() == before + 2
+""")
