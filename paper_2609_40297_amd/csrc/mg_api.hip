@@ -377,9 +377,11 @@ struct DevicePool {
         held = 0;
     }
 };
+constexpr int kPoolDevices = 64;
 struct Pools {
     std::mutex mu;
-    std::map<int, DevicePool> of;
+    DevicePool dev[kPoolDevices];
+    DevicePool* of(int device) { return device >= 0 && device < kPoolDevices ? &dev[device] : nullptr; }   // NULL: nothing is kept
 };
 // (never destroyed: plans that outlive main's end still give their blocks back)
 Pools& pools() {
@@ -397,10 +399,11 @@ size_t size_class(size_t bytes) {
 int count_map(int device, int delta) {
     Pools& G = pools();
     std::lock_guard<std::mutex> lk(G.mu);
-    DevicePool& P = G.of[device];
-    P.maps += delta;
-    if (P.maps == 0) P.drain();
-    return P.maps;
+    DevicePool* P = G.of(device);
+    if (!P) return 0;
+    P->maps += delta;
+    if (P->maps == 0) P->drain();
+    return P->maps;
 }
 
 }  // namespace
@@ -415,37 +418,49 @@ hipError_t pool_get(void** block, size_t bytes, int device) {
     const size_t cls = size_class(bytes);
     Pools& G = pools();
     std::lock_guard<std::mutex> lk(G.mu);
-    DevicePool& P = G.of[device];
-    if (cls > kPoolBlock) return hipMalloc(block, bytes);
-    auto it = P.blocks.find(cls);
-    if (it != P.blocks.end()) {
+    DevicePool* P = G.of(device);
+    if (!P || cls > kPoolBlock) return hipMalloc(block, bytes);
+    auto it = P->blocks.find(cls);
+    if (it != P->blocks.end()) {
         *block = it->second;
-        P.held -= cls;
-        P.blocks.erase(it);
+        P->held -= cls;
+        P->blocks.erase(it);
         return hipSuccess;
     }
     hipError_t e = hipMalloc(block, cls);
     if (e == hipErrorOutOfMemory) {              // without the pool's blocks and the class's rounding
         (void)hipGetLastError();
-        P.drain();
+        P->drain();
         e = hipMalloc(block, bytes);
-        if (e == hipSuccess) P.exact.insert(*block);
+        if (e == hipSuccess) {
+            try {
+                P->exact.insert(*block);
+            } catch (const std::bad_alloc&) {
+                (void)hipFree(*block);
+                e = hipErrorOutOfMemory;
+            }
+        }
     }
     return e;
 }
 
-void pool_put(void* block, size_t bytes, int device, bool waited) {
+// (noexcept: plans give their blocks back in their destructor)
+void pool_put(void* block, size_t bytes, int device, bool waited) noexcept {
     const size_t cls = size_class(bytes);
     Pools& G = pools();
     std::lock_guard<std::mutex> lk(G.mu);
-    DevicePool& P = G.of[device];
+    DevicePool* P = G.of(device);
     // (hipFree waits by itself, or fails as the wait did: then the block is lost, not shared)
-    if (P.exact.erase(block) != 0 || !waited || cls > kPoolBlock || P.held + cls > kPoolHeld || P.maps == 0) {
-        if (hipFree(block) != hipSuccess) (void)hipGetLastError();
-        return;
+    bool keep = P && P->exact.erase(block) == 0 && waited && cls <= kPoolBlock && P->held + cls <= kPoolHeld && P->maps != 0;
+    if (keep) {
+        try {
+            P->blocks.emplace(cls, block);
+            P->held += cls;
+        } catch (const std::bad_alloc&) {
+            keep = false;
+        }
     }
-    P.blocks.emplace(cls, block);
-    P.held += cls;
+    if (!keep && hipFree(block) != hipSuccess) (void)hipGetLastError();
 }
 
 bool sync_device(int device) {

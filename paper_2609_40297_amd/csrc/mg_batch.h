@@ -43,7 +43,7 @@ int upload_into(mg_map map, const HostTree& H, const mg_sensor* sensor, hipStrea
 // (sync_device says whether its wait succeeded; under a stream capture it fails);
 // a block without that is freed, never handed out again.
 hipError_t pool_get(void** block, size_t bytes, int device);
-void pool_put(void* block, size_t bytes, int device, bool waited);
+void pool_put(void* block, size_t bytes, int device, bool waited) noexcept;
 bool sync_device(int device);
 void forget_tree(mg_tree t);               // mg_batch.hip: drop cached launch plans that use t
 void forget_interval(mg_tree t);           // mg_interval.hip: free t's interval-mode buffers

@@ -54,3 +54,25 @@ t = new_tree(m, 30)                     # (with a wait that succeeds the blocks 
 mg.mg_eval_marginal_batch([t], g, y, stream=0)
 assert F.fake_mallocs() == before + 2
 """)
+
+
+@pytest.mark.parametrize("nth", [1, 2])
+def test_a_pool_without_host_memory_frees_the_block(nth):
+    """Host memory runs out while a tree and its plan are given back: the call succeeds, nothing is thrown
+    through it, and what the pool could not note is freed on the device."""
+    check(f"""
+m = new_map()
+g, y = Out(64), Out(64)
+for planned in (False, True):
+    t = new_tree(m, 30)
+    if planned:
+        mg.mg_eval_marginal_batch([t], g, y, stream=0)
+    before, frees = F.fake_live(0), F.fake_frees()
+    F.fake_fail_new({nth})
+    mg.mg_tree_destroy(t)
+    F.fake_fail_new(0)
+    assert F.fake_frees() - frees == (1 if planned or {nth} == 1 else 0)
+    assert (F.fake_live(0) < before) == (planned or {nth} == 1)
+mg.mg_map_destroy(m)
+assert F.fake_live(0) == 0
+""")
