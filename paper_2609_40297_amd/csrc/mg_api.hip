@@ -234,13 +234,18 @@ int acquire_sensor(const mg_sensor* s, hipStream_t stream, SensorRes** out) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     SensorKey key{s->n_az, s->n_el, s->yaw_bins, s->fov_h_deg, s->fov_v_deg, s->range_m, s->az_offset_deg, dev};
-    std::lock_guard<std::mutex> lk(g_sensor_mu);
-    auto it = g_sensors.find(key);
-    if (it != g_sensors.end()) {
+    auto known = [&]() {                         // (g_sensor_mu held)
+        auto it = g_sensors.find(key);
+        if (it == g_sensors.end()) return false;
         it->second->refs++;
         *out = it->second;
-        return MG_OK;
+        return true;
+    };
+    {
+        std::lock_guard<std::mutex> lk(g_sensor_mu);
+        if (known()) return MG_OK;
     }
+    // (made without the lock: an allocation that fails may free idle tables)
     std::unique_ptr<SensorRes> r(new (std::nothrow) SensorRes());
     if (!r) return fail(MG_E_NOMEM, "host allocation failed");
     r->key = key;
@@ -254,16 +259,16 @@ int acquire_sensor(const mg_sensor* s, hipStream_t stream, SensorRes** out) {
     }
     auto cleanup = [&]() { SensorRes* p = r.release(); free_sensor(p); };
     hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = hipMalloc(&r->d4, R * sizeof(float4));
-    if (e == hipSuccess) e = hipMalloc(&r->iv4, R * sizeof(float4));
-    if (e == hipSuccess) e = hipMalloc(&r->bins, T.W * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&r->c0, T.B * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&r->bv, T.W * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc(&r->ts, (T.H + 1) * sizeof(float));
+    if (e == hipSuccess) e = mgb::device_alloc(&r->d4, R * sizeof(float4));
+    if (e == hipSuccess) e = mgb::device_alloc(&r->iv4, R * sizeof(float4));
+    if (e == hipSuccess) e = mgb::device_alloc(&r->bins, T.W * sizeof(int32_t));
+    if (e == hipSuccess) e = mgb::device_alloc(&r->c0, T.B * sizeof(int32_t));
+    if (e == hipSuccess) e = mgb::device_alloc(&r->bv, T.W * sizeof(float2));
+    if (e == hipSuccess) e = mgb::device_alloc(&r->ts, (T.H + 1) * sizeof(float));
     const size_t nlut = T.lut_col.size() + T.lut_row.size();
     std::vector<uint16_t> luts(T.lut_col);
     luts.insert(luts.end(), T.lut_row.begin(), T.lut_row.end());
-    if (e == hipSuccess) e = hipMalloc(&r->luts, nlut * sizeof(uint16_t));
+    if (e == hipSuccess) e = mgb::device_alloc(&r->luts, nlut * sizeof(uint16_t));
     if (e == hipSuccess) e = hipMemcpyAsync(r->luts, luts.data(), nlut * sizeof(uint16_t), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(r->d4, d4.data(), R * sizeof(float4), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(r->iv4, iv4.data(), R * sizeof(float4), hipMemcpyHostToDevice, stream);
@@ -279,6 +284,11 @@ int acquire_sensor(const mg_sensor* s, hipStream_t stream, SensorRes** out) {
     r->bytes = R * 2 * sizeof(float4) + T.W * (sizeof(int32_t) + sizeof(float2)) + T.B * sizeof(int32_t) +
                (T.H + 1) * sizeof(float);
     r->refs = 1;
+    std::lock_guard<std::mutex> lk(g_sensor_mu);
+    if (known()) {                               // another thread's, made meanwhile
+        cleanup();
+        return MG_OK;
+    }
     SensorRes* p = r.release();
     g_sensors[key] = p;
     *out = p;
@@ -363,8 +373,8 @@ namespace {
 // work (500 nodes, 70 MB: upload 966 -> 38 us with blocks and tables kept and one
 // copy instead of ten, drop 391 -> 82 us). Per device, blocks of at most
 // kPoolBlock bytes and kPoolHeld in all, found again by their size class; the
-// pool is emptied when the device's last map is destroyed and when an allocation
-// fails.
+// pool is emptied, and idle sensor tables are freed, when the device's last map is
+// destroyed and when any allocation of the library fails (device_alloc).
 constexpr size_t kPoolBlock = size_t(256) << 20, kPoolHeld = size_t(512) << 20;
 struct DevicePool {
     std::multimap<size_t, void*> blocks;     // by size class
@@ -410,6 +420,26 @@ int count_map(int device, int delta) {
 
 namespace mgb {
 
+hipError_t device_alloc(void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();                     // (the next launch would report it)
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess) return e;
+    {
+        Pools& G = pools();
+        std::lock_guard<std::mutex> lk(G.mu);
+        if (G.of(device)) G.of(device)->drain();
+    }
+    {
+        std::lock_guard<std::mutex> lk(g_sensor_mu);
+        trim_sensors(device, 0);
+    }
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 hipError_t pool_get(void** block, size_t bytes, int device) {
     int current = -1;
     const hipError_t ec = hipGetDevice(&current);
@@ -417,28 +447,29 @@ hipError_t pool_get(void** block, size_t bytes, int device) {
     if (current != device) return hipErrorInvalidDevice;   // (hipMalloc's block would be another device's)
     const size_t cls = size_class(bytes);
     Pools& G = pools();
-    std::lock_guard<std::mutex> lk(G.mu);
     DevicePool* P = G.of(device);
-    if (!P || cls > kPoolBlock) return hipMalloc(block, bytes);
-    auto it = P->blocks.find(cls);
-    if (it != P->blocks.end()) {
-        *block = it->second;
-        P->held -= cls;
-        P->blocks.erase(it);
-        return hipSuccess;
+    if (!P || cls > kPoolBlock) return device_alloc(block, bytes);
+    {
+        std::lock_guard<std::mutex> lk(G.mu);
+        auto it = P->blocks.find(cls);
+        if (it != P->blocks.end()) {
+            *block = it->second;
+            P->held -= cls;
+            P->blocks.erase(it);
+            return hipSuccess;
+        }
     }
     hipError_t e = hipMalloc(block, cls);
-    if (e == hipErrorOutOfMemory) {              // without the pool's blocks and the class's rounding
-        (void)hipGetLastError();
-        P->drain();
-        e = hipMalloc(block, bytes);
-        if (e == hipSuccess) {
-            try {
-                P->exact.insert(*block);
-            } catch (const std::bad_alloc&) {
-                (void)hipFree(*block);
-                e = hipErrorOutOfMemory;
-            }
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    e = device_alloc(block, bytes);              // without the class's rounding
+    if (e == hipSuccess) {
+        std::lock_guard<std::mutex> lk(G.mu);
+        try {
+            P->exact.insert(*block);
+        } catch (const std::bad_alloc&) {
+            (void)hipFree(*block);
+            e = hipErrorOutOfMemory;
         }
     }
     return e;
@@ -522,7 +553,7 @@ int map_alloc(int32_t nx, int32_t ny, int32_t nz, float voxel_m, const float ori
     if (!m) return fail(MG_E_NOMEM, "host allocation failed");
     HIP_TRY(hipGetDevice(&m->device));
     const size_t n_mbricks = (size_t)((nx + 7) / 8) * ((ny + 7) / 8) * ((nz + 7) / 8);
-    hipError_t e = hipMalloc(&m->bricks, padded + n_mbricks);      // the grid, then the brick flags
+    hipError_t e = mgb::device_alloc(&m->bricks, padded + n_mbricks);      // the grid, then the brick flags
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, "map allocation: %s", hipGetErrorString(e));
     m->dev.bricks = m->bricks;
@@ -573,7 +604,7 @@ extern "C" int mg_map_create(const uint8_t* states, int32_t nx, int32_t ny, int3
     if (rc != MG_OK) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
     uint8_t* dense = nullptr;
-    hipError_t e = hipMalloc(&dense, nvox);
+    hipError_t e = mgb::device_alloc(&dense, nvox);
     if (e == hipSuccess) e = hipMemcpyAsync(dense, states, nvox, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = launch_brick(dense, m->bricks, m->dev, s);
     if (e == hipSuccess) e = launch_brick_flags(m->dev, s);

@@ -37,6 +37,16 @@ void free_host_tree(HostTree* H);
 int prepare(mg_map map, const float* pos_m, const int32_t* parent, int32_t n, const mg_sensor* sensor, HostTree* H);
 size_t block_bytes(const HostTree& H);
 int upload_into(mg_map map, const HostTree& H, const mg_sensor* sensor, hipStream_t s, void* block, mg_tree* out);
+// hipMalloc on the current device (mg_api.hip); out of memory, once more when the
+// blocks and sensor tables that the library keeps without use there are freed.
+hipError_t device_alloc(void** p, size_t bytes);
+template <class T>
+hipError_t device_alloc(T** p, size_t bytes) {
+    void* v = nullptr;
+    const hipError_t e = device_alloc(&v, bytes);
+    *p = (T*)v;
+    return e;
+}
 // Device blocks of trees and launch plans (mg_api.hip): kept when given back, up
 // to a bound, until the device's last map is destroyed. pool_get is for the
 // current device. `waited`: the device has finished every use of the block

@@ -252,7 +252,7 @@ int own_sets(State& st, const MapDev& M, const std::vector<int32_t>& level_ptr, 
     if (want <= st.nodes) return MG_OK;
     (void)hipFree(st.own);
     st = State();
-    hipError_t e = hipMalloc(&st.own, bytes * (size_t)want);
+    hipError_t e = mgb::device_alloc(&st.own, bytes * (size_t)want);
     if (e == hipSuccess) e = launch_zero_u32(st.own, (size_t)M.mask_words * (size_t)want, s);
     if (e != hipSuccess) {
         (void)hipFree(st.own);

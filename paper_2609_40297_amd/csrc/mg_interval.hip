@@ -617,7 +617,7 @@ extern "C" int mg_eval_interval(mg_tree t, void* hip_stream, int32_t wd, int32_t
             const size_t o_d = o_cs + align256(sizeof(float2) * H.cs.size());
             const size_t o_w = o_d + align256(sizeof(float) * npx * (size_t)v.n);
             const size_t total = o_w + sizeof(float) * npx * (size_t)v.n;
-            e = hipMalloc(&st.block, total);
+            e = mgb::device_alloc(&st.block, total);
             if (e != hipSuccess) {
                 st.block = nullptr;
                 return fail_hip(e, "interval buffers");

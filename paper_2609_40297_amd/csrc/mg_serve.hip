@@ -194,7 +194,7 @@ int mg_server_s::apply_update(Request* r) {
         (void)hipFree(d_upd);
         d_upd = nullptr;
         cap_upd = 0;
-        e = hipMalloc(&d_upd, sizeof(uint32_t) * std::max(words, (size_t)1024));
+        e = mgb::device_alloc(&d_upd, sizeof(uint32_t) * std::max(words, (size_t)1024));
         if (e != hipSuccess) return hip_fail(e, "server map update staging");
         cap_upd = std::max(words, (size_t)1024);
     }
@@ -241,7 +241,7 @@ int mg_server_s::grow(size_t trees, size_t items, size_t stage_words) {
         (void)hipHostFree(h_trees);
         d_trees = nullptr;
         h_trees = nullptr;
-        e = hipMalloc(&d_trees, sizeof(BatchTree) * c);
+        e = mgb::device_alloc(&d_trees, sizeof(BatchTree) * c);
         if (e == hipSuccess) e = hipHostMalloc(&h_trees, sizeof(BatchTree) * c, hipHostMallocDefault);
         if (e != hipSuccess) return hip_fail(e, "server descriptors");
         cap_trees = c;
@@ -252,7 +252,7 @@ int mg_server_s::grow(size_t trees, size_t items, size_t stage_words) {
         (void)hipHostFree(h_items);
         d_items = nullptr;
         h_items = nullptr;
-        e = hipMalloc(&d_items, sizeof(unsigned long long) * c);
+        e = mgb::device_alloc(&d_items, sizeof(unsigned long long) * c);
         if (e == hipSuccess) e = hipHostMalloc(&h_items, sizeof(unsigned long long) * c, hipHostMallocDefault);
         if (e != hipSuccess) return hip_fail(e, "server work lists");
         cap_items = c;
@@ -491,8 +491,8 @@ extern "C" int mg_server_create(const mg_server_config* cfg, mg_server* out) {
     hipError_t e = hipGetDevice(&S->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&S->compute, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&S->upload, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipMalloc(&S->arena_mem, (size_t)cfg->arena_bytes);
-    if (e == hipSuccess) e = hipMalloc(&S->d_status, sizeof(int32_t) * (size_t)cfg->max_inflight);
+    if (e == hipSuccess) e = mgb::device_alloc(&S->arena_mem, (size_t)cfg->arena_bytes);
+    if (e == hipSuccess) e = mgb::device_alloc(&S->d_status, sizeof(int32_t) * (size_t)cfg->max_inflight);
     if (e == hipSuccess)
         e = hipHostMalloc(&S->h_status, sizeof(int32_t) * 2 * (size_t)cfg->max_inflight, hipHostMallocDefault);
     if (e != hipSuccess) {

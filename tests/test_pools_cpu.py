@@ -76,3 +76,44 @@ for planned in (False, True):
 mg.mg_map_destroy(m)
 assert F.fake_live(0) == 0
 """)
+
+
+# A call that needs device memory, beside a pool of about 100 MB of idle blocks: what it calls, and the
+# bytes that are free without them.
+SHORT = {
+    "map": (0, "mg.mg_map_destroy(new_map((500, 500, 60)))"),
+    "dense copy of a map": (4300000, "mg.mg_map_destroy(new_map((500, 500, 14)))"),
+    "tree above the pool's blocks": (260 << 20, "assert mg.mg_tree_footprint_bytes(new_tree(m, 60000)) > 256 * MiB"),
+    "sensor tables": (64 << 10, "new_tree(m, 1, wide(5.0))"),           # (its block is idle: another range's)
+    "exact sets": (0, "mg.mg_eval_exact_marginal(keep, g, y, stream=0)"),
+    "interval buffers": (0, "mg.mg_eval_interval(keep, 64, 48, g, y, stream=0)"),
+    "server": (0, "S = mg.Server(SENSOR, 2, 50 * MiB); S.close()"),
+}
+
+
+@pytest.mark.parametrize("what", SHORT)
+def test_idle_blocks_are_given_back_when_an_allocation_fails(what):
+    free, call = SHORT[what]
+    check(f"""
+m = new_map()
+g, y = Out(64), Out(64)
+keep = new_tree(m, 30)
+wide = lambda range_m: W.Sensor(n_az=512, n_el=64, fov_h_deg=90.0, fov_v_deg=60.0, range_m=range_m, yaw_bins=16)
+t = [new_tree(m, 10000), new_tree(m, 11000), new_tree(m, 1, wide(6.0))]
+[mg.mg_tree_destroy(x) for x in t]
+assert F.fake_live(0) > 80 * MiB
+F.fake_limit(0, F.fake_live(0) + {free})
+{call}
+assert F.fake_held(0, 30 * MiB) < 80 * MiB or {'True' if 'above' in what else 'False'}
+""")
+
+
+def test_idle_sensor_tables_are_given_back_when_an_allocation_fails():
+    check("""
+m = new_map()
+wide = W.Sensor(n_az=2048, n_el=512, fov_h_deg=90.0, fov_v_deg=60.0, range_m=5.0, yaw_bins=16)
+mg.mg_tree_destroy(new_tree(m, 1, wide))
+assert F.fake_live(0) > 32 * MiB
+F.fake_limit(0, F.fake_live(0) - MiB)
+mg.mg_map_destroy(new_map((200, 200, 60)))
+""")
