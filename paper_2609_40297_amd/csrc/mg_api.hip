@@ -14,7 +14,6 @@
 #include <memory>
 #include <mutex>
 #include <new>
-#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -371,20 +370,36 @@ namespace {
 // uploads a tree, evaluates it and drops it, and a hipMalloc and hipFree of tens
 // of megabytes, and rebuilding its sensor's tables, took longer than its host
 // work (500 nodes, 70 MB: upload 966 -> 38 us with blocks and tables kept and one
-// copy instead of ten, drop 391 -> 82 us). Per device, blocks of at most
-// kPoolBlock bytes and kPoolHeld in all, found again by their size class; the
-// pool is emptied, and idle sensor tables are freed, when the device's last map is
+// copy instead of ten, drop 391 -> 82 us). Per device, at most kPoolCount blocks of
+// at most kPoolBlock bytes, kPoolHeld bytes in all, those given back longest ago
+// freed first; a block serves its own size class and the next smaller one. The pool
+// is emptied, and idle sensor tables are freed, when the device's last map is
 // destroyed and when any allocation of the library fails (device_alloc).
-constexpr size_t kPoolBlock = size_t(256) << 20, kPoolHeld = size_t(512) << 20;
+constexpr size_t kPoolBlock = size_t(256) << 20, kPoolHeld = size_t(512) << 20, kPoolCount = 1024;
 struct DevicePool {
-    std::multimap<size_t, void*> blocks;     // by size class
-    std::set<void*> exact;                   // blocks in use that are smaller than their class
+    struct Held {
+        void* block;
+        uint64_t since;                      // (a count of blocks given back)
+    };
+    std::multimap<size_t, Held> blocks;      // by size class
+    uint64_t given = 0;
     size_t held = 0;
     int maps = 0;                            // live maps on the device
     void drain() {
-        for (auto& b : blocks) (void)hipFree(b.second);
+        for (auto& b : blocks) (void)hipFree(b.second.block);
         blocks.clear();
         held = 0;
+    }
+    // Frees the blocks given back longest ago until `bytes` more fit.
+    void make_room(size_t bytes) {
+        while (!blocks.empty() && (held + bytes > kPoolHeld || blocks.size() >= kPoolCount)) {
+            auto oldest = blocks.begin();
+            for (auto it = blocks.begin(); it != blocks.end(); ++it)
+                if (it->second.since < oldest->second.since) oldest = it;
+            (void)hipFree(oldest->second.block);
+            held -= oldest->first;
+            blocks.erase(oldest);
+        }
     }
 };
 constexpr int kPoolDevices = 64;
@@ -440,53 +455,47 @@ hipError_t device_alloc(void** p, size_t bytes) {
     return e;
 }
 
-hipError_t pool_get(void** block, size_t bytes, int device) {
+hipError_t pool_get(void** block, size_t* held, size_t bytes, int device) {
     int current = -1;
     const hipError_t ec = hipGetDevice(&current);
     if (ec != hipSuccess) return ec;
     if (current != device) return hipErrorInvalidDevice;   // (hipMalloc's block would be another device's)
     const size_t cls = size_class(bytes);
+    *held = bytes;
     Pools& G = pools();
     DevicePool* P = G.of(device);
     if (!P || cls > kPoolBlock) return device_alloc(block, bytes);
     {
         std::lock_guard<std::mutex> lk(G.mu);
-        auto it = P->blocks.find(cls);
-        if (it != P->blocks.end()) {
-            *block = it->second;
-            P->held -= cls;
+        auto it = P->blocks.lower_bound(cls);
+        if (it != P->blocks.end() && it->first <= size_class(cls + 1)) {
+            *block = it->second.block;
+            *held = it->first;
+            P->held -= it->first;
             P->blocks.erase(it);
             return hipSuccess;
         }
     }
     hipError_t e = hipMalloc(block, cls);
+    if (e == hipSuccess) *held = cls;
     if (e != hipErrorOutOfMemory) return e;
     (void)hipGetLastError();
-    e = device_alloc(block, bytes);              // without the class's rounding
-    if (e == hipSuccess) {
-        std::lock_guard<std::mutex> lk(G.mu);
-        try {
-            P->exact.insert(*block);
-        } catch (const std::bad_alloc&) {
-            (void)hipFree(*block);
-            e = hipErrorOutOfMemory;
-        }
-    }
-    return e;
+    return device_alloc(block, bytes);           // without the class's rounding
 }
 
 // (noexcept: plans give their blocks back in their destructor)
-void pool_put(void* block, size_t bytes, int device, bool waited) noexcept {
-    const size_t cls = size_class(bytes);
+void pool_put(void* block, size_t held, int device, bool waited) noexcept {
     Pools& G = pools();
     std::lock_guard<std::mutex> lk(G.mu);
     DevicePool* P = G.of(device);
-    // (hipFree waits by itself, or fails as the wait did: then the block is lost, not shared)
-    bool keep = P && P->exact.erase(block) == 0 && waited && cls <= kPoolBlock && P->held + cls <= kPoolHeld && P->maps != 0;
+    // (a block smaller than its class serves no other; hipFree waits by itself, or fails
+    // as the wait did: then the block is lost, not shared)
+    bool keep = P && waited && held <= kPoolBlock && size_class(held) == held && P->maps != 0;
     if (keep) {
+        P->make_room(held);
         try {
-            P->blocks.emplace(cls, block);
-            P->held += cls;
+            P->blocks.emplace(held, DevicePool::Held{block, P->given++});
+            P->held += held;
         } catch (const std::bad_alloc&) {
             keep = false;
         }
@@ -736,6 +745,7 @@ struct mg_tree_s {
     TreeDev dev{};
     SensorDev sd{};
     size_t bytes = 0;
+    size_t held = 0;                      // bytes of the block as the pool gave it
     int device = 0;
     uint32_t* scratch_gain = nullptr;     // device outputs used when the caller gives none
     int32_t* scratch_yaw = nullptr;
@@ -958,14 +968,18 @@ extern "C" int mg_tree_upload(mg_map map, const float* pos_m, const int32_t* par
     int rc = prepare_tree(map, pos_m, parent, n, sensor, &H);
     if (rc != MG_OK) return rc;
     void* block = nullptr;
+    size_t held = 0;
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
-    hipError_t e = mgb::pool_get(&block, H.total, dev);
+    hipError_t e = mgb::pool_get(&block, &held, H.total, dev);
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, "tree allocation (%zu bytes): %s", H.total,
                     hipGetErrorString(e));
     rc = finish_upload(map, H, sensor, (hipStream_t)hip_stream, block, true, out);
-    if (rc != MG_OK) mgb::pool_put(block, H.total, dev, mgb::sync_device(dev));
+    if (rc != MG_OK)
+        mgb::pool_put(block, held, dev, mgb::sync_device(dev));
+    else
+        (*out)->held = held;
     return rc;
 }
 
@@ -976,7 +990,7 @@ extern "C" int mg_tree_destroy(mg_tree t) {
     mgb::forget_tree(t);
     mgb::forget_interval(t);
     mgb::forget_exact(t);
-    if (t->owns_block) mgb::pool_put(t->block, t->bytes, t->device, waited);
+    if (t->owns_block) mgb::pool_put(t->block, t->held, t->device, waited);
     release_sensor(t->sensor);
     t->map->trees--;
     delete t;

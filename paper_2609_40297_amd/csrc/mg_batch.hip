@@ -33,7 +33,7 @@ struct Plan {
     std::vector<mg_tree> trees;
     BatchOut out{};                        // output buffers of the captured graph (the other forms take each call's)
     void* block = nullptr;                 // BatchTree[n_trees] | items[total] | mitems (nodes with children) | ...
-    size_t block_bytes = 0;
+    size_t held = 0;                       // bytes of the block as the pool gave it
     const BatchTree* dtrees = nullptr;
     const unsigned long long* ditems = nullptr;
     const unsigned long long* dmitems = nullptr;
@@ -67,7 +67,7 @@ struct Plan {
         const bool waited = block && mgb::sync_device(device);     // its launches may still be queued
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
-        if (block) mgb::pool_put(block, block_bytes, device, waited);
+        if (block) mgb::pool_put(block, held, device, waited);
         if (h_abort) (void)hipHostFree(h_abort);
     }
 };
@@ -285,9 +285,8 @@ int build_plan(const std::vector<mg_tree>& trees, hipStream_t stream, std::uniqu
     const size_t o_plevel = take(sizeof(int32_t) * plevel.size());
     const size_t o_pmlevel = take(sizeof(int32_t) * pmlevel.size());
     const size_t o_psync = take(sizeof(uint32_t) * 2);
-    hipError_t e = mgb::pool_get(&P->block, off, P->device);
+    hipError_t e = mgb::pool_get(&P->block, &P->held, off, P->device);
     if (e != hipSuccess) return hip_fail(e, "batch plan allocation");
-    P->block_bytes = off;
     // one copy of everything
     std::vector<char> host(off, 0);
     auto put = [&](size_t o, const void* src, size_t bytes) { if (bytes) std::memcpy(host.data() + o, src, bytes); };

@@ -117,3 +117,31 @@ assert F.fake_live(0) > 32 * MiB
 F.fake_limit(0, F.fake_live(0) - MiB)
 mg.mg_map_destroy(new_map((200, 200, 60)))
 """)
+
+
+def test_a_full_pool_keeps_the_latest_blocks():
+    """Trees of many sizes, more than the pool holds, then the last size over and over: no allocation, and
+    never more than 512 MiB idle."""
+    check("""
+m = new_map()
+for n in range(6000, 20000, 1000):
+    mg.mg_tree_destroy(new_tree(m, n))
+    assert F.fake_held(0, MiB) <= 512 * MiB
+before = F.fake_mallocs()
+for _ in range(3):
+    mg.mg_tree_destroy(new_tree(m, n))
+assert F.fake_mallocs() == before
+""")
+
+
+def test_a_tree_takes_a_block_of_the_next_size():
+    check("""
+m = new_map()
+mg.mg_tree_destroy(new_tree(m, 10000))
+before = F.fake_mallocs()
+for n in (9800, 9400, 9800, 10000):       # (the classes are 6 to 12 % apart)
+    mg.mg_tree_destroy(new_tree(m, n))
+assert F.fake_mallocs() == before
+mg.mg_tree_destroy(new_tree(m, 5000))     # (half the size does not)
+assert F.fake_mallocs() == before + 1
+""")
