@@ -203,7 +203,8 @@ void build_tables(const mg_sensor* s, int32_t w, int32_t wb, HostTables* T) {
 // Device copy of one sensor's tables, shared by all trees with that sensor on
 // that device (reference counted). Tables that the last tree has dropped stay
 // for the next one (a replan's tree is usually alone), up to kIdleSensors bytes
-// of them per device, until the device's last map is destroyed.
+// of them per device, those dropped longest ago freed first, until the device's
+// last map is destroyed.
 struct SensorRes {
     SensorKey key;
     int refs = 0;
@@ -214,11 +215,13 @@ struct SensorRes {
     float* ts = nullptr;
     uint16_t* luts = nullptr;   // lut_col then lut_row
     size_t bytes = 0;
+    uint64_t since = 0;         // when the last tree dropped it (a count of drops)
 };
 
 constexpr size_t kIdleSensors = size_t(64) << 20;
 std::mutex g_sensor_mu;
 std::map<SensorKey, SensorRes*> g_sensors;
+uint64_t g_sensor_drops = 0;
 
 void free_sensor(SensorRes* r) {
     (void)hipFree(r->d4); (void)hipFree(r->iv4); (void)hipFree(r->bins); (void)hipFree(r->c0); (void)hipFree(r->bv); (void)hipFree(r->ts);
@@ -294,24 +297,30 @@ int acquire_sensor(const mg_sensor* s, hipStream_t stream, SensorRes** out) {
     return MG_OK;
 }
 
-// Frees the device's tables without a tree, those past `keep` bytes (g_sensor_mu held).
+// Frees the device's tables without a tree, the longest unused first, until those
+// left take at most `keep` bytes (g_sensor_mu held).
 void trim_sensors(int device, size_t keep) {
-    size_t idle = 0;
-    for (auto it = g_sensors.begin(); it != g_sensors.end();) {
-        SensorRes* r = it->second;
-        if (r->refs == 0 && r->key.device == device && idle + r->bytes > keep) {
-            it = g_sensors.erase(it);
-            free_sensor(r);
-            continue;
+    for (;;) {
+        size_t idle = 0;
+        auto oldest = g_sensors.end();
+        for (auto it = g_sensors.begin(); it != g_sensors.end(); ++it) {
+            const SensorRes* r = it->second;
+            if (r->refs != 0 || r->key.device != device) continue;
+            idle += r->bytes;
+            if (oldest == g_sensors.end() || r->since < oldest->second->since) oldest = it;
         }
-        if (r->refs == 0 && r->key.device == device) idle += r->bytes;
-        ++it;
+        if (oldest == g_sensors.end() || idle <= keep) return;
+        SensorRes* r = oldest->second;
+        g_sensors.erase(oldest);
+        free_sensor(r);
     }
 }
 
 void release_sensor(SensorRes* r) {
     std::lock_guard<std::mutex> lk(g_sensor_mu);
-    if (--r->refs == 0) trim_sensors(r->key.device, kIdleSensors);
+    if (--r->refs != 0) return;
+    r->since = g_sensor_drops++;
+    trim_sensors(r->key.device, kIdleSensors);
 }
 
 SensorDev sensor_dev(const SensorRes* r, float rv) {

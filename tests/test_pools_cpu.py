@@ -145,3 +145,19 @@ assert F.fake_mallocs() == before
 mg.mg_tree_destroy(new_tree(m, 5000))     # (half the size does not)
 assert F.fake_mallocs() == before + 1
 """)
+
+
+def test_idle_sensor_tables_dropped_last_are_kept():
+    """Tables of more sensors than are kept idle, dropped in the order of their keys and against it: the
+    last one's are still there."""
+    check("""
+m = new_map()
+wide = lambda range_m: W.Sensor(n_az=1024, n_el=512, fov_h_deg=90.0, fov_v_deg=60.0, range_m=range_m, yaw_bins=16)
+for ranges in ((2.0, 3.0, 4.0, 5.0, 6.0, 7.0), (7.0, 6.0, 5.0, 4.0, 3.0, 2.0)):
+    for r in ranges:
+        mg.mg_tree_destroy(new_tree(m, 1, wide(r)))
+        assert F.fake_held(0, 8 * MiB) <= 64 * MiB
+    before = F.fake_mallocs()
+    mg.mg_tree_destroy(new_tree(m, 1, wide(r)))
+    assert F.fake_mallocs() == before
+""")
