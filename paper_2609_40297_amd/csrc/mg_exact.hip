@@ -230,10 +230,12 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
     }
 }
 
-// Per-tree device state: own sets of up to `nodes` nodes, all clear between calls.
+// Per-tree device state: own sets of up to `nodes` nodes, all clear between calls
+// but after one that failed, whose voxels may still be in them.
 struct State {
     uint32_t* own = nullptr;
     int32_t nodes = 0;
+    bool clear = false;
 };
 
 std::mutex g_mu;
@@ -243,14 +245,18 @@ int fail_hip(hipError_t e, const char* what) {
     return mgb::set_error(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, what);
 }
 
-// Own sets for the widest of the levels' lists, at most kPoolBytes of them.
+// Own sets for the widest of the levels' lists, at most kPoolBytes of them, for a
+// call that says itself when it has left them clear.
 int own_sets(State& st, const MapDev& M, const std::vector<int32_t>& level_ptr, hipStream_t s) {
     int32_t want = 1;
     for (size_t d = 0; d + 1 < level_ptr.size(); ++d) want = std::max(want, level_ptr[d + 1] - level_ptr[d]);
     const size_t bytes = sizeof(uint32_t) * (size_t)M.mask_words;
     want = (int32_t)std::min<size_t>((size_t)want, std::max<size_t>(1, kPoolBytes / bytes));
-    if (want <= st.nodes) return MG_OK;
-    (void)hipFree(st.own);
+    if (want <= st.nodes && st.clear) {
+        st.clear = false;
+        return MG_OK;
+    }
+    (void)hipFree(st.own);                       // (after the work of a call that failed)
     st = State();
     hipError_t e = mgb::device_alloc(&st.own, bytes * (size_t)want);
     if (e == hipSuccess) e = launch_zero_u32(st.own, (size_t)M.mask_words * (size_t)want, s);
@@ -350,6 +356,7 @@ extern "C" int mg_eval_exact(mg_tree t, void* hip_stream, const int32_t* yaw_bin
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "exact-gain kernels");
+    st.clear = true;
     return MG_OK;
 }
 
@@ -383,5 +390,6 @@ extern "C" int mg_eval_exact_marginal(mg_tree t, void* hip_stream, uint32_t* gai
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "exact marginal gain");
+    st.clear = true;
     return MG_OK;
 }
