@@ -310,8 +310,10 @@ int mg_interval_tables(const mg_sensor* sensor, float voxel_m, int32_t wd, int32
  * ancestor's I (the per-incidence counterpart of the depth-buffer gain),
  * x_set = |I(n) minus the ancestors' I| (may be NULL), a_set = |I(n)| (may be
  * NULL). Synchronises hip_stream twice (windows checked on the host; the call
- * returns after the work). The first call on a tree allocates its sets (a bit
- * per map voxel for each node of its widest level, at most 1 GiB or one node's).
+ * returns after the work). A call allocates the sets that it needs and the device
+ * does not hold yet (a bit per map voxel for each node of the tree's widest level,
+ * at most 1 GiB or one node's; calls of different trees share them and wait for
+ * one another), freed with the last tree that used them.
  * It overwrites the tree's path masks. MG_E_INVALID for a window outside
  * [0, yaw_bins). */
 int mg_eval_exact(mg_tree tree, void* hip_stream, const int32_t* yaw_bin, uint32_t* x_ray, uint32_t* x_set,

@@ -30,6 +30,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <set>
 #include <vector>
 
 #include "mg_batch.h"
@@ -230,52 +231,57 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
     }
 }
 
-// Per-tree device state: own sets of up to `nodes` nodes, all clear between calls
-// but after one that failed, whose voxels may still be in them.
+// Own sets of one device, which its trees' calls take in turn (they hold the lock
+// and return after the work): all clear between calls but after one that failed,
+// whose voxels may still be in them. Freed with the last tree that used them.
 struct State {
     uint32_t* own = nullptr;
-    int32_t nodes = 0;
+    size_t words = 0;
     bool clear = false;
+    std::set<mg_tree> users;
 };
 
 std::mutex g_mu;
-std::map<mg_tree, State> g_state;
+std::map<int, State> g_state;                    // by device
 
 int fail_hip(hipError_t e, const char* what) {
     return mgb::set_error(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, what);
 }
 
-// Own sets for the widest of the levels' lists, at most kPoolBytes of them, for a
-// call that says itself when it has left them clear.
-int own_sets(State& st, const MapDev& M, const std::vector<int32_t>& level_ptr, hipStream_t s) {
+// Own sets for the widest of the levels' lists (*nodes of them), at most kPoolBytes,
+// for a call that says itself when it has left them clear.
+int own_sets(State& st, mg_tree t, const MapDev& M, const std::vector<int32_t>& level_ptr, hipStream_t s, int32_t* nodes) {
     int32_t want = 1;
     for (size_t d = 0; d + 1 < level_ptr.size(); ++d) want = std::max(want, level_ptr[d + 1] - level_ptr[d]);
-    const size_t bytes = sizeof(uint32_t) * (size_t)M.mask_words;
-    want = (int32_t)std::min<size_t>((size_t)want, std::max<size_t>(1, kPoolBytes / bytes));
-    if (want <= st.nodes && st.clear) {
+    want = (int32_t)std::min<size_t>((size_t)want, std::max<size_t>(1, kPoolBytes / (sizeof(uint32_t) * (size_t)M.mask_words)));
+    const size_t words = (size_t)M.mask_words * (size_t)want;
+    st.users.insert(t);
+    *nodes = want;
+    if (words <= st.words && st.clear) {
         st.clear = false;
         return MG_OK;
     }
     (void)hipFree(st.own);                       // (after the work of a call that failed)
-    st = State();
-    hipError_t e = mgb::device_alloc(&st.own, bytes * (size_t)want);
-    if (e == hipSuccess) e = launch_zero_u32(st.own, (size_t)M.mask_words * (size_t)want, s);
+    st.own = nullptr;
+    st.words = 0;
+    hipError_t e = mgb::device_alloc(&st.own, sizeof(uint32_t) * words);
+    if (e == hipSuccess) e = launch_zero_u32(st.own, words, s);
     if (e != hipSuccess) {
         (void)hipFree(st.own);
-        st = State();
+        st.own = nullptr;
         return fail_hip(e, "exact-gain sets");
     }
-    st.nodes = want;
+    st.words = words;
     return MG_OK;
 }
 
-// Own sets, counts and unions of the listed nodes (of one level), as many at a time as the pool holds.
-hipError_t merge_level(const State& st, const mgb::TreeView& v, const int32_t* nodes, int32_t n, const int32_t* yaw,
+// Own sets, counts and unions of the listed nodes (of one level), as many at a time as there are sets (held).
+hipError_t merge_level(const State& st, int32_t held, const mgb::TreeView& v, const int32_t* nodes, int32_t n, const int32_t* yaw,
                        uint32_t* a_set, uint32_t* x_set, hipStream_t s) {
     const SensorDev& S = *v.sd;
     const int32_t chunks = (int32_t)((v.map->build_slots + kMergeThreads - 1) / kMergeThreads);
-    for (int32_t at = 0; at < n; at += st.nodes) {
-        const int32_t cnt = std::min(st.nodes, n - at);
+    for (int32_t at = 0; at < n; at += held) {
+        const int32_t cnt = std::min(held, n - at);
         const int64_t waves = (int64_t)cnt * ((S.WB + kRayBlockCols - 1) / kRayBlockCols) * S.nrb;
         int seg = 8;
         while (seg > 1 && waves * seg > kSetWaves) seg >>= 1;
@@ -307,10 +313,14 @@ hipError_t merge_level(const State& st, const mgb::TreeView& v, const int32_t* n
 namespace mgb {
 void forget_exact(mg_tree t) {
     std::lock_guard<std::mutex> lk(mgx::g_mu);
-    auto it = mgx::g_state.find(t);
-    if (it == mgx::g_state.end()) return;
-    (void)hipFree(it->second.own);
-    mgx::g_state.erase(it);
+    for (auto& d : mgx::g_state) {
+        mgx::State& st = d.second;
+        if (st.users.erase(t) == 0 || !st.users.empty()) continue;
+        (void)hipFree(st.own);
+        st.own = nullptr;
+        st.words = 0;
+        st.clear = false;
+    }
 }
 }  // namespace mgb
 
@@ -339,9 +349,10 @@ extern "C" int mg_eval_exact(mg_tree t, void* hip_stream, const int32_t* yaw_bin
             if (k[i] < 0 || k[i] >= S.B) return mgb::set_error(MG_E_INVALID, "a window index is outside [0, yaw_bins)");
     }
     std::lock_guard<std::mutex> lk(g_mu);
-    State& st = g_state[t];
+    State& st = g_state[dev];
+    int32_t held = 0;
     const bool sets = x_set || a_set;        // (without them only a union of ancestors is asked for)
-    rc = own_sets(st, *v.map, sets ? *v.level_ptr : *v.mask_level_ptr, s);
+    rc = own_sets(st, t, *v.map, sets ? *v.level_ptr : *v.mask_level_ptr, s, &held);
     if (rc != MG_OK) return rc;
     e = launch_zero_u32(x_ray, (size_t)n, s);
     if (e == hipSuccess && x_set) e = launch_zero_u32(x_set, (size_t)n, s);
@@ -351,8 +362,8 @@ extern "C" int mg_eval_exact(mg_tree t, void* hip_stream, const int32_t* yaw_bin
         const int32_t mb = (*v.mask_level_ptr)[d], mcnt = (*v.mask_level_ptr)[d + 1] - mb;
         e = launch_trace_window(*v.map, S, Tr, Tr.level_nodes + b, cnt, yaw_bin, x_ray, sets, s);
         if (e == hipSuccess)
-            e = sets ? merge_level(st, v, Tr.level_nodes + b, cnt, yaw_bin, a_set, x_set, s)
-                     : merge_level(st, v, Tr.mask_nodes + mb, mcnt, yaw_bin, nullptr, nullptr, s);
+            e = sets ? merge_level(st, held, v, Tr.level_nodes + b, cnt, yaw_bin, a_set, x_set, s)
+                     : merge_level(st, held, v, Tr.mask_nodes + mb, mcnt, yaw_bin, nullptr, nullptr, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "exact-gain kernels");
@@ -374,8 +385,9 @@ extern "C" int mg_eval_exact_marginal(mg_tree t, void* hip_stream, uint32_t* gai
     const SensorDev& S = *v.sd;
     const TreeDev& Tr = *v.td;
     std::lock_guard<std::mutex> lk(g_mu);
-    State& st = g_state[t];
-    rc = own_sets(st, *v.map, *v.mask_level_ptr, s);
+    State& st = g_state[dev];
+    int32_t held = 0;
+    rc = own_sets(st, t, *v.map, *v.mask_level_ptr, s, &held);
     if (rc != MG_OK) return rc;
     // level by level: new incidences per bin, window, then the set at that window
     e = launch_zero_u32(Tr.bins, (size_t)S.B * v.n, s);
@@ -386,7 +398,7 @@ extern "C" int mg_eval_exact_marginal(mg_tree t, void* hip_stream, uint32_t* gai
         e = launch_trace(*v.map, S, Tr, nodes, cnt, true, false, s);
         if (e == hipSuccess) e = launch_finish(S, Tr, nodes, cnt, true, gain, yaw_bin, s);
         if (e == hipSuccess)
-            e = merge_level(st, v, Tr.mask_nodes + mb, mcnt, (const int32_t*)yaw_bin, nullptr, nullptr, s);
+            e = merge_level(st, held, v, Tr.mask_nodes + mb, mcnt, (const int32_t*)yaw_bin, nullptr, nullptr, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "exact marginal gain");

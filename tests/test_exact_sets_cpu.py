@@ -40,3 +40,27 @@ assert F.fake_dirty() == 0
 {CALLS[call]}
 assert F.fake_dirty() == 0
 """)
+
+
+def test_trees_share_a_devices_sets():
+    """Trees on maps of different sizes take the sets in turn: one allocation per device, as large as the
+    largest call needs, freed with the last of these trees."""
+    check("""
+m, small = new_map((200, 200, 60)), new_map()
+g, y = Out(512), Out(512)
+big = new_tree(m, 200, star=True)
+others = [new_tree(small, n, star=True) for n in (30, 90, 200)] + [new_tree(m, n, star=True) for n in (3, 150)]
+mg.mg_eval_exact_marginal(big, g, y, stream=0)
+mg.mg_eval_exact(big, y, g, Out(512), Out(512), stream=0)
+before = F.fake_live(0)
+for t in others + [big]:
+    mg.mg_eval_exact(t, y, g, Out(512), Out(512), stream=0)
+    mg.mg_eval_exact_marginal(t, g, y, stream=0)
+assert F.fake_live(0) == before and F.fake_dirty() == 0
+assert F.fake_held(0, 199 * 25 * 25 * 8 * 64) >= 199 * 25 * 25 * 8 * 64
+for t in [big] + others[:-1]:
+    mg.mg_tree_destroy(t)
+held = F.fake_held(0, 199 * 25 * 25 * 8 * 64)
+mg.mg_tree_destroy(others[-1])
+assert F.fake_held(0, 199 * 25 * 25 * 8 * 64) < held
+""")
