@@ -312,7 +312,7 @@ int mg_interval_tables(const mg_sensor* sensor, float voxel_m, int32_t wd, int32
  * NULL). Synchronises hip_stream twice (windows checked on the host; the call
  * returns after the work). A call allocates the sets that it needs and the device
  * does not hold yet (a bit per map voxel for each node of the tree's widest level,
- * at most 1 GiB or one node's; calls of different trees share them and wait for
+ * at most 1 GiB or one node's, fewer where device memory is short; calls of different trees share them and wait for
  * one another), freed with the last tree that used them.
  * It overwrites the tree's path masks. MG_E_INVALID for a window outside
  * [0, yaw_bins). */

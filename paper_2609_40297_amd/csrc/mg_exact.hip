@@ -237,6 +237,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
 struct State {
     uint32_t* own = nullptr;
     size_t words = 0;
+    size_t asked = 0;                            // words a call wanted when they were allocated: more than `words` if memory was short
     bool clear = false;
     std::set<mg_tree> users;
 };
@@ -248,30 +249,38 @@ int fail_hip(hipError_t e, const char* what) {
     return mgb::set_error(e == hipErrorOutOfMemory ? MG_E_NOMEM : MG_E_DEVICE, what);
 }
 
-// Own sets for the widest of the levels' lists (*nodes of them), at most kPoolBytes,
-// for a call that says itself when it has left them clear.
+// Own sets for the widest of the levels' lists (*nodes of them), at most kPoolBytes
+// and fewer where device memory is short, for a call that says itself when it has
+// left them clear.
 int own_sets(State& st, mg_tree t, const MapDev& M, const std::vector<int32_t>& level_ptr, hipStream_t s, int32_t* nodes) {
-    int32_t want = 1;
-    for (size_t d = 0; d + 1 < level_ptr.size(); ++d) want = std::max(want, level_ptr[d + 1] - level_ptr[d]);
-    want = (int32_t)std::min<size_t>((size_t)want, std::max<size_t>(1, kPoolBytes / (sizeof(uint32_t) * (size_t)M.mask_words)));
-    const size_t words = (size_t)M.mask_words * (size_t)want;
+    const size_t per = M.mask_words;
+    size_t want = 1;
+    for (size_t d = 0; d + 1 < level_ptr.size(); ++d) want = std::max(want, (size_t)(level_ptr[d + 1] - level_ptr[d]));
+    want = std::min(want, std::max<size_t>(1, kPoolBytes / (sizeof(uint32_t) * per)));
     st.users.insert(t);
-    *nodes = want;
-    if (words <= st.words && st.clear) {
+    if (st.clear && st.words >= per && std::max(st.words, st.asked) >= per * want) {
+        *nodes = (int32_t)std::min(want, st.words / per);
         st.clear = false;
         return MG_OK;
     }
+    st.clear = false;
     (void)hipFree(st.own);                       // (after the work of a call that failed)
     st.own = nullptr;
     st.words = 0;
-    hipError_t e = mgb::device_alloc(&st.own, sizeof(uint32_t) * words);
-    if (e == hipSuccess) e = launch_zero_u32(st.own, words, s);
+    st.asked = per * want;
+    hipError_t e = mgb::device_alloc(&st.own, sizeof(uint32_t) * per * want);
+    while (e == hipErrorOutOfMemory && want > 1) {
+        want = (want + 1) / 2;
+        e = mgb::device_alloc(&st.own, sizeof(uint32_t) * per * want);
+    }
+    if (e == hipSuccess) e = launch_zero_u32(st.own, per * want, s);
     if (e != hipSuccess) {
         (void)hipFree(st.own);
         st.own = nullptr;
         return fail_hip(e, "exact-gain sets");
     }
-    st.words = words;
+    st.words = per * want;
+    *nodes = (int32_t)want;
     return MG_OK;
 }
 

@@ -64,3 +64,37 @@ held = F.fake_held(0, 199 * 25 * 25 * 8 * 64)
 mg.mg_tree_destroy(others[-1])
 assert F.fake_held(0, 199 * 25 * 25 * 8 * 64) < held
 """)
+
+
+def test_sets_of_fewer_nodes_where_memory_is_short():
+    """Device memory for the sets of a few nodes only: the call takes the level in parts, and the next one
+    does not ask for more again."""
+    check("""
+m = new_map((200, 200, 60))
+t = new_tree(m, 200, star=True)
+g, xs, a, y = Out(512), Out(512), Out(512), Out(512, np.int32)
+F.fake_limit(0, F.fake_live(0) + 5 * 25 * 25 * 8 * 64)
+mg.mg_eval_exact(t, y, g, xs, a, stream=0)
+before = F.fake_mallocs()
+mg.mg_eval_exact(t, y, g, xs, a, stream=0)
+mg.mg_eval_exact_marginal(t, g, y, stream=0)
+assert F.fake_mallocs() == before and F.fake_dirty() == 0
+mg.mg_tree_destroy(t)
+t = new_tree(m, 5)
+F.fake_limit(0, 1)                                 # (not even one node's)
+assert code(mg.mg_eval_exact, t, y, g, xs, a, stream=0) == mg.MG_E_NOMEM
+""")
+
+
+def test_sets_are_clear_after_a_first_call_of_a_larger_tree_that_failed():
+    check("""
+m = new_map()
+g, y = Out(512), Out(512)
+t, wide = new_tree(m, 30), new_tree(m, 200, star=True)
+mg.mg_eval_exact_marginal(t, g, y, stream=0)
+F.fake_fail_kernel(b"k_exact_merge", 1)
+assert code(mg.mg_eval_exact, wide, y, g, Out(512), Out(512), stream=0) == mg.MG_E_DEVICE
+mg.mg_eval_exact(wide, y, g, Out(512), Out(512), stream=0)
+mg.mg_eval_exact_marginal(t, g, y, stream=0)
+assert F.fake_dirty() == 0
+""")
