@@ -155,9 +155,14 @@ __device__ __forceinline__ uint32_t code_of_words(const uint32_t (&q)[16]) {
 // Merges each listed node's own set with its parent's union, a thread per brick
 // (in blocks of 2x2x2 bricks, as the mask builder visits them): counts (may be
 // null) and, for a node with children, its union and code words, of which only
-// what can be read is written (mg_internal.h). The own set is left clear.
+// what can be read is written (mg_internal.h). The own set is left clear. Bricks
+// that the node's rays cannot reach hold nothing of its set, which is not read there
+// (and a leaf has no union to write there): 300 nodes, 128 x 24 rays of 50 voxels, on a
+// 1024 x 1024 x 200 grid, the three counts at given windows: 1715 -> 808 us (1225 with
+// the hash sets, whose cost did not grow with the grid); 500 nodes of rays that reach
+// most of their grid (200 x 200 x 60): 1166 and 1166 us.
 __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev Tr, const int32_t* __restrict__ nodes,
-                                                               int32_t chunks, uint32_t* __restrict__ own,
+                                                               int32_t chunks, float rv, uint32_t* __restrict__ own,
                                                                uint32_t* __restrict__ a_set,
                                                                uint32_t* __restrict__ x_set) {
     const int32_t item = (int32_t)(blockIdx.x / (uint32_t)chunks);
@@ -170,7 +175,14 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
     const uint32_t bx = at.x, by = at.y, bz = at.z;
     const bool in_map = bx < M.mbx && by < M.mby && bz < M.mbz;
     const uint32_t b = in_map ? bx + M.mbx * (by + M.mby * bz) : 0u;
-    const uint32_t bu = in_map ? (M.brick_unk[b] & 3u) : (uint32_t)kBrickKnown;
+    // distance of the brick's box from the node: a voxel entered before the range lies
+    // within it but for rounding, far below the voxel added
+    const float4 p = Tr.q4[node];
+    const float x0 = (float)(8u * bx), y0 = (float)(8u * by), z0 = (float)(8u * bz);
+    const float dx = fmaxf(fmaxf(x0 - p.x, p.x - (x0 + 8.f)), 0.f), dy = fmaxf(fmaxf(y0 - p.y, p.y - (y0 + 8.f)), 0.f),
+                dz = fmaxf(fmaxf(z0 - p.z, p.z - (z0 + 8.f)), 0.f);
+    const bool reach = dx * dx + dy * dy + dz * dz <= (rv + 1.f) * (rv + 1.f);
+    const uint32_t bu = in_map & (reach | (slot >= 0)) ? (M.brick_unk[b] & 3u) : (uint32_t)kBrickKnown;
     uint32_t cw = 0u, members = 0u, fresh = 0u;
     if (bu != kBrickKnown) {
         uint32_t q[16];
@@ -178,7 +190,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
         uint32_t any = 0u;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const uint4 v = o[k];
+            const uint4 v = reach ? o[k] : make_uint4(0u, 0u, 0u, 0u);
             q[4 * k] = v.x; q[4 * k + 1] = v.y; q[4 * k + 2] = v.z; q[4 * k + 3] = v.w;
             any |= v.x | v.y | v.z | v.w;
         }
@@ -191,11 +203,11 @@ __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev
         }
         // (a brick the node adds nothing to keeps the parent's code, and its words where they can be read)
         if (any != 0u || (slot >= 0 && (pc == kMaskMixed || bu == kBrickSomeUnknown))) {
-            const uint4* p = reinterpret_cast<const uint4*>(Tr.masks + (size_t)(ps >= 0 ? ps : 0) * M.mask_words + (size_t)b * 16u);
+            const uint4* par = reinterpret_cast<const uint4*>(Tr.masks + (size_t)(ps >= 0 ? ps : 0) * M.mask_words + (size_t)b * 16u);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t u = pc == kMaskAll ? ~0u : 0u;
-                const uint4 v = pc == kMaskMixed ? p[k] : make_uint4(u, u, u, u);
+                const uint4 v = pc == kMaskMixed ? par[k] : make_uint4(u, u, u, u);
                 const uint32_t pv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -310,7 +322,7 @@ hipError_t merge_level(const State& st, int32_t held, const mgb::TreeView& v, co
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_exact_merge, dim3((unsigned)cnt * (unsigned)chunks), dim3(kMergeThreads), 0, s, *v.map,
-                           *v.td, nodes + at, chunks, st.own, a_set, x_set);
+                           *v.td, nodes + at, chunks, S.rv, st.own, a_set, x_set);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
