@@ -154,13 +154,15 @@ __global__ void k_map_scatter(const uint32_t* __restrict__ ids, const uint8_t* _
 // one (by, bz), read in 16-byte loads (the run is contiguous) into LDS and written
 // row by row, kBytes (8, 4 or 1, as the rows' alignment allows) per thread. Bound
 // by HBM: 1 B read and 1 B written a voxel. 512 x 512 x 128: 14 us, 4.8 TB/s; a
-// byte per thread, its address found by two divisions: 78 us.
+// byte per thread, its address found by two divisions: 78 us. A launch of fewer than
+// kReadFill workgroups (two per CU) takes shorter runs, down to 4 bricks: 129 x 127 x 48,
+// 96 workgroups of 32 bricks, 24.2 us a call; 480 of 4 bricks, 20.8 (20.6 the other way).
+constexpr uint64_t kReadFill = 512;
 constexpr int kRowBrick = 528;      // LDS stride of a brick: rows of neighbouring bricks in other banks
 template <int kBytes>
-__global__ __launch_bounds__(256) void k_unbrick(const uint8_t* __restrict__ bricks, MapDev m,
+__global__ __launch_bounds__(256) void k_unbrick(const uint8_t* __restrict__ bricks, MapDev m, int32_t tb,
                                                  uint8_t* __restrict__ dense, uint32_t keep) {
     __shared__ __align__(16) uint8_t tile[kTileBricks * kRowBrick];
-    const int32_t tb = m.nbx < kTileBricks ? m.nbx : kTileBricks;   // (nbx is a power of two)
     const int32_t bx0 = (int32_t)blockIdx.x * tb, by = (int32_t)blockIdx.y, bz = (int32_t)blockIdx.z;
     const int32_t tid = (int32_t)threadIdx.x;
     const size_t base = ((size_t)bx0 + (size_t)m.nbx * ((size_t)by + (size_t)m.nby * (size_t)bz)) * 512u;
@@ -241,16 +243,18 @@ hipError_t launch_map_scatter(const uint32_t* ids, const uint8_t* states, uint32
 }
 
 hipError_t launch_unbrick(const MapDev& m, uint8_t* dense, hipStream_t s, bool marks) {
-    const int32_t tb = m.nbx < kTileBricks ? m.nbx : kTileBricks;
+    // bricks a workgroup: fewer while the launch would leave CUs idle
+    int32_t tb = m.nbx < kTileBricks ? m.nbx : kTileBricks;         // (nbx is a power of two)
+    while (tb > 4 && (uint64_t)((m.mbx + (uint32_t)tb - 1u) / (uint32_t)tb) * m.mby * m.mbz < kReadFill) tb >>= 1;
     const dim3 grid(((unsigned)m.mbx + (unsigned)tb - 1u) / (unsigned)tb, m.mby, m.mbz);
     const uint32_t keep = marks ? 0xffu : 3u;
     // (rows start at multiples of nx from dense: a piece never straddles a row's end)
     if (m.nx % 8 == 0 && (uintptr_t)dense % 8 == 0)
-        hipLaunchKernelGGL(k_unbrick<8>, grid, dim3(256), 0, s, m.bricks, m, dense, keep);
+        hipLaunchKernelGGL(k_unbrick<8>, grid, dim3(256), 0, s, m.bricks, m, tb, dense, keep);
     else if (m.nx % 4 == 0 && (uintptr_t)dense % 4 == 0)
-        hipLaunchKernelGGL(k_unbrick<4>, grid, dim3(256), 0, s, m.bricks, m, dense, keep);
+        hipLaunchKernelGGL(k_unbrick<4>, grid, dim3(256), 0, s, m.bricks, m, tb, dense, keep);
     else
-        hipLaunchKernelGGL(k_unbrick<1>, grid, dim3(256), 0, s, m.bricks, m, dense, keep);
+        hipLaunchKernelGGL(k_unbrick<1>, grid, dim3(256), 0, s, m.bricks, m, tb, dense, keep);
     return hipGetLastError();
 }
 

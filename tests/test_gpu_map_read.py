@@ -50,3 +50,14 @@ def test_marks_of_blocks(mg, dims):
     M = mg.Map(st, 1.0, (0.0, 0.0, 0.0))
     assert np.array_equal(M.read_marked().cpu().numpy(), _expected_marks(st))
     M.close()
+
+
+@pytest.mark.parametrize("dims", [(129, 127, 48), (257, 176, 190), (260, 121, 100), (264, 100, 72)])
+def test_read_back_of_larger_grids(mg, dims):
+    """Workgroups of 4, 32, 16 and 8 bricks (the most that leave the chip full), rows of odd and even widths."""
+    rng = np.random.Generator(np.random.PCG64(sum(dims)))
+    st = rng.integers(0, 3, dims[::-1]).astype(np.uint8)
+    M = mg.Map(st, 1.0, (0.0, 0.0, 0.0))
+    log(f"[read] {dims}")
+    assert np.array_equal(M.read().cpu().numpy(), st)
+    M.close()
