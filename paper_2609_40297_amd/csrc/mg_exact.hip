@@ -162,9 +162,9 @@ __device__ __forceinline__ uint32_t code_of_words(const uint32_t (&q)[16]) {
 // the hash sets, whose cost did not grow with the grid); 500 nodes of rays that reach
 // most of their grid (200 x 200 x 60): 1166 and 1166 us.
 __global__ __launch_bounds__(kMergeThreads) void k_exact_merge(MapDev M, TreeDev Tr, const int32_t* __restrict__ nodes,
-                                                               int32_t chunks, float rv, uint32_t* __restrict__ own,
+                                                               int32_t chunks, uint32_t* __restrict__ own,
                                                                uint32_t* __restrict__ a_set,
-                                                               uint32_t* __restrict__ x_set) {
+                                                               uint32_t* __restrict__ x_set, float rv) {
     const int32_t item = (int32_t)(blockIdx.x / (uint32_t)chunks);
     const uint32_t sl = (blockIdx.x - (uint32_t)item * (uint32_t)chunks) * kMergeThreads + threadIdx.x;
     const int32_t node = nodes[item];
@@ -322,7 +322,7 @@ hipError_t merge_level(const State& st, int32_t held, const mgb::TreeView& v, co
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_exact_merge, dim3((unsigned)cnt * (unsigned)chunks), dim3(kMergeThreads), 0, s, *v.map,
-                           *v.td, nodes + at, chunks, S.rv, st.own, a_set, x_set);
+                           *v.td, nodes + at, chunks, st.own, a_set, x_set, S.rv);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
