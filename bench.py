@@ -19,7 +19,7 @@ Modes
            every level.
   batched  the whole request in one call (mg_eval_marginal_batch), one copy
            of the results at the end; per depth level a trace, a window and a
-           mask-builder launch on three stream groups.
+           mask-builder launch, on three stream groups unless the batch is small.
   graph    the same call with the plan's launches recorded once into a HIP
            graph and replayed (mg_batch_config(-1, 1)).
   persistent  the same call configured as one cooperative launch per step
@@ -561,8 +561,10 @@ def roofline_of(wc, trace, steps, n_total, yaw_bins, ms_per_step, traffic):
     busy = trace["busy_ms"] / steps                 # union of the trace and builder launch intervals
     summed = trace["total_ms"] / steps              # their summed durations (groups overlap on their streams)
     achieved = alg_step / (busy * 1e-3) / 1e9
-    return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    return {"bound": "issue", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
+            "achieved_is": "the method's algorithmic bytes over the kernels' time; most of them are never read, so this "
+                           "is no HBM bandwidth (traffic over busy_ms_per_step is)",
             "traffic_unit": "HBM bytes per step of the trace and mask-builder dispatches (rocprofv3 FETCH_SIZE + "
                             "WRITE_SIZE, each scaled by what it reads for a plain device copy)",
             "kernels": ["k_trace_multi", "k_mask_build_multi"],

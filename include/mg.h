@@ -228,7 +228,8 @@ int mg_score_branches(const mg_tree* trees, int32_t n_trees, void* hip_stream, c
  *          shape, and blocks until done; 0 .. count-1 = that shape
  *          (mg_trace_shapes).
  *   launch: 0 (default) = per depth level a trace, a window and a mask-builder
- *          launch, on three stream groups; 1 = those launches recorded once
+ *          launch, on three stream groups or, for a batch of little work, on
+ *          hip_stream alone; 1 = those launches recorded once
  *          into a HIP graph that each call replays (on a library stream joined
  *          to hip_stream by events before and after); 2 = one persistent
  *          cooperative launch per call (Sec. IV-C's level order over all trees:
@@ -435,8 +436,10 @@ int mg_timing_enable(int32_t on);
 /* Waits for the timed launches since the last read, returns the sum of their
  * durations (ms), the union of their intervals (ms during which at least one
  * ran: launches of different groups of a batch plan overlap), their number
- * and the workgroups the trace launches ran (any pointer may be NULL), and
- * resets the sums.
+ * and the node tiles of the trace launches (per node, the workgroups that the
+ * plan's launch shape takes with one lane a ray; a launch that gives a ray to
+ * several lanes runs more, smaller ones) (any pointer may be NULL), and resets
+ * the sums.
  * At most 65536 launches may be timed between two reads (MG_E_BUSY from the
  * launch call beyond that). */
 int mg_timing_read(double* total_ms, double* busy_ms, int64_t* launches, int64_t* workgroups);

@@ -74,7 +74,10 @@ struct Plan {
 
 // Configuration for plans built from now on (mg_batch_config).
 int g_cfg_shape = -1;                      // -1: autotune
-bool g_cfg_graph = false;                  // replaying a graph measured slower than direct launches
+// Off: a graph holds its output buffers and is captured anew for others. With the
+// same ones it saves short levels their launches (a 500-node tree of split levels
+// 1.15 ms replayed, 1.36 launched one by one) and is even on large batches.
+bool g_cfg_graph = false;
 bool g_cfg_persistent = false;             // one persistent cooperative launch per call
 uint32_t g_barrier_polls = 1u << 25;       // polls of a grid-barrier wait before it gives up (seconds)
 // Autotuned shapes per workload shape (sensor, range, map dims, sizes).
@@ -98,7 +101,10 @@ constexpr int32_t kGroups = 3;             // independent groups of a plan, one 
 // share grows with them, and overlaps other groups' traces). One tree, whole and
 // split: 20 nodes 79 and 198 us (64 x 64 x 32 grid), 100 nodes 363 and 412, 300
 // (8.3e6) 668 and 717, 500 (13.8e6) 924 and 888 (200 x 200 x 60 grid, 5408 slots);
-// 20 nodes 545 and 393 on a 512 x 512 x 128 grid (65536 slots).
+// 20 nodes 545 and 393 on a 512 x 512 x 128 grid (65536 slots). These are single
+// trees of one sensor each, alone in their process: where the streams' queues are
+// shared with other work, split plans lose more (the 500 nodes in a process with
+// many streams 1.13 ms level by level, 2.13 split).
 constexpr double kWholeWork = 8388608.0;
 constexpr uint32_t kWholeSlots = 16384;
 
@@ -321,7 +327,7 @@ struct Timing {
     int device = -1;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev;
     size_t used = 0;
-    int64_t units = 0;                     // workgroups (node tiles) launched while timed
+    int64_t units = 0;                     // node tiles of the launches while timed, with one lane a ray
 };
 Timing g_timing;
 constexpr size_t kMaxTimedLaunches = 1u << 16;

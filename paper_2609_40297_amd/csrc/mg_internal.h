@@ -103,22 +103,21 @@ __device__ __forceinline__ uint8_t brick_summary(bool any_unk, bool all_unk, boo
                      (all_free ? kBrickAllFree : 0));
 }
 
-// Occupancy grid in 8x8x8-voxel bricks (512 B each, x fastest inside a
-// brick, bricks x fastest): a ray stays inside one brick for several steps,
-// so its gathers hit few cache lines. Brick counts are powers of two with at
-// least one padding voxel past the grid on every axis, so a voxel's byte
-// address is a bit-field merge of its coordinates; coordinate -1 wraps to the
-// last padding voxel of its axis, which holds kOutside like all padding.
 // Division by a count that the host knows, exact for every n: `mul` falls short of
 // 2^32 / d by less than 1, so the product's high word is the quotient or one less. (A
-// variable divisor costs a wave some 30 instructions before its first step: 500
-// nodes 895 us with those, 885 without.)
+// variable divisor costs a wave some 30 instructions before its first step.)
 inline uint32_t divisor_mul(uint32_t d) { return d > 1u ? (uint32_t)((1ull << 32) / d) : ~0u; }
 __device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint32_t mul) {
     const uint32_t q = __umulhi(n, mul);
     return q + (n - q * d >= d ? 1u : 0u);
 }
 
+// Occupancy grid in 8x8x8-voxel bricks (512 B each, x fastest inside a
+// brick, bricks x fastest): a ray stays inside one brick for several steps,
+// so its gathers hit few cache lines. Brick counts are powers of two with at
+// least one padding voxel past the grid on every axis, so a voxel's byte
+// address is a bit-field merge of its coordinates; coordinate -1 wraps to the
+// last padding voxel of its axis, which holds kOutside like all padding.
 struct MapDev {
     const uint8_t* bricks;
     int32_t nx, ny, nz;     // true extent in voxels
@@ -192,7 +191,11 @@ __device__ __forceinline__ uint3 slot_brick(uint32_t sl, const MapDev& M) {
 // of T is not in doubt, and the nearest one is decided by its own parameter,
 // computed as the single step computes it. (A boundary the ray starts on or has
 // passed is never crossed again: the coordinate does not fall.) A single voxel is
-// the same step with edge 1.
+// the same step with edge 1. Where states change from voxel to voxel and no block
+// is marked, that is more work than a step of one axis: 200 nodes on states drawn
+// voxel by voxel, the absolute pass, 412 us with a single-voxel step of its own and
+// 640 so (with ancestors 1306 and 1385); a branch for waves of single voxels takes
+// 535 and 1267 there and 1 to 3 % longer on maps of rooms and walls.
 struct RayWalk {
     int32_t mx, my, mz;      // 0, or ~0 on an axis the ray moves down
     float qx, qy, qz;        // the node, mirrored
@@ -307,7 +310,7 @@ struct TreeDev {
     int32_t* c0;               // [n]
     uint32_t* masks;           // [nodes with children][mask_words]
     const int2* mask_slot;     // [n] index into masks: the node's (-1 for a leaf) and its parent's (-1 for the root);
-                               // side by side: found through the ancestor list the parent's took three dependent loads (500 nodes 907 us, 895 so)
+                               // side by side: found through the ancestor list the parent's took three dependent loads
     const int32_t* mask_nodes; // nodes with children, by depth level
     float* tmax;               // [nodes with children][2][n_tiles]: largest, then smallest first hit of each tile of the window
     uint32_t* mcode;           // [nodes with children][mask bricks]: code words

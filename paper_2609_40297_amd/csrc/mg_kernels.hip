@@ -133,8 +133,9 @@ __device__ __forceinline__ bool left_of(float2 b, float rx, float ry) { return b
 // this permutation of the grid gives each XCD runs of kRun consecutive work
 // units (neighbouring pixel blocks, or bricks, of one node) while the runs
 // still alternate over the whole grid; the grid's last partial round keeps
-// the identity. Runs of 8 in the per-tree trace: 500 nodes 886 us in plain order,
-// 876 (16 and 64: 879 and 886); its builder gains nothing. Multi-tree launches take
+// the identity. Runs of 8 in the per-tree trace: 500 nodes 893 to 898 us in plain
+// order, 881 to 889 so, 333 odd ones 638 to 643 and 624 to 634 (four processes each;
+// runs of 16 and 64 are within that spread); its builder gains nothing. Multi-tree launches take
 // 16 (128.9 ms against 136 in plain order, 24000 nodes).
 constexpr uint32_t kTreeRun = 8, kBatchRun = 16;
 template <uint32_t kRun>
@@ -246,7 +247,7 @@ __device__ int brick_view(const SensorDev& S, const float* __restrict__ tm, floa
     const float per_row = 1.0f / (float)rows;
     for (int32_t k = g; k < tiles; k += 4 * kLanes) {
 #pragma unroll
-        for (int32_t e = 0; e < 4; ++e) {                    // four tiles' loads in flight (500 nodes: 921 us one by one, 910)
+        for (int32_t e = 0; e < 4; ++e) {                    // four tiles' loads in flight (500 nodes, four processes: 896 to 900 us one by one, 881 to 889)
             const int32_t t = min(k + e * kLanes, tiles - 1);
             const int32_t c = (int32_t)(((float)t + 0.5f) * per_row);   // t / rows: t < 64
             const int32_t at = (tc0 + c) * S.trows + tr0 + (t - c * rows);
@@ -1311,9 +1312,9 @@ static int32_t build_bricks(uint32_t slots, int32_t n_nodes, int32_t most) {
 // once even with a wave per brick (1024 of 8 waves fill the chip): bound by one
 // workgroup's chain of loads, so each brick gets a wave of its own, 8 lanes share
 // a brick's view, and the tables are requested at the start, needed or not. 20
-// nodes in 4 levels (up to 160 workgroups a launch): 86.7 us with four waves,
-// 77.2 us (lanes 16 or 1024 threads: 77.7 and 77.2); 500 nodes, of whose levels
-// one is that small: 910 and 908. Larger launches lose by it: with chunks of up
+// nodes in 4 levels (up to 160 workgroups a launch): 109 to 112 us with four waves,
+// 97 to 104 so (four processes each; lanes 16 or 1024 threads are even); 500 nodes,
+// of whose levels one is that small, are even (887 and 884). Larger launches lose by it: with chunks of up
 // to 16 and 32 bricks in 8 waves the 500 nodes take 954 and 971 us against 920.
 constexpr uint64_t kFewChunks = 1024;
 static bool few_chunks(uint64_t chunks, int32_t bricks) { return bricks == 8 && chunks <= kFewChunks; }
@@ -1337,8 +1338,9 @@ hipError_t launch_mask_build(const MapDev& m, const SensorDev& sd, const TreeDev
 
 // Workgroups that share a node's window selection: one tile a thread, while the
 // launch stays within kFinishFill workgroups. 500 nodes of 345 tiles (two
-// workgroups for levels of up to 512): 926 us with one each, 920 us; up to 4096
-// workgroups gains nothing more and repeats selections that fill the chip anyway
+// workgroups for levels of up to 512): 887 to 893 us with one each, 881 to 889 so,
+// 100 nodes 560 to 562 and 554 to 558 (four processes each), 20 nodes even; up to
+// 4096 workgroups gains nothing more and repeats selections that fill the chip anyway
 // (16 trees of up to 2000 nodes: 8.45 and 8.54 ms).
 constexpr int32_t kFinishFill = 1024;
 static int32_t finish_parts(const SensorDev& sd, int32_t n_items, bool tiles) {
@@ -1501,7 +1503,7 @@ namespace {
 
 template <int kTh>
 void launch_multi(const BatchTree* trees, const unsigned long long* items, int32_t n_items, const SensorDev& sd,
-                  bool depth, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int shape) {
+                  bool depth, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
     const int seg = trace_segments(sd, n_items, sd.W);
     const SensorDev st = trace_sensor(sd, seg, seg > 1 ? 64 : kTh, sd.W);
     const dim3 grid((unsigned)n_items * (unsigned)st.T);
@@ -1526,7 +1528,7 @@ void launch_multi_shape(int shape, const BatchTree* trees, const unsigned long l
                         const SensorDev& sd, bool depth, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
     if constexpr (I < kNumShapes) {
         if (shape == I)
-            launch_multi<kShapes[I].threads>(trees, items, n_items, sd, depth, s, t0, t1, I);
+            launch_multi<kShapes[I].threads>(trees, items, n_items, sd, depth, s, t0, t1);
         else
             launch_multi_shape<I + 1>(shape, trees, items, n_items, sd, depth, s, t0, t1);
     }

@@ -272,7 +272,7 @@ def score_batch(trees, gain, lam=0.5, stream=None):
 
 
 def mg_batch_config(shape: int = -1, launch: int = 0):
-    """launch: 0 launches one by one on stream groups, 1 graph replay, 2 one persistent cooperative launch."""
+    """launch: 0 launches one by one (on stream groups where there is work for them), 1 graph replay, 2 one persistent cooperative launch."""
     _check(lib().mg_batch_config(int(shape), int(launch)))
 
 
@@ -304,7 +304,7 @@ def mg_timing_enable(on: bool):
 
 
 def mg_timing_read():
-    """(summed trace-kernel ms, ms during which one ran, timed launches, workgroups) since the last read."""
+    """(summed trace-kernel ms, ms during which one ran, timed launches, node tiles) since the last read."""
     ms, busy, n, wg = C.c_double(), C.c_double(), C.c_int64(), C.c_int64()
     _check(lib().mg_timing_read(C.byref(ms), C.byref(busy), C.byref(n), C.byref(wg)))
     return ms.value, busy.value, n.value, wg.value
