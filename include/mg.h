@@ -148,8 +148,10 @@ int mg_tree_destroy(mg_tree tree);
 int32_t mg_tree_nodes(mg_tree tree);
 int32_t mg_tree_buffer_pixels(mg_tree tree);
 
-/* Device bytes held by the tree (node data, depth buffers, bins): what an
- * admission controller must reserve for it. */
+/* Device bytes the tree needs (node data, depth buffers, bins): what an
+ * admission controller must reserve for it. A tree uploaded on its own may hold up
+ * to a quarter more, in a block kept for the next tree (mg_tree_destroy), but not
+ * where device memory is short. */
 int64_t mg_tree_footprint_bytes(mg_tree tree);
 
 /* Path-dependent marginal gain of every node (eq. 2 with depth buffers,
