@@ -375,16 +375,29 @@ extern "C" int mg_sensor_tables(const mg_sensor* sensor, float* dir, float* inv,
 
 namespace {
 
+// Sizes in steps of an eighth to a sixteenth of themselves, so that trees of similar size share blocks.
+size_t size_class(size_t bytes) {
+    size_t step = 4096;
+    while (step * 16 <= bytes) step *= 2;
+    return (bytes + step - 1) / step * step;
+}
+
 // Blocks given back by destroyed trees and plans, for the next ones: a replan
 // uploads a tree, evaluates it and drops it, and a hipMalloc and hipFree of tens
 // of megabytes, and rebuilding its sensor's tables, took longer than its host
 // work (500 nodes, 70 MB: upload 966 -> 38 us with blocks and tables kept and one
 // copy instead of ten, drop 391 -> 82 us). Per device, at most kPoolCount blocks of
 // at most kPoolBlock bytes, kPoolHeld bytes in all, those given back longest ago
-// freed first; a block serves its own size class and the next smaller one. The pool
-// is emptied, and idle sensor tables are freed, when the device's last map is
+// freed first; a block serves its own size class and the next smaller one. Giving a
+// block back waits for nothing; it is handed out again after a wait for the device
+// (wait_device). Where only blocks without one would do, the wait is made at the
+// second of these, at kFresh of any size, or where the pool holds kFreshHeld bytes,
+// so that it serves some replans and blocks are not made in its place. The pool is
+// emptied, and idle sensor tables are freed, when the device's last map is
 // destroyed and when any allocation of the library fails (device_alloc).
 constexpr size_t kPoolBlock = size_t(256) << 20, kPoolHeld = size_t(512) << 20, kPoolCount = 1024;
+constexpr int kFresh = 4;
+constexpr size_t kFreshHeld = kPoolHeld / 4;
 struct DevicePool {
     struct Held {
         void* block;
@@ -392,6 +405,7 @@ struct DevicePool {
     };
     std::multimap<size_t, Held> blocks;      // by size class
     uint64_t given = 0;
+    uint64_t done = 0;                       // the device has finished with blocks given back before this count
     size_t held = 0;
     int maps = 0;                            // live maps on the device
     void drain() {
@@ -405,10 +419,33 @@ struct DevicePool {
             auto oldest = blocks.begin();
             for (auto it = blocks.begin(); it != blocks.end(); ++it)
                 if (it->second.since < oldest->second.since) oldest = it;
-            (void)hipFree(oldest->second.block);
+            if (hipFree(oldest->second.block) == hipSuccess)       // (which waits for the device)
+                done = given;
+            else
+                (void)hipGetLastError();
             held -= oldest->first;
             blocks.erase(oldest);
         }
+    }
+    // Takes a block of class `cls` or the next that the device has finished with. At
+    // none, how many would do that it may still use, and whether a wait is due.
+    int take(size_t cls, void** block, size_t* bytes, bool* due) {
+        int fresh = 0, any = 0;
+        for (auto it = blocks.lower_bound(cls); it != blocks.end() && it->first <= size_class(cls + 1); ++it) {
+            if (it->second.since >= done) {
+                ++fresh;
+                continue;
+            }
+            *block = it->second.block;
+            *bytes = it->first;
+            held -= it->first;
+            blocks.erase(it);
+            return 0;
+        }
+        if (fresh > 0)
+            for (const auto& b : blocks) any += b.second.since >= done ? 1 : 0;
+        *due = fresh > 1 || any >= kFresh || held >= kFreshHeld;
+        return fresh;
     }
 };
 constexpr int kPoolDevices = 64;
@@ -421,13 +458,6 @@ struct Pools {
 Pools& pools() {
     static Pools* p = new Pools();
     return *p;
-}
-
-// Sizes in steps of an eighth to a sixteenth of themselves, so that trees of similar size share blocks.
-size_t size_class(size_t bytes) {
-    size_t step = 4096;
-    while (step * 16 <= bytes) step *= 2;
-    return (bytes + step - 1) / step * step;
 }
 
 int count_map(int device, int delta) {
@@ -470,40 +500,51 @@ hipError_t pool_get(void** block, size_t* held, size_t bytes, int device) {
     if (ec != hipSuccess) return ec;
     if (current != device) return hipErrorInvalidDevice;   // (hipMalloc's block would be another device's)
     const size_t cls = size_class(bytes);
+    *block = nullptr;
     *held = bytes;
     Pools& G = pools();
     DevicePool* P = G.of(device);
     if (!P || cls > kPoolBlock) return device_alloc(block, bytes);
-    {
+    int fresh = 0;
+    bool due = false;
+    uint64_t given = 0;
+    auto take = [&]() {
         std::lock_guard<std::mutex> lk(G.mu);
-        auto it = P->blocks.lower_bound(cls);
-        if (it != P->blocks.end() && it->first <= size_class(cls + 1)) {
-            *block = it->second.block;
-            *held = it->first;
-            P->held -= it->first;
-            P->blocks.erase(it);
-            return hipSuccess;
+        fresh = P->take(cls, block, held, &due);
+        given = P->given;
+        return *block != nullptr;
+    };
+    auto take_after_wait = [&]() {
+        if (fresh == 0 || !wait_device(device)) return false;
+        {
+            std::lock_guard<std::mutex> lk(G.mu);
+            P->done = std::max(P->done, given);
         }
-    }
-    hipError_t e = hipMalloc(block, cls);
+        return take();
+    };
+    if (take()) return hipSuccess;
+    if (due && take_after_wait()) return hipSuccess;
+    const hipError_t e = hipMalloc(block, cls);
     if (e == hipSuccess) *held = cls;
     if (e != hipErrorOutOfMemory) return e;
     (void)hipGetLastError();
+    if (take_after_wait()) return hipSuccess;
     return device_alloc(block, bytes);           // without the class's rounding
 }
 
 // (noexcept: plans give their blocks back in their destructor)
-void pool_put(void* block, size_t held, int device, bool waited) noexcept {
+void pool_put(void* block, size_t held, int device) noexcept {
     Pools& G = pools();
     std::lock_guard<std::mutex> lk(G.mu);
     DevicePool* P = G.of(device);
-    // (a block smaller than its class serves no other; hipFree waits by itself, or fails
-    // as the wait did: then the block is lost, not shared)
-    bool keep = P && waited && held <= kPoolBlock && size_class(held) == held && P->maps != 0;
+    // (a block smaller than its class serves no other; hipFree waits for the device by
+    // itself, or fails: then the block is lost, not shared)
+    bool keep = P && held <= kPoolBlock && size_class(held) == held && P->maps != 0;
     if (keep) {
         P->make_room(held);
         try {
-            P->blocks.emplace(held, DevicePool::Held{block, P->given++});
+            P->blocks.emplace(held, DevicePool::Held{block, P->given});
+            ++P->given;
             P->held += held;
         } catch (const std::bad_alloc&) {
             keep = false;
@@ -512,12 +553,17 @@ void pool_put(void* block, size_t held, int device, bool waited) noexcept {
     if (!keep && hipFree(block) != hipSuccess) (void)hipGetLastError();
 }
 
-bool sync_device(int device) {
+// hipFree waits for the device's work on every stream as hipDeviceSynchronize does,
+// and unlike it also while a stream is captured in relaxed mode, whose capture the
+// latter would end. A small block costs 0.7 us where there is nothing to wait for.
+bool wait_device(int device) noexcept {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return false;
     if (dev != device && hipSetDevice(device) != hipSuccess) return false;
-    const bool waited = hipDeviceSynchronize() == hipSuccess;
-    if (!waited) (void)hipGetLastError();          // (the next launch would report it)
+    void* p = nullptr;
+    const hipError_t e = hipMalloc(&p, 64);
+    const bool waited = (e == hipSuccess ? hipFree(p) : e == hipErrorOutOfMemory ? hipDeviceSynchronize() : e) == hipSuccess;
+    if (e != hipSuccess || !waited) (void)hipGetLastError();     // (the next launch would report it)
     if (dev != device) (void)hipSetDevice(dev);
     return waited;
 }
@@ -986,7 +1032,7 @@ extern "C" int mg_tree_upload(mg_map map, const float* pos_m, const int32_t* par
                     hipGetErrorString(e));
     rc = finish_upload(map, H, sensor, (hipStream_t)hip_stream, block, true, out);
     if (rc != MG_OK)
-        mgb::pool_put(block, held, dev, mgb::sync_device(dev));
+        mgb::pool_put(block, held, dev);
     else
         (*out)->held = held;
     return rc;
@@ -994,12 +1040,10 @@ extern "C" int mg_tree_upload(mg_map map, const float* pos_m, const int32_t* par
 
 extern "C" int mg_tree_destroy(mg_tree t) {
     if (!t) return fail(MG_E_INVALID, "tree is NULL");
-    // (work on the tree may still be queued on any stream)
-    const bool waited = t->owns_block && mgb::sync_device(t->device);
     mgb::forget_tree(t);
     mgb::forget_interval(t);
     mgb::forget_exact(t);
-    if (t->owns_block) mgb::pool_put(t->block, t->held, t->device, waited);
+    if (t->owns_block) mgb::pool_put(t->block, t->held, t->device);    // (work on it may still be queued)
     release_sensor(t->sensor);
     t->map->trees--;
     delete t;

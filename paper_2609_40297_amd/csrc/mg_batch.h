@@ -50,12 +50,11 @@ hipError_t device_alloc(T** p, size_t bytes) {
 // Device blocks of trees and launch plans (mg_api.hip): kept when given back, up
 // to a bound, until the device's last map is destroyed. pool_get is for the
 // current device and says how many bytes it gave (held), which pool_put is told.
-// `waited`: the device has finished every use of the block (sync_device says
-// whether its wait succeeded; under a stream capture it fails); a block without
-// that is freed, never handed out again.
+// Work that uses a block may still be queued when it is given back: it is handed
+// out again only after a wait for the device that succeeded.
 hipError_t pool_get(void** block, size_t* held, size_t bytes, int device);
-void pool_put(void* block, size_t held, int device, bool waited) noexcept;
-bool sync_device(int device);
+void pool_put(void* block, size_t held, int device) noexcept;
+bool wait_device(int device) noexcept;     // whether all its work so far has finished (it fails under most stream captures)
 void forget_tree(mg_tree t);               // mg_batch.hip: drop cached launch plans that use t
 void forget_interval(mg_tree t);           // mg_interval.hip: free t's interval-mode buffers
 void forget_exact(mg_tree t);              // mg_exact.hip: free t's sets

@@ -64,10 +64,12 @@ struct Plan {
     uint32_t* psync = nullptr;
     uint32_t* h_abort = nullptr;
     ~Plan() {
-        const bool waited = block && mgb::sync_device(device);     // its launches may still be queued
-        if (exec) (void)hipGraphExecDestroy(exec);
+        if (exec) {
+            (void)mgb::wait_device(device);        // it may still run
+            (void)hipGraphExecDestroy(exec);
+        }
         if (graph) (void)hipGraphDestroy(graph);
-        if (block) mgb::pool_put(block, held, device, waited);
+        if (block) mgb::pool_put(block, held, device);     // (its launches may still be queued)
         if (h_abort) (void)hipHostFree(h_abort);
     }
 };
@@ -595,11 +597,8 @@ int configure(Plan& P, const BatchOut& out, hipStream_t s) {
 namespace mgb {
 void forget_tree(mg_tree t) {
     std::lock_guard<std::mutex> lk(g_mu);
-    bool any = false;
     for (auto it = g_plans.begin(); it != g_plans.end();) {
         if (std::find(it->first.begin(), it->first.end(), t) != it->first.end()) {
-            if (!any) (void)hipDeviceSynchronize();      // launches of the plan may still be queued
-            any = true;
             it = g_plans.erase(it);
         } else {
             ++it;

@@ -15,6 +15,7 @@ struct Dim3 {
     uint32_t x, y, z;
 };
 
+constexpr size_t kSmall = 256;     // (smaller blocks are not counted: the library waits by freeing one)
 enum { kOk = 0, kInvalid = 1, kOutOfMemory = 2, kInvalidDevice = 101, kCapture = 900, kLaunch = 719 };
 
 namespace {
@@ -30,7 +31,8 @@ std::map<const void*, std::string>* g_names = new std::map<const void*, std::str
 thread_local int t_device = 0;
 thread_local int t_last = kOk;
 size_t g_limit[2] = {SIZE_MAX, SIZE_MAX}, g_live[2] = {0, 0};
-int64_t g_mallocs = 0, g_frees = 0, g_syncs = 0, g_dirty = 0;
+int64_t g_mallocs = 0, g_frees = 0, g_waits = 0, g_dirty = 0;
+void* g_uploaded = nullptr;            // destination of the last copy from the host
 int g_fail_sync = 0, g_fail_nth = 0;
 char g_fail_name[64] = "";
 thread_local int t_fail_new = 0;
@@ -92,6 +94,8 @@ size_t fake_live(int dev) { return g_live[dev]; }
 int64_t fake_mallocs() { return g_mallocs; }
 int64_t fake_frees() { return g_frees; }
 int64_t fake_dirty() { return g_dirty; }
+int64_t fake_waits() { return g_waits; }                    // waits for a device that succeeded (frees among them)
+void* fake_last_block() { return g_uploaded; }
 void fake_fail_sync(int on) { g_fail_sync = on; }
 void fake_fail_kernel(const char* name, int nth) {
     snprintf(g_fail_name, sizeof(g_fail_name), "%s", name);
@@ -125,7 +129,7 @@ int hipMalloc(void** p, size_t bytes) {
     (*g_blocks)[*p] = Block{t_device, bytes};
     t_fail_new = fail;
     g_live[t_device] += bytes;
-    ++g_mallocs;
+    g_mallocs += bytes > kSmall;
     return kOk;
 }
 int hipFree(void* p) {
@@ -135,15 +139,20 @@ int hipFree(void* p) {
     if (b == g_blocks->end()) return set(kInvalid);
     if (g_fail_sync) return set(kCapture);
     g_live[b->second.device] -= b->second.bytes;
+    g_frees += b->second.bytes > kSmall;
+    ++g_waits;
     g_blocks->erase(b);
     free(p);
-    ++g_frees;
     return kOk;
 }
 int hipHostMalloc(void** p, size_t bytes, unsigned) { *p = calloc(bytes ? bytes : 1, 1); return kOk; }
 int hipHostFree(void* p) { free(p); return kOk; }
 int hipMemcpy(void* d, const void* s, size_t n, int) { memcpy(d, s, n); return kOk; }
-int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) { memcpy(d, s, n); return kOk; }
+int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void*) {
+    memcpy(d, s, n);
+    if (kind == 1) g_uploaded = d;
+    return kOk;
+}
 int hipGetSymbolAddress(void** p, const void*) {
     static void* scratch[2] = {};
     if (!scratch[t_device]) scratch[t_device] = calloc(17u << 20, 1);
@@ -155,7 +164,7 @@ int hipGetSymbolAddress(void** p, const void*) {
 int hipGetDevice(int* d) { *d = t_device; return kOk; }
 int hipSetDevice(int d) { if (d < 0 || d > 1) return set(kInvalidDevice); t_device = d; return kOk; }
 int hipDeviceGetAttribute(int* v, int, int) { *v = 65536; return kOk; }
-int hipDeviceSynchronize() { ++g_syncs; return g_fail_sync ? set(kCapture) : kOk; }
+int hipDeviceSynchronize() { if (g_fail_sync) return set(kCapture); ++g_waits; return kOk; }
 int hipGetLastError() { const int e = t_last; t_last = kOk; return e; }
 const char* hipGetErrorString(int e) { return e == kOutOfMemory ? "out of memory" : (e == kOk ? "no error" : "an error"); }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 1; return kOk; }

@@ -17,8 +17,9 @@ import numpy as np
 F = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
 for f in ("fake_live", "fake_held"):
     getattr(F, f).restype = C.c_size_t
-for f in ("fake_mallocs", "fake_frees", "fake_dirty"):
+for f in ("fake_mallocs", "fake_frees", "fake_dirty", "fake_waits"):
     getattr(F, f).restype = C.c_int64
+F.fake_last_block.restype = C.c_void_p
 F.fake_limit.argtypes = [C.c_int, C.c_size_t]
 F.fake_held.argtypes = [C.c_int, C.c_size_t]
 F.fake_device_of.argtypes = [C.c_void_p]

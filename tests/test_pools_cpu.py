@@ -34,25 +34,49 @@ assert F.fake_live(0) > before and F.fake_live(1) == 0
 
 
 def test_a_block_whose_use_could_not_be_waited_for_is_not_given_to_the_next_tree():
-    """A tree and its plan dropped while the device cannot be waited for (a stream is being captured): work
-    on their blocks may still be queued, so no later tree or plan gets them."""
+    """Trees and their plans dropped, then others made while the device cannot be waited for (a stream is
+    being captured): work on the blocks given back may still be queued, so none is handed out."""
     check("""
 m = new_map()
 g, y = Out(64), Out(64)
-t = new_tree(m, 30)
-mg.mg_eval_marginal_batch([t], g, y, stream=0)
-F.fake_fail_sync(1)
-mg.mg_tree_destroy(t)
-F.fake_fail_sync(0)
+def replan():
+    t = new_tree(m, 30)
+    mg.mg_eval_marginal_batch([t], g, y, stream=0)
+    return t
+def drop(t):
+    F.fake_fail_sync(1)                  # (and dropping waits for nothing)
+    mg.mg_tree_destroy(t)
+    F.fake_fail_sync(0)
+first = [replan() for _ in range(3)]
+[drop(t) for t in first]
 before = F.fake_mallocs()
-t = new_tree(m, 30)
-assert F.fake_mallocs() == before + 1
-mg.mg_eval_marginal_batch([t], g, y, stream=0)
+F.fake_fail_sync(1)
+t = replan()
 assert F.fake_mallocs() == before + 2
-mg.mg_tree_destroy(t)
-t = new_tree(m, 30)                     # (with a wait that succeeds the blocks are reused)
-mg.mg_eval_marginal_batch([t], g, y, stream=0)
+F.fake_fail_sync(0)
+drop(t)
+for _ in range(5):                       # (with waits that succeed the blocks are reused)
+    drop(replan())
 assert F.fake_mallocs() == before + 2
+""")
+
+
+def test_a_block_is_waited_for_before_it_is_handed_out_again():
+    """Every block that a tree gets has either never been used, or the device has been waited for since it
+    was given back; and a wait serves more than one replan."""
+    check("""
+m = new_map()
+given, waits, reused = {}, 0, 0
+for k in range(24):
+    t = new_tree(m, 30)
+    b = F.fake_last_block()
+    waits = F.fake_waits()
+    if b in given:
+        reused += 1
+        assert waits > given[b], k
+    mg.mg_tree_destroy(t)
+    given[b] = F.fake_waits()
+assert reused >= 20 and F.fake_waits() <= 13
 """)
 
 
@@ -137,7 +161,7 @@ assert F.fake_mallocs() == before
 def test_a_tree_takes_a_block_of_the_next_size():
     check("""
 m = new_map()
-mg.mg_tree_destroy(new_tree(m, 10000))
+[mg.mg_tree_destroy(t) for t in [new_tree(m, 10000), new_tree(m, 10000)]]
 before = F.fake_mallocs()
 for n in (9800, 9400, 9800, 10000):       # (the classes are 6 to 12 % apart)
     mg.mg_tree_destroy(new_tree(m, n))
