@@ -142,6 +142,9 @@ int mg_map_read_marked(mg_map map, void* hip_stream, uint8_t* bytes);
 int mg_tree_upload(mg_map map, const float* pos_m, const int32_t* parent, int32_t n,
                    const mg_sensor* sensor, void* hip_stream, mg_tree* out);
 
+/* Gives the tree's memory back (to the library, for later trees: it is used again
+ * once the device has finished the work already enqueued). Waits for nothing, except
+ * where the tree has interval-mode buffers, sets or a plan with a graph to free. */
 int mg_tree_destroy(mg_tree tree);
 
 /* Number of nodes and depth-buffer size (n_el * w_buf) of a tree; -1 on a NULL handle. */

@@ -385,8 +385,8 @@ size_t size_class(size_t bytes) {
 // Blocks given back by destroyed trees and plans, for the next ones: a replan
 // uploads a tree, evaluates it and drops it, and a hipMalloc and hipFree of tens
 // of megabytes, and rebuilding its sensor's tables, took longer than its host
-// work (500 nodes, 70 MB: upload 966 -> 38 us with blocks and tables kept and one
-// copy instead of ten, drop 391 -> 82 us). Per device, at most kPoolCount blocks of
+// work (500 nodes, 70 MB, a replan: upload 950 -> 130 us with blocks and tables kept
+// and one copy instead of ten, its waits among them, drop 375 -> 1.5 us). Per device, at most kPoolCount blocks of
 // at most kPoolBlock bytes, kPoolHeld bytes in all, those given back longest ago
 // freed first; a block serves its own size class and the next smaller one. Giving a
 // block back waits for nothing; it is handed out again after a wait for the device
